@@ -2,8 +2,8 @@
 
 Default workload (the headline `value`): exponential window, 1 frequency
 bin, 5000 slots of T_sft = 1800 s (about 104 days, 15% gaps), 1000 t0 values
-at T_sft spacing by 1000 tau values from 2 T_sft to 30 days, FP32 data sums
-with FP64 antenna sums (the plain method).  One step computes the full 2F
+at T_sft spacing by 1000 tau values from 2 T_sft to 30 days, FP32 maps with
+FP64 sums (windows sliding along t0).  One step computes the full 2F
 map (written to device memory) and the per-bin max 2F, argmax and logB, with
 the atoms already resident on the device.
 
@@ -14,7 +14,7 @@ eq. Nsums-exp, counted over present SFTs).
 The same JSON line also carries, unless --no-extras:
   exp_256_bins   256 bins sharing one set of antenna atoms, split hi + lo
                  half-precision (f16x3) and bf16 (bf16x3) parts on matrix
-                 cores against the plain FP32 form, each with its 2F error
+                 cores against FP32 (sliding windows), each with its 2F error
                  against the oracle on sampled cells;
   uneven_batch   64 uneven candidates as one batch (one captured graph, one
                  persistent fused launch, the matrix-core launch) in FP32,
@@ -56,7 +56,7 @@ PEAK_ALU_TFLOPS = 78.6    # non-packed FP32 and FP64 vector FMA, 256 CU x 64 lan
 PEAK_HBM_GBS = 8000.0
 PEAK_BF16_TFLOPS = 2500.0  # dense bf16 and fp16 matrix cores
 MATRIX_PRECS = ("f16x3", "bf16x3")
-DTYPES = {"fp32": "f32+f64", "fp64": "f64", "bf16x3": "bf16x3(f32 acc)+f64", "f16x3": "f16x3(f32 acc)+f64",
+DTYPES = {"fp32": "f64", "fp64": "f64", "bf16x3": "bf16x3(f32 acc)+f64", "f16x3": "f16x3(f32 acc)+f64",
           "recur64": "f64"}
 
 
@@ -345,23 +345,28 @@ def sampled_error(twoF, res, atoms, win, n_cells: int, seed: int):
     return float((np.abs(got - ref) / np.maximum(np.abs(ref), 1.0)).max()), int(mi.shape[0])
 
 
+def slide_flops(atoms, win):
+    """FP64 flops of an exponential map by sliding windows: per tau and
+    channel one FMA per slot for the anchors and one in and one out of the
+    window per slot that the rows cover, per cell D and its inverse (about
+    12), and per cell and bin 2F and its reduction (about 24)."""
+    ch = 3 + 4 * atoms.n_bins
+    rows = float(win.t0[-1] - win.t0[0]) / atoms.t_sft + 1.0
+    return win.n_tau * 2.0 * ch * (atoms.n_slots + 2.0 * min(rows, atoms.n_slots)) \
+        + win.n_t0 * win.n_tau * (24.0 * atoms.n_bins + 12.0)
+
+
 def roofline_for(atoms, win, prec, prof, workload):
     """Roofline of the dominant kernel of one map computation from the
     per-kernel HIP-event times of the timed steps."""
     mfma = win.kind == "exp" and prec in MATRIX_PRECS and prof["mfma"][0] > 0
-    recur = win.kind == "exp" and prec == "recur64" and prof["recur"][0] > 0
+    recur = win.kind == "exp" and prof["recur"][0] > 0
     dom = "mfma" if mfma else ("recur" if recur else ("exp" if win.kind == "exp" else "rect"))
     n_launch, k_ms = prof[dom]
     avg_ms = k_ms / max(n_launch, 1)
     present, _ = work_counts(atoms, win)
     if recur:
-        # FP64 flops of the recurrence: the boundary window per tau (w^2 and
-        # one FMA per antenna and data channel per slot), two passes per row
-        # of (scale + head FMA + tail FMA) per channel, and the finalize
-        # (about 30 flops per cell and bin)
-        ch = 3 + 4 * atoms.n_bins
-        band = np.minimum(-(-3 * win.tau // atoms.t_sft), atoms.n_slots)
-        flops = float((band * (1 + 2 * ch)).sum()) + win.n_tau * win.n_t0 * (2 * 5 * ch + 30 * atoms.n_bins)
+        flops = slide_flops(atoms, win)
         roof = {"bound": "alu", "achieved": flops / (avg_ms * 1e-3) / 1e12, "peak": PEAK_ALU_TFLOPS,
                 "unit": "TFLOP/s"}
     elif mfma:
@@ -390,7 +395,7 @@ def roofline_for(atoms, win, prec, prof, workload):
                 "unit": "GB/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
     roof["traffic"] = traffic_from_profile(workload, {"exp": "exp_valu", "rect": "rect",
-                                                      "mfma": "exp_mfma", "recur": "exp_recur"}[dom],
+                                                      "mfma": "exp_mfma", "recur": "slide"}[dom],
                                            prec if mfma else None)
     roof["kernel"] = dom
     roof["kernel_avg_ms"] = avg_ms
@@ -457,7 +462,7 @@ def bench_exp256(args, tf, torch):
     """256 frequency bins sharing one set of antenna atoms (2000 slots, 10%
     gaps, 500 x 500 grid, map written): the batched mixed-precision forms
     (split hi + lo half-precision or bf16 parts on matrix cores, FP32
-    accumulation, A/B/C/D in FP64) against the plain FP32 VALU form, each
+    accumulation, A/B/C/D in FP64) against FP32 (sliding windows), each
     with its largest 2F error against the FP64 oracle on sampled cells."""
     atoms, win = tfsynth.workload_exp_bins()
     present, slots = work_counts(atoms, win)
@@ -492,6 +497,7 @@ def bench_batch(args, tf, torch, prec):
     exp_present = exp_slots = rect_cells = 0
     abc_cells_sfts = 0   # A/B/C inside the fused kernel (not split-form or matrix-core maps)
     valu_present = 0     # exp cells*SFTs*bins summed on the VALU
+    slide = 0.0          # flops of the exponential maps by sliding windows
     mfma_present = 0     # exp cells*SFTs*bins on the matrix cores
     for a, w in cands:
         if w.kind == "exp":
@@ -500,8 +506,11 @@ def bench_batch(args, tf, torch, prec):
             exp_slots += sl
             mc = mfma_cells(a, w, prec) if prec in MATRIX_PRECS else 0
             mfma_present += mc
+            if prec not in MATRIX_PRECS:
+                slide += slide_flops(a, w)
+                continue
             valu_present += p - mc
-            if not split_form(a, w, "fp32" if prec in MATRIX_PRECS else prec) and mc == 0:
+            if not split_form(a, w, "fp32") and mc == 0:
                 abc_cells_sfts += p // a.n_bins
         else:
             rect_cells += w.n_t0 * w.n_tau * a.n_bins
@@ -587,6 +596,13 @@ def bench_batch(args, tf, torch, prec):
         out["roofline_fused"] = roof_f
         out["roofline_mfma"] = roof_m
         roof = roof_m if mfma_ms >= fused_ms else roof_f
+    if slide:
+        # the sliding maps' launches are most of the step: its flops over all of it
+        total = slide + 30.0 * rect_cells
+        roof = {"bound": "alu", "achieved": total / (st["last_ms"] * 1e-3) / 1e12, "peak": PEAK_ALU_TFLOPS,
+                "unit": "TFLOP/s", "kernel": "step", "kernel_avg_ms": st["last_ms"], "traffic": None}
+        roof["frac"] = roof["achieved"] / roof["peak"]
+        out["roofline_fused"] = roof_f
     out["roofline"] = roof
     batch.close()
     for aid in ids:

@@ -75,7 +75,14 @@ typedef enum {
 /*
  * Arithmetic of the windowed sums.  A, B, C, D and F are FP64 in every mode.
  *   FP64   : F_a, F_b sums in FP64.
- *   FP32   : F_a, F_b sums in FP32 (the paper's single precision).
+ *   FP32   : F_a, F_b sums in FP32 (the paper's single precision) or better.
+ *            Exponential windows in FP64, FP32 and RECUR64 are summed by
+ *            sliding windows along t0, in FP64: a cell costs the slots between
+ *            two t0 rows instead of its whole window.  Atoms with non-finite
+ *            values, or whose data spread over more than 2^20 between 64-slot
+ *            stretches, maps whose workspace the arena cannot hold, and maps
+ *            planned under an explicit tfstat_tiling_config are summed
+ *            directly in the named precision.
  *   BF16X3 : F_a, F_b sums on bf16 matrix cores with split hi + lo operands
  *            (three products: hi*hi + hi*lo + lo*hi) and FP32 accumulation
  *            (section 3, exponential case: every cell is one banded
@@ -101,12 +108,9 @@ typedef enum {
  *            matrix cores (shorter windows amplify the parts' rounding).
  *            Builds its own planes on first use (16 bytes per slot and bin;
  *            sets of 2 to 48 bins 32 more).
- *   RECUR64: exponential windows on a regular t0 grid whose step is a whole
- *            number of SFT slots (at most 64): every sum in FP64 by the exact
- *            recurrence of the window sums from one t0 to the next, O(1)
- *            per cell and channel instead of O(window length); windows
- *            holding fewer than two SFTs are summed directly.  Other grids
- *            run the FP64 direct sums.
+ *   RECUR64: exponential windows: every sum in FP64 by the exact recurrence
+ *            of the window sums from one t0 to the next (the sliding windows
+ *            above, whatever the tiling), on any t0 grid.
  * Rectangular windows use FP64 prefix sums in every mode.
  */
 typedef enum {
@@ -305,8 +309,10 @@ int tfstat_cancel(tfstat_ctx *ctx, tfstat_ticket t);
 int tfstat_serve_config(tfstat_ctx *ctx, int32_t max_batch);
 
 /*
- * Tiling of exponential-window maps (section 3: every cell sums its own
- * window).  The VALU sums take 64 t0 rows at a time.
+ * Tiling of the direct sums of exponential-window maps (section 3: every cell
+ * sums its own window).  Either value set here other than the default sends
+ * FP64 and FP32 exponential maps to the direct sums (see tfstat_precision).
+ * The VALU sums take 64 t0 rows at a time.
  *
  * Runs form.  When the rows of a tile start far apart in slot space (a t0
  * step of many SFTs), the union of their windows does not fit one
@@ -417,7 +423,7 @@ typedef enum {
     TFSTAT_K_MERGE = 5,       /* per-bin reduction merge */
     TFSTAT_K_MFMA = 6,        /* exponential F_a, F_b on matrix cores */
     TFSTAT_K_ABC = 7,         /* exponential A, B, C (FP64) */
-    TFSTAT_K_RECUR = 8,       /* exponential sums by the t0 recurrence */
+    TFSTAT_K_RECUR = 8,       /* exponential sums by sliding windows along t0 */
     TFSTAT_K_COUNT = 9
 } tfstat_kernel_kind;
 

@@ -1044,14 +1044,6 @@ __global__ __launch_bounds__(256) void weights_batch_kernel(WeightBatchParams p)
 }
 
 // ---------------------------------------------------------------------------
-// FP32 plane of the data atoms.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void build_x32_kernel(const double *x64, float *x32, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        x32[i] = (float)x64[i];
-}
-
-// ---------------------------------------------------------------------------
 // Exclusive prefix sums over slots (rectangular windows: section 3's running
 // sums turned into O(1) differences per cell), carried as unevaluated
 // double-double pairs so that a window's difference keeps full FP64 accuracy
@@ -1060,9 +1052,17 @@ __global__ __launch_bounds__(256) void build_x32_kernel(const double *x64, float
 // bin); group g's prefixes are laid out [g][K+1][8]: the four hi terms,
 // then the four lo terms, hi + lo = sum_{j<k} in[j][c], so that one window
 // end of one group is one contiguous 64-byte read.
-// Lane = channel, wave = slot segment.
+// Lane = channel, wave = kScanSlots consecutive slots held in registers,
+// workgroup = kScanBlock slots of 64 channels.  The chain of dependent
+// double-double sums bounds this, not its bytes, so the slots are spread over
+// workgroups: scan_totals_kernel sums every block, and a block of scan_kernel
+// adds the blocks before it to its own prefixes (256 bins x 2000 slots, both
+// launches: 161 us with one workgroup per 64 channels, 24 us now).  A job
+// without totals (tot null: the arena is short) runs its blocks one after the
+// other, with the same sums in the same order.
 // ---------------------------------------------------------------------------
 constexpr int kScanWaves = 16;
+constexpr int kScanSlots = kScanBlock / kScanWaves;
 
 struct DD {
     double h, l;
@@ -1086,72 +1086,97 @@ __device__ inline DD dd_add(DD x, DD y) {
     return DD{t.h, x.l + y.l + t.l};
 }
 
-__device__ __attribute__((always_inline)) inline void scan_chunk(const double *__restrict__ in,
-                                                                 int64_t stride, double *__restrict__ out,
-                                                                 int32_t K, int32_t C, int chunk,
-                                                                 DD (*tot)[64]) {
+// The wave's slots of block blk (zero past the end) and their sum.
+__device__ __attribute__((always_inline)) inline DD scan_load(const ScanJob &j, int blk, double *v) {
+    const int c = j.chunk * 64 + (threadIdx.x & 63);
+    const int k0 = blk * kScanBlock + (threadIdx.x >> 6) * kScanSlots;
+#pragma unroll
+    for (int u = 0; u < kScanSlots; ++u)
+        v[u] = c < j.C && k0 + u < j.K ? j.in[(size_t)(k0 + u) * j.stride + c] : 0.0;
+    DD sum{0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < kScanSlots; ++u) sum = dd_add(sum, v[u]);
+    return sum;
+}
+
+__device__ __attribute__((always_inline)) inline void scan_totals(const ScanJob &j, int blk, DD (*tot)[64]) {
+    const int lane = threadIdx.x & 63;
+    double v[kScanSlots];
+    tot[threadIdx.x >> 6][lane] = scan_load(j, blk, v);
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        DD run{0.0, 0.0};
+        for (int w = 0; w < kScanWaves; ++w) run = dd_add(run, tot[w][lane]);
+        j.tot[(size_t)blk * 64 + lane] = double2{run.h, run.l};
+    }
+}
+
+// Blocks [blk, end) one after the other.
+__device__ __attribute__((always_inline)) inline void scan_blocks(const ScanJob &j, int blk, int end, DD (*tot)[64]) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int c = chunk * 64 + lane;
-    const int seg = (K + kScanWaves - 1) / kScanWaves;
-    const int kb = min(K, wave * seg);
-    const int ke = min(K, kb + seg);
-    constexpr size_t row = 8;
-    double *o = out + (size_t)(c >> 2) * ((size_t)K + 1) * 8 + (c & 3);   // this channel's hi terms
-    // kSU slots' loads are issued before their (sequential) sums
-    constexpr int kSU = 8;
-    DD sum{0.0, 0.0};
-    if (c < C) {
-        int k = kb;
-        for (; k + kSU <= ke; k += kSU) {
-            double v[kSU];
-#pragma unroll
-            for (int u = 0; u < kSU; ++u) v[u] = in[(size_t)(k + u) * stride + c];
-#pragma unroll
-            for (int u = 0; u < kSU; ++u) sum = dd_add(sum, v[u]);
-        }
-        for (; k < ke; ++k) sum = dd_add(sum, in[(size_t)k * stride + c]);
+    const int c = j.chunk * 64 + lane;
+    double *o = j.out + (size_t)(c >> 2) * ((size_t)j.K + 1) * 8 + (c & 3);   // this channel's hi terms
+    if (blk == 0 && wave == 0 && c < j.C) {
+        o[0] = 0.0;
+        o[4] = 0.0;
     }
-    tot[wave][lane] = sum;
-    __syncthreads();
-    DD run{0.0, 0.0};
-    for (int w = 0; w < wave; ++w) run = dd_add(run, tot[w][lane]);
-    if (c < C) {
-        if (wave == 0) {
-            o[0] = 0.0;
-            o[4] = 0.0;
+    DD base{0.0, 0.0};   // the blocks before this one
+    for (int b = 0; b < blk; ++b) {
+        const double2 t = j.tot[(size_t)b * 64 + lane];
+        base = dd_add(base, DD{t.x, t.y});
+    }
+    for (; blk < end; ++blk) {
+        double v[kScanSlots];
+        const DD sum = scan_load(j, blk, v);
+        __syncthreads();   // every wave has read the previous block's sums
+        tot[wave][lane] = sum;
+        __syncthreads();
+        DD all{0.0, 0.0}, before{0.0, 0.0};
+        for (int w = 0; w < kScanWaves; ++w) {
+            if (w == wave) before = all;
+            all = dd_add(all, tot[w][lane]);
         }
-        int k = kb;
-        for (; k + kSU <= ke; k += kSU) {
-            double v[kSU];
+        DD run = dd_add(base, before);
+        const int k0 = blk * kScanBlock + wave * kScanSlots;
+        if (c < j.C) {
 #pragma unroll
-            for (int u = 0; u < kSU; ++u) v[u] = in[(size_t)(k + u) * stride + c];
-#pragma unroll
-            for (int u = 0; u < kSU; ++u) {
+            for (int u = 0; u < kScanSlots; ++u) {
                 run = dd_add(run, v[u]);
-                o[(size_t)(k + u + 1) * row] = run.h;
-                o[(size_t)(k + u + 1) * row + 4] = run.l;
+                if (k0 + u < j.K) {
+                    o[(size_t)(k0 + u + 1) * 8] = run.h;
+                    o[(size_t)(k0 + u + 1) * 8 + 4] = run.l;
+                }
             }
         }
-        for (; k < ke; ++k) {
-            run = dd_add(run, in[(size_t)k * stride + c]);
-            o[(size_t)(k + 1) * row] = run.h;
-            o[(size_t)(k + 1) * row + 4] = run.l;
-        }
+        base = dd_add(base, all);
     }
 }
 
-__global__ __launch_bounds__(kScanWaves * 64) void scan_kernel(const double *__restrict__ in,
-                                                               int64_t stride, double *__restrict__ out,
-                                                               int32_t K, int32_t C) {
-    __shared__ DD tot[kScanWaves][64];
-    scan_chunk(in, stride, out, K, C, blockIdx.x, tot);
+__device__ inline void scan_task(const ScanJob &j, int blk, bool totals, DD (*tot)[64]) {
+    if (totals)
+        scan_totals(j, blk, tot);
+    else
+        scan_blocks(j, blk, j.tot ? blk + 1 : (j.K + kScanBlock - 1) / kScanBlock, tot);
 }
 
-__global__ __launch_bounds__(kScanWaves * 64) void scan_batch_kernel(const ScanJob *jobs) {
+// One map: chunk 0 of the grid is the antenna's, the others the data's.
+__global__ __launch_bounds__(kScanWaves * 64) void scan_kernel(ScanJob abc, ScanJob x, int totals) {
+    __shared__ DD tot[kScanWaves][64];
+    ScanJob j = blockIdx.x == 0 ? abc : x;
+    if (blockIdx.x) {
+        j.chunk = blockIdx.x - 1;
+        if (j.tot) j.tot += (size_t)j.chunk * j.n_blk * 64;
+    }
+    scan_task(j, blockIdx.y, totals != 0, tot);
+}
+
+// Many maps: one job per (chunk, block).
+__global__ __launch_bounds__(kScanWaves * 64) void scan_batch_kernel(const ScanJob *jobs, int totals) {
     __shared__ DD tot[kScanWaves][64];
     const ScanJob j = jobs[blockIdx.x];
-    scan_chunk(j.in, j.stride, j.out, j.K, j.C, j.chunk, tot);
+    if (totals && j.blk + 1 >= j.n_blk) return;   // nothing follows the last block
+    scan_task(j, j.blk, totals != 0, tot);
 }
 
 // ---------------------------------------------------------------------------
@@ -1621,18 +1646,14 @@ hipError_t launch_weights(const WeightParams &p, int64_t max_per_block, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_build_x32(const double *x64, float *x32, int64_t n, hipStream_t s) {
-    int64_t g = (n + 255) / 256;
-    if (g < 1) g = 1;
-    if (g > 8192) g = 8192;
-    hipLaunchKernelGGL(build_x32_kernel, dim3((unsigned)g), dim3(256), 0, s, x64, x32, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_scan(const double *in, int64_t stride, double *out, int32_t K, int32_t C,
-                       hipStream_t s) {
-    hipLaunchKernelGGL(scan_kernel, dim3((unsigned)((C + 63) / 64)), dim3(kScanWaves * 64), 0, s,
-                       in, stride, out, K, C);
+hipError_t launch_scan(const ScanJob &abc, const ScanJob &x, hipStream_t s) {
+    const unsigned chunks = 1u + (unsigned)((x.C + 63) / 64);
+    const unsigned blocks = (unsigned)((x.K + kScanBlock - 1) / kScanBlock);
+    if (blocks > 65535u) return hipErrorInvalidValue;
+    const bool split = blocks > 1 && x.tot != nullptr;
+    if (split)
+        hipLaunchKernelGGL(scan_kernel, dim3(chunks, blocks - 1), dim3(kScanWaves * 64), 0, s, abc, x, 1);
+    hipLaunchKernelGGL(scan_kernel, dim3(chunks, split ? blocks : 1u), dim3(kScanWaves * 64), 0, s, abc, x, 0);
     return hipGetLastError();
 }
 
@@ -1662,9 +1683,10 @@ hipError_t launch_abc_batch(const AbcBatchParams &p, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_scan_batch(const ScanJob *jobs, int32_t n_jobs, hipStream_t s) {
+hipError_t launch_scan_batch(const ScanJob *jobs, int32_t n_jobs, int32_t split, hipStream_t s) {
     if (n_jobs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(scan_batch_kernel, dim3((unsigned)n_jobs), dim3(kScanWaves * 64), 0, s, jobs);
+    if (split) hipLaunchKernelGGL(scan_batch_kernel, dim3((unsigned)n_jobs), dim3(kScanWaves * 64), 0, s, jobs, 1);
+    hipLaunchKernelGGL(scan_batch_kernel, dim3((unsigned)n_jobs), dim3(kScanWaves * 64), 0, s, jobs, 0);
     return hipGetLastError();
 }
 

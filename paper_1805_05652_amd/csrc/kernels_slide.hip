@@ -1,0 +1,664 @@
+// Exponential windows by sliding sums (FP64).
+//
+// For one tau and one channel y (a^2, b^2, ab with u = e^(-2 T_sft / tau);
+// Re / Im of F_a, F_b of a bin with u = e^(-T_sft / tau)) the window of row m
+// holds the slots [lo, hi), lo = clamp(k0_m, 0, K), hi = clamp(k0_m + L_m, 0,
+// K), L_m = ceil((3 tau - delta_m) / T_sft) (section 2, eq. winexp), and its
+// sum normalised to slot lo is
+//   G_m = sum_{k in [lo, hi)} u^(k - lo) y_k.
+// The row's own scale e^(-(t_lo - t0_m) / tau), squared on A, B, C, cancels
+// in 2F = 2 (B |F_a|^2 + A |F_b|^2 - 2 C Re F_a F_b*) / D and in the
+// degenerate-window rule, so G is all a cell needs.  Going down the rows both
+// window ends move down: a slot entering at the front is G <- u G + y, a slot
+// leaving at the back is G <- G - u^(k - lo) y_k.  Section 3 finds no reuse
+// of the exponential sums across tau; along t0 there is one, and a cell costs
+// the slots between two rows instead of its whole window.
+//
+// Lane = tau, wave = 64 taus x BG bins x one segment of rows, from the
+// segment's last row down.  A front slot is the same in every lane (scalar
+// loads); a back slot is the lane's own (gathered from a stage in LDS, or
+// through the caches where the taus of a wave span too many slots).  A
+// segment starts from H(k) = sum_{j >= k} u^(j - k) y_j at its last row's two
+// ends, G = H(lo) - u^(hi - lo) H(hi); slide_anchor_kernel leaves H at every
+// range_len-th slot.
+//
+// Errors.  The factors are below one, so rounding errors fade with the
+// weights; what an earlier, stronger slot leaves behind is 2^-52 of it.  A
+// cell whose A or B is below 2^-13 of the largest slot's a^2 or b^2 (an empty
+// window, or one of weak SFTs only) is summed directly, so that D keeps at
+// least 38 bits relative to A B and the degenerate rule decides as on direct
+// sums.  Atoms with non-finite values or with 64-slot stretches far below
+// their column's largest value (atoms_kernel) keep the direct forms.
+#include "tfstat_device.h"
+
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+namespace tfs {
+
+namespace {
+
+template <typename T>
+using ConstParams = const __attribute__((address_space(4))) T;
+template <typename T>
+__device__ inline ConstParams<T> *const_ptr(const T *p) {
+    return reinterpret_cast<ConstParams<T> *>(reinterpret_cast<uintptr_t>(p));
+}
+
+// The lane's tau: decay per slot and 3 tau in slots (q) and seconds left (r).
+struct LaneTau {
+    double c;        // ln rho = -T_sft / tau
+    double rho, rho2;
+    int q, r;
+};
+
+// 3 tau = q T + r; q clamped so that k0 + q + 1 stays an int and still passes
+// every data end (k0 >= -2^30, K <= 2^28).
+__device__ inline void tau_qr(int64_t tau, int64_t T, int &q, int &r) {
+    constexpr int64_t kMaxQ = 1342177280;
+    const int64_t span = min(3 * tau, kMaxQ * T);
+    // quotient below 2^31 by one FP64 division, within one of the exact one
+    int64_t qq = (int64_t)((double)span / (double)T);
+    int64_t rr = span - qq * T;
+    if (rr < 0) {
+        --qq;
+        rr += T;
+    } else if (rr >= T) {
+        ++qq;
+        rr -= T;
+    }
+    q = (int)qq;
+    r = (int)rr;
+}
+
+__device__ inline LaneTau lane_tau(int64_t tau, int64_t T) {
+    LaneTau t;
+    t.c = -(double)T / (double)tau;
+    t.rho = exp(t.c);
+    t.rho2 = exp(2.0 * t.c);
+    tau_qr(tau, T, t.q, t.r);
+    return t;
+}
+
+__device__ inline int clamp_slot(int k, int K) { return min(max(k, 0), K); }
+// End slot of the window of row (k0, delta) for 3 tau = q T + r: slots
+// k0 .. k0 + L - 1 with L = q + (r > delta).
+__device__ inline int end_slot(int k0, int delta, int q, int r, int K) {
+    return clamp_slot(k0 + q + (r > delta ? 1 : 0), K);
+}
+
+// Channel sums of BG bins and the antenna.
+template <int BG>
+struct Sums {
+    double a[3];
+    double x[BG][4];
+    __device__ inline void zero() {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[c] = 0.0;
+#pragma unroll
+        for (int b = 0; b < BG; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[b][c] = 0.0;
+    }
+    // this <- (fa, fx) this + y
+    __device__ inline void shift(double fa, double fx, const Sums &y) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[c] = fma(fa, a[c], y.a[c]);
+#pragma unroll
+        for (int b = 0; b < BG; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[b][c] = fma(fx, x[b][c], y.x[b][c]);
+    }
+    // this <- this + (fa, fx) y
+    __device__ inline void add(double fa, double fx, const Sums &y) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[c] = fma(fa, y.a[c], a[c]);
+#pragma unroll
+        for (int b = 0; b < BG; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[b][c] = fma(fx, y.x[b][c], x[b][c]);
+    }
+    // channel c of 3 + 4 BG
+    __device__ inline double get(int c) const { return c < 3 ? a[c] : x[(c - 3) >> 2][(c - 3) & 3]; }
+    __device__ inline void set(int c, double v) {
+        if (c < 3) a[c] = v;
+        else x[(c - 3) >> 2][(c - 3) & 3] = v;
+    }
+};
+
+// Slot k (the same in every lane; scalar loads).  Bins past the last repeat it.
+template <int BG, typename PP>
+__device__ __attribute__((always_inline)) inline Sums<BG> uniform_slot(PP &p, int k, int bin0) {
+    Sums<BG> y;
+    ConstParams<double> *ab = const_ptr(p.abc) + (size_t)k * 4;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) y.a[c] = ab[c];
+#pragma unroll
+    for (int b = 0; b < BG; ++b) {
+        ConstParams<double> *x = const_ptr(p.x64) + ((size_t)k * p.n_bins + min(bin0 + b, p.n_bins - 1)) * 4;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) y.x[b][c] = x[c];
+    }
+    return y;
+}
+
+// Slots whose scalar loads are in flight together (38 scalar registers each
+// for four bins, 14 for one).
+template <int BG>
+constexpr int front_unroll() {
+    return BG == 1 ? 4 : 2;
+}
+
+// H at slot k taken down to slot lo, front slots added.
+template <int BG, int U, typename PP>
+__device__ __attribute__((always_inline)) inline void run_down(PP &p, const LaneTau &t, int bin0, int k, int lo,
+                                                               Sums<BG> &H) {
+#pragma unroll 1
+    for (; k > lo; k -= U) {
+        Sums<BG> y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) y[u] = uniform_slot<BG>(p, max(k - 1 - u, 0), bin0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k - 1 - u >= lo) H.shift(t.rho2, t.rho, y[u]);
+    }
+}
+
+// Slots [kbeg, kend) that the windows of a tau tile's segment heads reach;
+// ranges of range_len slots from kbeg.
+struct TileSpan {
+    int kbeg, kend;
+};
+template <typename PP>
+__device__ inline TileSpan tile_span(PP &p, int tt) {
+    ConstParams<RowPlan> *rows = const_ptr(p.rows);
+    TileSpan s;
+    const int m0 = min(p.seg_rows, p.n_t0) - 1;
+    s.kbeg = clamp_slot(rows[m0].k0, p.K);
+    int q, r;
+    tau_qr(const_ptr(p.tau)[min(tt * 64 + 63, p.n_tau - 1)], p.t_sft, q, r);
+    s.kend = max(end_slot(rows[p.n_t0 - 1].k0, rows[p.n_t0 - 1].delta, q, r, p.K), s.kbeg);
+    return s;
+}
+
+// ---------------------------------------------------------------------------
+// Anchors.  Workgroup = one (tau tile, bin group) column x kSlideWaves
+// consecutive ranges (a super-range), wave = range: its sum T = H over its own
+// slots, then by a Horner step over the later ranges of the workgroup the
+// local H at its end (anc) and, for the whole super-range, the sum at its
+// start (sup).
+// ---------------------------------------------------------------------------
+template <int BG>
+struct AnchorSmem {
+    double tot[kSlideWaves][3 + 4 * BG][64];
+};
+
+template <int BG, typename PP>
+__device__ __attribute__((always_inline)) inline void slide_anchor(PP &p, char *smem, int col, int sup) {
+    constexpr int CH = 3 + 4 * BG;
+    AnchorSmem<BG> &sm = *reinterpret_cast<AnchorSmem<BG> *>(smem);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tt = col / p.n_bg;
+    const int bin0 = (col - tt * p.n_bg) * BG;
+    const TileSpan sp = tile_span(p, tt);
+    const int g0 = sup * kSlideWaves;
+    if (sp.kbeg + g0 * p.range_len >= sp.kend) return;   // the whole workgroup: no slots
+    const LaneTau t = lane_tau(p.tau[min(tt * 64 + lane, p.n_tau - 1)], p.t_sft);
+    const int kb = sp.kbeg + (g0 + wave) * p.range_len;
+    const int ke = min(kb + p.range_len, sp.kend);
+    Sums<BG> H;
+    H.zero();
+    run_down<BG, front_unroll<BG>()>(p, t, bin0, ke, kb, H);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) sm.tot[wave][c][lane] = H.get(c);
+    __syncthreads();
+    // ranges after this one, from the last: full ranges decay by rho^range_len
+    // (a short or empty one is last, where the sum so far is zero)
+    const double f = exp(t.c * (double)p.range_len), f2 = f * f;
+    Sums<BG> E;
+    E.zero();
+    for (int w = kSlideWaves - 1; w > wave; --w) {
+        Sums<BG> y;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) y.set(c, sm.tot[w][c][lane]);
+        E.shift(f2, f, y);
+    }
+    double *o = p.anc + (((size_t)col * p.n_range + g0 + wave) * CH) * 64 + lane;
+    if (kb < ke) {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) o[(size_t)c * 64] = E.get(c);
+    }
+    if (wave == 0) {
+        const double l = exp(t.c * (double)(ke - kb)), l2 = l * l;
+        E.shift(l2, l, H);
+        double *s = p.sup + (((size_t)col * p.n_sup + sup) * CH) * 64 + lane;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) s[(size_t)c * 64] = E.get(c);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Rows.
+// ---------------------------------------------------------------------------
+// Back slots of a workgroup's four segments, staged once; entry kTailCap is
+// zero (lanes without a slot to drop read it).
+template <int BG>
+constexpr int tail_cap() {
+    return BG == 1 ? 1023 : BG == 2 ? 767 : 607;
+}
+template <int BG>
+struct RowsSmem {
+    double2 ab[tail_cap<BG>() + 1];
+    double c[tail_cap<BG>() + 1];
+    float4 x[BG][tail_cap<BG>() + 1];
+};
+
+template <int BG, typename PP>
+__device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *smem, int col, int quad) {
+    constexpr int CH = 3 + 4 * BG;
+    constexpr int kCap = tail_cap<BG>();
+    constexpr int kU = BG == 1 ? 4 : BG == 2 ? 2 : 1;   // slots in flight
+    RowsSmem<BG> &sm = *reinterpret_cast<RowsSmem<BG> *>(smem);
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tt = col / p.n_bg;
+    const int bin0 = (col - tt * p.n_bg) * BG;
+    const int n_bins = p.n_bins;
+    const int K = p.K;
+    const int RL = p.range_len;
+    ConstParams<RowPlan> *rows = const_ptr(p.rows);
+    const TileSpan sp = tile_span(p, tt);
+    const int n = tt * 64 + lane;
+    const bool n_ok = n < p.n_tau;
+    const LaneTau t = lane_tau(p.tau[min(n, p.n_tau - 1)], p.t_sft);
+
+    // stage the back slots the four segments drop, and those between their
+    // last ends and the next range boundary
+    const int s0 = quad * 4;
+    int w_lo, w_hi;
+    {
+        const int m_a = s0 * p.seg_rows, m_b = min((s0 + 4) * p.seg_rows, p.n_t0) - 1;
+        int q, r;
+        tau_qr(const_ptr(p.tau)[tt * 64], p.t_sft, q, r);
+        w_lo = end_slot(rows[m_a].k0, rows[m_a].delta, q, r, K);
+        tau_qr(const_ptr(p.tau)[min(tt * 64 + 63, p.n_tau - 1)], p.t_sft, q, r);
+        w_hi = max(end_slot(rows[m_b].k0, rows[m_b].delta, q, r, K), sp.kbeg);
+        w_hi = min(sp.kbeg + (w_hi - sp.kbeg + RL - 1) / RL * RL, sp.kend);
+    }
+    const int n_w = w_hi - w_lo;
+    const bool staged = p.exact32 && n_w <= kCap;
+    if (staged) {
+        for (int i = tid; i < n_w; i += 256) {
+            const double *ab = p.abc + (size_t)(w_lo + i) * 4;
+            sm.ab[i] = *reinterpret_cast<const double2 *>(ab);
+            sm.c[i] = ab[2];
+#pragma unroll
+            for (int b = 0; b < BG; ++b)
+                sm.x[b][i] = *reinterpret_cast<const float4 *>(
+                    p.x32 + ((size_t)(w_lo + i) * n_bins + min(bin0 + b, n_bins - 1)) * 4);
+        }
+        if (tid == 0) {
+            sm.ab[kCap] = double2{0.0, 0.0};
+            sm.c[kCap] = 0.0;
+#pragma unroll
+            for (int b = 0; b < BG; ++b) sm.x[b][kCap] = float4{0.f, 0.f, 0.f, 0.f};
+        }
+        __syncthreads();
+    }
+    const int seg = s0 + wave;
+    if (seg >= p.n_seg) return;
+
+    // the lane's back slot k, zero where !on
+    auto lane_slot = [&](int k, bool on) {
+        Sums<BG> y;
+        if (staged) {
+            const int i = on ? k - w_lo : kCap;
+            const double2 ab = sm.ab[i];
+            y.a[0] = ab.x;
+            y.a[1] = ab.y;
+            y.a[2] = sm.c[i];
+#pragma unroll
+            for (int b = 0; b < BG; ++b) {
+                const float4 v = sm.x[b][i];
+                y.x[b][0] = v.x;
+                y.x[b][1] = v.y;
+                y.x[b][2] = v.z;
+                y.x[b][3] = v.w;
+            }
+        } else {
+            const size_t kk = on ? k : K;   // row K is zero
+            const double2 ab = *reinterpret_cast<const double2 *>(p.abc + kk * 4);
+            y.a[0] = ab.x;
+            y.a[1] = ab.y;
+            y.a[2] = p.abc[kk * 4 + 2];
+#pragma unroll
+            for (int b = 0; b < BG; ++b) {
+                const double *x = p.x64 + (kk * n_bins + min(bin0 + b, n_bins - 1)) * 4;
+                const double2 u = *reinterpret_cast<const double2 *>(x);
+                const double2 v = *reinterpret_cast<const double2 *>(x + 2);
+                y.x[b][0] = u.x;
+                y.x[b][1] = u.y;
+                y.x[b][2] = v.x;
+                y.x[b][3] = v.y;
+            }
+        }
+        return y;
+    };
+    const double *anc = p.anc + ((size_t)col * p.n_range * CH) * 64 + lane;
+    const double *sup = p.sup + ((size_t)col * p.n_sup * CH) * 64 + lane;
+    const int n_range = (sp.kend - sp.kbeg + RL - 1) / RL;
+    const int n_sup = (n_range + kSlideWaves - 1) / kSlideWaves;
+    const double fsup = exp(t.c * (double)(kSlideWaves * RL));   // decay of a whole super-range
+    // H at the first range end at or after slot k (kbeg <= k < kend; lanes with
+    // !on get zero), and that end
+    auto range_end = [&](int k, bool on, Sums<BG> &H) {
+        const int g = on ? max((k - sp.kbeg + RL - 1) / RL - 1, 0) : n_range - 1;
+        const int u = g / kSlideWaves;
+        H.zero();
+        // (a short super-range is the last: nothing comes after it)
+#pragma unroll 1
+        for (int v = n_sup - 1; __any(v > u); v -= kU) {
+            Sums<BG> y[kU];
+#pragma unroll
+            for (int i = 0; i < kU; ++i)
+#pragma unroll
+                for (int c = 0; c < CH; ++c) y[i].set(c, sup[((size_t)max(v - i, 0) * CH + c) * 64]);
+#pragma unroll
+            for (int i = 0; i < kU; ++i)
+                if (v - i > u) H.shift(fsup * fsup, fsup, y[i]);
+        }
+        const int ge = min(sp.kbeg + (g + 1) * RL, sp.kend);
+        const int ue = min(sp.kbeg + (u + 1) * kSlideWaves * RL, sp.kend);
+        const double f = exp(t.c * (double)(ue - ge)), f2 = f * f;
+        Sums<BG> y;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) y.set(c, anc[((size_t)g * CH + c) * 64]);
+        H.shift(f2, f, y);
+        return ge;
+    };
+
+    const int m_lo = seg * p.seg_rows;
+    int m = min(m_lo + p.seg_rows, p.n_t0) - 1;
+    int k0 = rows[m].k0, delta = rows[m].delta;
+    int lo = clamp_slot(k0, K);
+    int hi = max(end_slot(k0, delta, t.q, t.r, K), lo);
+    Sums<BG> G;
+    G.zero();
+    if (__any(hi > lo)) {
+        Sums<BG> H;
+        // G = H(lo) - rho^(hi - lo) H(hi)
+        const bool back = hi > lo && hi < sp.kend;
+        if (__any(back)) {
+            int k = range_end(hi, back, H);
+#pragma unroll 1
+            for (; __any(back && k > hi); k -= kU) {
+                Sums<BG> y[kU];
+#pragma unroll
+                for (int u = 0; u < kU; ++u) y[u] = lane_slot(k - 1 - u, back && k - 1 - u >= hi);
+#pragma unroll
+                for (int u = 0; u < kU; ++u) {
+                    const bool on = back && k - 1 - u >= hi;
+                    H.shift(on ? t.rho2 : 1.0, on ? t.rho : 1.0, y[u]);
+                }
+            }
+            const double w = back ? -exp(t.c * (double)(hi - lo)) : 0.0;
+            const double w2 = -w * w;
+            G.add(w2, w, H);
+        }
+        int k = range_end(lo, true, H);
+        k = __builtin_amdgcn_readfirstlane(k);
+        run_down<BG, kU>(p, t, bin0, k, lo, H);
+        const double in = hi > lo ? 1.0 : 0.0;
+        G.add(in, in, H);
+    }
+    // rho^q and rho^(q + 1): weights of the first slot past a window
+    const double wq = exp(t.c * (double)t.q), wq1 = wq * t.rho;
+    const double ga = p.guard_a, gb = p.guard_b;
+
+    double fm[BG], fs[BG];
+    int im[BG];
+#pragma unroll
+    for (int b = 0; b < BG; ++b) {
+        fm[b] = -INFINITY;
+        fs[b] = 0.0;
+        im[b] = 0;
+    }
+#pragma unroll 1
+    for (;;) {
+        // the cell (m, n)
+        auto cell = [&](const Sums<BG> &S) {
+            const double A = S.a[0], B = S.a[1], C = S.a[2];
+            const double D = A * B - C * C;
+            const double kD = hi > lo && D > kDegenerateRtol * A * B ? 2.0 / D : 0.0;
+            const double kA = kD * A, kB = kD * B, kC = 2.0 * kD * C;
+#pragma unroll
+            for (int b = 0; b < BG; ++b) {
+                const double *f = S.x[b];
+                const double v = kB * (f[0] * f[0] + f[1] * f[1]) + kA * (f[2] * f[2] + f[3] * f[3]) -
+                                 kC * (f[0] * f[2] + f[1] * f[3]);
+                if (p.twoF && n_ok && bin0 + b < n_bins)
+                    p.twoF[((size_t)(bin0 + b) * p.n_t0 + m) * p.n_tau + n] = (float)v;
+                // running maximum (the earlier row on a tie) and sum of exp(F - max)
+                const double F = 0.5 * v;
+                const double d = F - fm[b];
+                const bool up = d >= 0.0;
+                const double e = (double)__expf(-(float)fabs(d));
+                fs[b] = up ? fma(fs[b], e, 1.0) : fs[b] + e;
+                fm[b] = up ? F : fm[b];
+                im[b] = up ? m : im[b];
+            }
+        };
+        const bool direct = hi > lo && (G.a[0] < ga || G.a[1] < gb);
+        if (__any(direct)) {
+            // too weak beside what has left the window: the plain sum
+            Sums<BG> S;
+            S.zero();
+            double w = 1.0;
+#pragma unroll 1
+            for (int k = lo; __any(direct && k < hi); ++k) {
+                const double ww = k < hi ? w : 0.0;
+                S.add(ww * ww, ww, uniform_slot<BG>(p, k, bin0));
+                w *= t.rho;
+            }
+            if (direct) cell(S);
+        }
+        if (!direct) cell(G);
+        if (m == m_lo) break;
+        --m;
+        k0 = rows[m].k0;
+        delta = rows[m].delta;
+        const int lo_n = clamp_slot(k0, K);
+        const int hi_n = max(end_slot(k0, delta, t.q, t.r, K), lo_n);
+        // slots that enter at the front
+        if (lo - lo_n == 1)
+            G.shift(t.rho2, t.rho, uniform_slot<BG>(p, lo_n, bin0));
+        else
+            run_down<BG, kU>(p, t, bin0, lo, lo_n, G);
+        lo = lo_n;
+        // slots that leave at the back: weight rho^(k - lo)
+        if (__any(hi > hi_n)) {
+            double w = hi_n - lo_n == t.q ? wq : wq1;
+            if (__any(hi > hi_n && (unsigned)(hi_n - lo_n - t.q) > 1u)) w = exp(t.c * (double)(hi_n - lo_n));
+            w = -w;
+#pragma unroll 1
+            for (int k = hi_n; __any(k < hi); ++k) {
+                const Sums<BG> y = lane_slot(k, k < hi);
+                G.add(-w * w, w, y);
+                w *= t.rho;
+            }
+            hi = hi_n;
+        }
+    }
+
+    // the wave's lanes: maximum with its first cell, sum rescaled to it
+#pragma unroll
+    for (int b = 0; b < BG; ++b) {
+        double mx = n_ok ? fm[b] : -INFINITY;
+        long long ix = (long long)im[b] * p.n_tau + n;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const double fo = __shfl_xor(mx, o, 64);
+            const long long io = __shfl_xor(ix, o, 64);
+            if (fo > mx || (fo == mx && io < ix)) {
+                mx = fo;
+                ix = io;
+            }
+        }
+        double sv = n_ok ? fs[b] * (double)__expf((float)(fm[b] - mx)) : 0.0;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) sv += __shfl_xor(sv, o, 64);
+        if (lane == 0 && bin0 + b < n_bins) {
+            Partial &o = p.part[(size_t)(bin0 + b) * p.n_tiles + (size_t)tt * p.n_seg + seg];
+            o.fmax = mx;
+            o.s = sv;
+            o.idx = ix;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Once per upload: the FP32 plane, and what the sums ask of the atoms.
+// Workgroup = 64 columns (4 per bin; the last one: the antenna's 4); a lane
+// takes stretches of 64 slots of one column, as many lanes per column as fit.
+// ---------------------------------------------------------------------------
+constexpr int kRangeWaves = 16;
+__global__ __launch_bounds__(64 * kRangeWaves) void atoms_kernel(const double *x64, const double *abc, float *x32,
+                                                                 int32_t K, int32_t n_bins, RangeInfo *info) {
+    __shared__ double smax[kRangeWaves][64], smin[kRangeWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool ant = blockIdx.x == gridDim.x - 1;
+    const int C = ant ? 4 : 4 * n_bins;
+    const int c0 = ant ? 0 : blockIdx.x * 64;
+    const int n_c = min(C - c0, 64);          // columns of this workgroup
+    const int subs = 64 / n_c;                // lanes per column
+    const int c = c0 + lane % n_c;
+    const int sub = lane / n_c;
+    const double *in = ant ? abc : x64;
+    double mx = 0.0, mn = INFINITY;
+    bool bad = false, inexact = false;
+    if (sub < subs) {
+        for (int k0 = (wave * subs + sub) * 64; k0 < K; k0 += kRangeWaves * subs * 64) {
+            double b = 0.0;
+            const int k1 = min(k0 + 64, K);
+#pragma unroll 8
+            for (int k = k0; k < k1; ++k) {
+                const double v = in[(size_t)k * C + c];
+                const float f = (float)v;
+                if (!ant) x32[(size_t)k * C + c] = f;
+                bad |= !(fabs(v) < INFINITY);
+                inexact |= (double)f != v;
+                b = fmax(b, fabs(v));
+            }
+            mx = fmax(mx, b);
+            if (b > 0.0) mn = fmin(mn, b);
+        }
+        if (!ant && wave == 0 && sub == 0) x32[(size_t)K * C + c] = 0.f;   // row K is zero
+    }
+    smax[wave][lane] = mx;
+    smin[wave][lane] = mn;
+    __syncthreads();
+    if (wave == 0 && lane < n_c) {
+        for (int w = 0; w < kRangeWaves; ++w)
+            for (int l = lane; l < subs * n_c; l += n_c) {
+                mx = fmax(mx, smax[w][l]);
+                mn = fmin(mn, smin[w][l]);
+            }
+        if (ant) {
+            if (lane == 0) info->amax = (unsigned long long)__double_as_longlong(mx);
+            if (lane == 1) info->bmax = (unsigned long long)__double_as_longlong(mx);
+        } else {
+            bad |= mn < mx * 0x1p-20;
+        }
+    }
+    if (bad) atomicOr(&info->wide, 1);
+    if (inexact && !ant) atomicOr(&info->inexact32, 1);
+}
+
+template <int BG>
+__global__ __launch_bounds__(64 * kSlideWaves) void slide_anchor_kernel(SlideParams p) {
+    __shared__ __attribute__((aligned(16))) char smem[sizeof(AnchorSmem<BG>)];
+    slide_anchor<BG>(p, smem, blockIdx.x, blockIdx.y);
+}
+
+template <int BG>
+__global__ __launch_bounds__(256, 3) void slide_rows_kernel(SlideParams p) {
+    __shared__ __attribute__((aligned(16))) char smem[sizeof(RowsSmem<BG>)];
+    slide_rows<BG>(p, smem, blockIdx.x, blockIdx.y);
+}
+
+// Many maps, one workgroup per entry; the bins per group are the map's.
+template <typename T>
+__device__ inline ConstParams<T> &const_params(const T *p) {
+    return *const_ptr(p);
+}
+__global__ __launch_bounds__(64 * kSlideWaves) void slide_anchor_batch_kernel(SlideBatchParams b) {
+    __shared__ __attribute__((aligned(16))) char smem[sizeof(AnchorSmem<4>)];
+    ConstParams<int32_t> *e = const_ptr(b.anchors) + 4 * (size_t)blockIdx.x;
+    auto &p = const_params(b.jobs + e[0]);
+    switch (p.bg) {
+    case 1: slide_anchor<1>(p, smem, e[1], e[2]); break;
+    case 2: slide_anchor<2>(p, smem, e[1], e[2]); break;
+    case 3: slide_anchor<3>(p, smem, e[1], e[2]); break;
+    default: slide_anchor<4>(p, smem, e[1], e[2]); break;
+    }
+}
+__global__ __launch_bounds__(256, 3) void slide_rows_batch_kernel(SlideBatchParams b) {
+    __shared__ __attribute__((aligned(16))) char smem[sizeof(RowsSmem<4>)];
+    ConstParams<int32_t> *e = const_ptr(b.rows) + 4 * (size_t)blockIdx.x;
+    auto &p = const_params(b.jobs + e[0]);
+    switch (p.bg) {
+    case 1: slide_rows<1>(p, smem, e[1], e[2]); break;
+    case 2: slide_rows<2>(p, smem, e[1], e[2]); break;
+    case 3: slide_rows<3>(p, smem, e[1], e[2]); break;
+    default: slide_rows<4>(p, smem, e[1], e[2]); break;
+    }
+}
+
+}  // namespace
+
+hipError_t launch_slide_batch(const SlideBatchParams &p, hipStream_t s) {
+    if (p.n_rows <= 0) return hipSuccess;
+    hipLaunchKernelGGL(slide_anchor_batch_kernel, dim3((unsigned)p.n_anchors), dim3(64 * kSlideWaves), 0, s, p);
+    hipLaunchKernelGGL(slide_rows_batch_kernel, dim3((unsigned)p.n_rows), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_atoms(const double *x64, const double *abc, float *x32, int32_t K, int32_t n_bins, RangeInfo *info,
+                        hipStream_t s) {
+    const unsigned g = (unsigned)((4 * (int64_t)n_bins + 63) / 64) + 1u;
+    hipLaunchKernelGGL(atoms_kernel, dim3(g), dim3(64 * kRangeWaves), 0, s, x64, abc, x32, K, n_bins, info);
+    return hipGetLastError();
+}
+
+hipError_t launch_slide(const SlideParams &p, hipStream_t s) {
+    if (p.n_tau <= 0 || p.n_t0 <= 0 || p.seg_rows < 1 || p.range_len < 1) return hipErrorInvalidValue;
+    const unsigned cols = (unsigned)(p.n_tt * p.n_bg);
+    const dim3 ga(cols, (unsigned)p.n_sup), gr(cols, (unsigned)((p.n_seg + 3) / 4));
+    if (ga.y > 65535u || gr.y > 65535u) return hipErrorInvalidValue;
+    switch (p.bg) {
+    case 1:
+        hipLaunchKernelGGL(slide_anchor_kernel<1>, ga, dim3(64 * kSlideWaves), 0, s, p);
+        hipLaunchKernelGGL(slide_rows_kernel<1>, gr, dim3(256), 0, s, p);
+        break;
+    case 2:
+        hipLaunchKernelGGL(slide_anchor_kernel<2>, ga, dim3(64 * kSlideWaves), 0, s, p);
+        hipLaunchKernelGGL(slide_rows_kernel<2>, gr, dim3(256), 0, s, p);
+        break;
+    case 3:
+        hipLaunchKernelGGL(slide_anchor_kernel<3>, ga, dim3(64 * kSlideWaves), 0, s, p);
+        hipLaunchKernelGGL(slide_rows_kernel<3>, gr, dim3(256), 0, s, p);
+        break;
+    case 4:
+        hipLaunchKernelGGL(slide_anchor_kernel<4>, ga, dim3(64 * kSlideWaves), 0, s, p);
+        hipLaunchKernelGGL(slide_rows_kernel<4>, gr, dim3(256), 0, s, p);
+        break;
+    default:
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace tfs

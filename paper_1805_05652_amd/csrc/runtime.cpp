@@ -167,7 +167,10 @@ struct AtomsSet {
     double *abc = nullptr;
     double *x64 = nullptr;
     float *x32 = nullptr;
-    int32_t *npref = nullptr;   // [K+1] present SFTs in slots [0, k)
+    // sliding sums (kernels_slide.hip): whether they apply to these atoms,
+    // whether x32 holds x64 exactly, and the largest a^2 and b^2
+    bool slide_ok = false, exact32 = false;
+    double amax = 0.0, bmax = 0.0;
     // bf16 hi / lo planes for the matrix-core path, built on first use
     void *planes = nullptr;
     unsigned short *xhi = nullptr, *xlo = nullptr;
@@ -271,6 +274,8 @@ constexpr int32_t kRunsAuto = -1;
 // FP32 maps with at least this many bins (and rows close enough for the band
 // stage) take the split form: A/B/C pass, then F_a/F_b-only tiles.
 constexpr int32_t kSplitMinBins = 8;
+// Waves a sliding map aims at (1024 SIMDs, three waves each).
+constexpr int64_t kSlideTarget = 3072;
 
 // ---------------------------------------------------------------------------
 // One map computation: plan (host, integer), workspace, launches, results.
@@ -298,8 +303,11 @@ struct Job {
     int n_groups = 0;
     bool tail2 = false;
     int64_t wtot = 0, max_blk = 0;
-    bool use_recur = false;    // RECUR64: exponential sums by the t0 recurrence
-    int32_t recur_stride = 0, recur_k0 = 0, recur_bg = 1;
+    // exponential sums by sliding windows along t0 (kernels_slide.hip)
+    bool slide = false;
+    int no_slide = 0;          // 1: smallest workspace, 2: the direct forms (the arena is short)
+    bool forced = false;       // tile shape forced by the caller: the direct forms
+    int32_t bg = 1, n_bg = 1, n_tt = 1, n_seg = 1, seg_rows = 1, range_len = 1, n_range = 1, n_sup = 1;
     bool use_mfma = false;     // BF16X3 on matrix cores for long bands
     // matrix-core form: true = weights computed per row (exponential
     // windows, any t0 grid); false = shifted weight tables (shape windows
@@ -310,6 +318,9 @@ struct Job {
     std::vector<int64_t> gsh_off;
     int64_t gsh_total = 0, gsh_max = 0;
 
+    bool small_ws = false;       // the arena is short: rect maps without block totals
+    int32_t scan_blk = 0;        // rect maps: blocks of the prefix sums that have totals
+
     // memory
     size_t ws_bytes = 0;
     void *ws = nullptr;
@@ -318,12 +329,44 @@ struct Job {
     size_t off_rows = 0, off_tau = 0, off_lcol = 0, off_lblk = 0, off_boff = 0, off_order = 0,
            tables_bytes = 0;
     size_t off_g32 = 0, off_gsq = 0, off_g64 = 0, off_pabc = 0, off_px = 0, off_part = 0,
-           off_res = 0, off_abc = 0, off_lg = 0, off_gshoff = 0, off_gsh = 0, off_shape = 0;
+           off_res = 0, off_abc = 0, off_lg = 0, off_gshoff = 0, off_gsh = 0, off_shape = 0, off_anc = 0, off_sup = 0, off_ptot = 0;
 
     // timing
     std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> timed;
     hipEvent_t done = nullptr;
 };
+
+// Sliding sums of an exponential map (kernels_slide.hip), from the map alone
+// (its results may not depend on what it is batched with).  They cost a
+// window's ends instead of its slots, so every map takes them whose atoms allow
+// it, unless the caller chose a tile form of the direct sums.
+void plan_slide(Job &j) {
+    const AtomsSet &at = *j.at;
+    const bool tiling = j.runs_min_spread != kRunsAuto || j.split_min_bins != kSplitMinBins;
+    if (!at.slide_ok || j.no_slide > 1 || j.forced || matrix_prec(j.prec)) return;
+    if (tiling && j.prec != TFSTAT_PREC_RECUR64) return;
+    const int n_t0 = (int)j.win.t0.size(), n_tau = (int)j.win.tau.size();
+    j.slide = true;
+    j.n_tt = (n_tau + 63) / 64;
+    j.n_bg = (at.n_bins + 3) / 4;
+    j.bg = (at.n_bins + j.n_bg - 1) / j.n_bg;
+    const int64_t cols = (int64_t)j.n_tt * j.n_bg;
+    // segments for about kSlideTarget waves.  A segment starts from anchors,
+    // about 32 slots away: of rows that lie closer it takes at least 4
+    const int64_t apart = n_t0 > 1 ? ((int64_t)j.rows[n_t0 - 1].k0 - j.rows[0].k0) / (n_t0 - 1) : 1;
+    const int64_t least = apart >= 8 ? 1 : (apart >= 4 ? 2 : 4);
+    int64_t n_seg = j.no_slide ? 1 : std::min<int64_t>((kSlideTarget + cols - 1) / cols, (n_t0 + least - 1) / least);
+    n_seg = std::max<int64_t>(n_seg, 1);
+    j.seg_rows = (int32_t)((n_t0 + n_seg - 1) / n_seg);
+    j.n_seg = (n_t0 + j.seg_rows - 1) / j.seg_rows;
+    // ranges of the anchors: long ones where the columns alone fill the chip
+    int32_t rl = 128;
+    while (rl > 16 && cols * (at.K / rl) < kSlideTarget) rl /= 2;
+    if (j.no_slide) rl = std::max(128, (at.K + tfs::kSlideWaves - 1) / tfs::kSlideWaves);
+    j.range_len = rl;
+    j.n_sup = std::max<int32_t>(1, (at.K + rl * tfs::kSlideWaves - 1) / (rl * tfs::kSlideWaves));
+    j.n_range = j.n_sup * tfs::kSlideWaves;
+}
 
 void plan_job(Job &j) {
     const AtomsSet &at = *j.at;
@@ -366,24 +409,8 @@ void plan_job(Job &j) {
         j.lcol[n] = (int32_t)std::min(shortest, cap);
     }
     j.n_row_tiles = (n_t0 + 63) / 64;
-    // Recurrence path: RECUR64 on a regular t0 grid whose step is a whole
-    // number of slots (then every row has the same delta).
-    j.use_recur = false;
-    if (j.win.type == TFSTAT_WIN_EXP && j.prec == TFSTAT_PREC_RECUR64) {
-        bool ok = true;
-        int64_t step = n_t0 > 1 ? j.win.t0[1] - j.win.t0[0] : T;
-        for (int m = 1; m < n_t0 && ok; ++m) ok = j.win.t0[m] - j.win.t0[m - 1] == step;
-        ok = ok && step % T == 0 && step / T <= 64;
-        const int64_t k0 = ceil_div(j.win.t0[0] - at.T0, T);
-        const int64_t klast = k0 + (int64_t)(n_t0 - 1) * (step / T);
-        ok = ok && k0 > -((int64_t)1 << 30) && klast < ((int64_t)1 << 30);
-        if (ok) {
-            j.use_recur = true;
-            j.recur_stride = (int32_t)(step / T);
-            j.recur_k0 = (int32_t)k0;
-            j.recur_bg = at.n_bins >= 4 ? 4 : (at.n_bins >= 2 ? 2 : 1);
-        }
-    }
+    j.slide = false;
+    if (j.win.type == TFSTAT_WIN_EXP) plan_slide(j);
     // Matrix-core path (BF16X3).  Exponential windows: any t0 grid, maps of
     // at least kMfmaMinBins bins whose bf16 component planes stay under
     // 2^31 bytes.  Shape windows: rows on consecutive slots with one delta.
@@ -391,7 +418,7 @@ void plan_job(Job &j) {
     // band grows with tau, so block b's shortest is that of its first tau).
     j.use_mfma = false;
     j.mfma_rows = false;
-    if (is_exp && matrix_prec(j.prec)) {
+    if (is_exp && !j.slide && matrix_prec(j.prec)) {
         bool ok;
         if (is_shape) {
             // the shifted bf16 tables; F16X3 shape windows run the FP32 sums
@@ -412,9 +439,9 @@ void plan_job(Job &j) {
         j.use_mfma = ok && long_block;
         if (!j.use_mfma) j.mfma_rows = false;
     }
-    if (is_exp && j.use_recur) {
+    if (j.slide) {
         j.NB = 0;
-        j.n_tiles = n_tau;
+        j.n_tiles = j.n_tt * j.n_seg;
     } else if (is_exp) {
         const int prec = (j.prec == TFSTAT_PREC_FP64 || j.prec == TFSTAT_PREC_RECUR64) ? 0 : 1;
         // median slot span of the 64-row tiles (tile form choice below)
@@ -531,7 +558,7 @@ void plan_job(Job &j) {
     j.off_rows = take(sizeof(tfs::RowPlan) * n_t0);
     j.off_tau = take(sizeof(int64_t) * n_tau);
     j.off_lcol = take(sizeof(int32_t) * n_tau);
-    if (is_exp && !j.use_recur) {
+    if (is_exp && !j.slide) {
         j.off_lblk = take(sizeof(int32_t) * j.NB);
         j.off_boff = take(sizeof(int64_t) * j.NB);
         j.off_order = take(sizeof(int32_t) * j.NB);
@@ -542,8 +569,10 @@ void plan_job(Job &j) {
         if (is_shape) j.off_shape = take(sizeof(double) * j.win.shape.size());
     }
     j.tables_bytes = o;
-    if (is_exp && j.use_recur) {
-        // no weight tables
+    if (j.slide) {
+        const size_t ch = (size_t)j.n_tt * j.n_bg * (3 + 4 * j.bg) * 64 * sizeof(double);
+        j.off_anc = take(ch * j.n_range);
+        j.off_sup = take(ch * j.n_sup);
     } else if (is_exp) {
         j.off_g32 = take(sizeof(float) * std::max<int64_t>(j.wtot, 1));
         j.off_gsq = take(sizeof(double) * std::max<int64_t>(j.wtot, 1));
@@ -558,10 +587,29 @@ void plan_job(Job &j) {
     } else {
         j.off_pabc = take(sizeof(double) * 8 * ((size_t)at.K + 1));
         j.off_px = take(sizeof(double) * 8 * (size_t)at.n_bins * ((size_t)at.K + 1));
+        // block totals of the prefix sums (one set per 64 channels)
+        const int64_t n_blk = (at.K + tfs::kScanBlock - 1) / tfs::kScanBlock;
+        j.scan_blk = n_blk > 1 && n_blk <= 65535 && !j.small_ws ? (int32_t)n_blk : 0;
+        j.off_ptot = take(sizeof(double2) * 64 * (size_t)j.scan_blk * (1 + (4 * (size_t)at.n_bins + 63) / 64));
     }
     j.off_part = take(sizeof(tfs::Partial) * (size_t)j.n_tiles * at.n_bins);
     j.off_res = take(sizeof(tfs::BinResultDev) * at.n_bins);
     j.ws_bytes = o;
+}
+
+// Plans a map again with less workspace, for an arena that cannot hold it;
+// false when it has no smaller plan.  Sliding maps: RECUR64 ones (never large)
+// with the smallest workspace first, others by the direct forms; rect maps:
+// without block totals.
+bool plan_smaller(Job &j) {
+    if (j.slide)
+        j.no_slide = j.prec == TFSTAT_PREC_RECUR64 && j.no_slide == 0 ? 1 : 2;
+    else if (!banded(j.win.type) && j.scan_blk > 0)
+        j.small_ws = true;
+    else
+        return false;
+    plan_job(j);
+    return true;
 }
 
 struct EventPool {
@@ -697,7 +745,7 @@ void fill_tables(const Job &j, char *h) {
     std::memcpy(h + j.off_rows, j.rows.data(), sizeof(tfs::RowPlan) * n_t0);
     std::memcpy(h + j.off_tau, j.win.tau.data(), sizeof(int64_t) * n_tau);
     std::memcpy(h + j.off_lcol, j.lcol.data(), sizeof(int32_t) * n_tau);
-    if (banded(j.win.type) && !j.use_recur) {
+    if (banded(j.win.type) && !j.slide) {
         if (j.win.type == TFSTAT_WIN_SHAPE)
             std::memcpy(h + j.off_shape, j.win.shape.data(), sizeof(double) * j.win.shape.size());
         std::memcpy(h + j.off_lblk, j.lblk.data(), sizeof(int32_t) * j.NB);
@@ -834,6 +882,55 @@ tfs::AbcRecurParams abc_recur_params(Job &j) {
     return q;
 }
 
+tfs::SlideParams slide_params(Job &j) {
+    const AtomsSet &at = *j.at;
+    tfs::SlideParams q{};
+    q.K = at.K;
+    q.n_bins = at.n_bins;
+    q.n_t0 = (int32_t)j.win.t0.size();
+    q.n_tau = (int32_t)j.win.tau.size();
+    q.t_sft = at.t_sft;
+    q.bg = j.bg;
+    q.n_bg = j.n_bg;
+    q.n_tt = j.n_tt;
+    q.n_seg = j.n_seg;
+    q.seg_rows = j.seg_rows;
+    q.range_len = j.range_len;
+    q.n_range = j.n_range;
+    q.n_sup = j.n_sup;
+    q.n_tiles = j.n_tiles;
+    q.exact32 = at.exact32;
+    q.guard_a = at.amax * 0x1p-13;
+    q.guard_b = at.bmax * 0x1p-13;
+    q.rows = ws_ptr<tfs::RowPlan>(j, j.off_rows);
+    q.tau = ws_ptr<int64_t>(j, j.off_tau);
+    q.abc = at.abc;
+    q.x64 = at.x64;
+    q.x32 = at.x32;
+    q.anc = ws_ptr<double>(j, j.off_anc);
+    q.sup = ws_ptr<double>(j, j.off_sup);
+    q.twoF = j.twoF;
+    q.part = ws_ptr<tfs::Partial>(j, j.off_part);
+    return q;
+}
+
+// Prefix sums of 64 channels of a rect map: the antenna's (chunk -1) or chunk
+// `chunk` of the data's.
+tfs::ScanJob scan_job(Job &j, int32_t chunk, int32_t blk) {
+    const AtomsSet &at = *j.at;
+    tfs::ScanJob q{};
+    q.in = chunk < 0 ? at.abc : at.x64;
+    q.out = ws_ptr<double>(j, chunk < 0 ? j.off_pabc : j.off_px);
+    q.tot = j.scan_blk ? ws_ptr<double2>(j, j.off_ptot) + (size_t)(chunk + 1) * j.scan_blk * 64 : nullptr;
+    q.C = chunk < 0 ? 4 : 4 * at.n_bins;
+    q.stride = q.C;
+    q.K = at.K;
+    q.chunk = std::max(chunk, 0);
+    q.blk = blk;
+    q.n_blk = j.scan_blk;
+    return q;
+}
+
 tfs::RectParams rect_params(Job &j) {
     tfs::RectParams p{};
     p.K = j.at->K;
@@ -927,29 +1024,12 @@ void enqueue_job(tfstat_ctx *ctx, Job &j, hipStream_t s) {
     fill_tables(j, h);
     hip_check(hipMemcpyAsync(j.ws, h, j.tables_bytes, hipMemcpyHostToDevice, s), "upload tables");
 
-    const auto *tau = ws_ptr<int64_t>(j, j.off_tau);
-    auto *part = ws_ptr<tfs::Partial>(j, j.off_part);
     auto *res = ws_ptr<tfs::BinResultDev>(j, j.off_res);
 
-    if (is_exp && j.use_recur) {
-        tfs::RecurParams rp{};
-        rp.K = at.K;
-        rp.n_bins = at.n_bins;
-        rp.n_t0 = n_t0;
-        rp.n_tau = n_tau;
-        rp.t_sft = at.t_sft;
-        rp.k0_first = j.recur_k0;
-        rp.stride = j.recur_stride;
-        rp.delta = j.rows[0].delta;
-        rp.n_tiles = j.n_tiles;
-        rp.tau = tau;
-        rp.abc = at.abc;
-        rp.x64 = at.x64;
-        rp.npref = at.npref;
-        rp.twoF = j.twoF;
-        rp.part = part;
+    if (j.slide) {
+        const tfs::SlideParams sp = slide_params(j);
         record_kernel(ctx, j, TFSTAT_K_RECUR, s, true);
-        hip_check(tfs::launch_exp_recur(rp, j.recur_bg, s), "exp recurrence kernel");
+        hip_check(tfs::launch_slide(sp, s), "sliding sums kernels");
         record_kernel(ctx, j, TFSTAT_K_RECUR, s, false);
     } else if (is_exp) {
         tfs::WeightParams wp = weight_params(j);
@@ -1020,12 +1100,8 @@ void enqueue_job(tfstat_ctx *ctx, Job &j, hipStream_t s) {
             }
         }
     } else {
-        double *pabc = ws_ptr<double>(j, j.off_pabc);
-        double *px = ws_ptr<double>(j, j.off_px);
         record_kernel(ctx, j, TFSTAT_K_SCAN, s, true);
-        hip_check(tfs::launch_scan(at.abc, 4, pabc, at.K, 4, s), "scan kernel");
-        hip_check(tfs::launch_scan(at.x64, 4 * (int64_t)at.n_bins, px, at.K, 4 * at.n_bins, s),
-                  "scan kernel");
+        hip_check(tfs::launch_scan(scan_job(j, -1, 0), scan_job(j, 0, 0), s), "scan kernel");
         record_kernel(ctx, j, TFSTAT_K_SCAN, s, false);
         tfs::RectParams p = rect_params(j);
         record_kernel(ctx, j, TFSTAT_K_RECT, s, true);
@@ -1160,8 +1236,10 @@ struct tfstat_batch {
     tfs::WeightBatchParams wbp{};
     const tfs::ScanJob *scan_jobs = nullptr;
     int n_scan = 0;
+    bool scan_split = false;
     tfs::MergeBatchParams mbp{};
     tfs::AbcBatchParams abp{};       // A/B/C pre-pass of the split-form and matrix-core maps
+    tfs::SlideBatchParams slp{};     // sliding sums of exponential maps
     tfs::MfmaBatchParams mfp{};      // matrix-core work of the BF16X3 / F16X3 maps
     tfs::AbcRecurBatchParams rap{};  // recurrence A/B/C of exponential split and matrix-core maps
     tfs::BinResultDev *res_dev = nullptr;
@@ -1172,6 +1250,7 @@ struct tfstat_batch {
     hipEvent_t evm1 = nullptr;                  // after the matrix-core launch (timed runs)
     double tune_ms = 0.0, last_ms = 0.0, last_fused_ms = 0.0, last_mfma_ms = 0.0;
     bool holds_atoms = false;
+    bool forced = false;             // tile shape forced by the caller
 };
 
 namespace {
@@ -1222,7 +1301,9 @@ int job_shape(const Job &j) {
 // ctx->mu.
 bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bool have_lock) {
     const int32_t n = (int32_t)b->jobs.size();
-    std::vector<int> shape(n, -1), eidx(n, -1), ridx(n, -1), midx(n, -1);
+    std::vector<int> shape(n, -1), eidx(n, -1), ridx(n, -1), midx(n, -1), sidx(n, -1);
+    int n_slide = 0;
+    size_t n_anchor = 0, n_srows = 0;   // workgroups of the sliding maps' two launches
     int n_exp = 0, n_rect = 0, n_went = 0, n_scan = 0, n_abc = 0, n_mfma_maps = 0, n_rabc_maps = 0;
     size_t n_rabc = 0;   // recurrence A/B/C entries (exponential windows)
     std::vector<int> aidx(n, -1);
@@ -1230,9 +1311,14 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     int32_t max_chunks = 1;
     b->res_off.assign(n, 0);
     b->n_results = 0;
+    b->scan_split = false;
     for (int32_t i = 0; i < n; ++i) {
         Job &j = *b->jobs[i];
-        if (banded(j.win.type)) {
+        if (j.slide) {
+            sidx[i] = n_slide++;
+            n_anchor += (size_t)j.n_tt * j.n_bg * j.n_sup;
+            n_srows += (size_t)j.n_tt * j.n_bg * ((j.n_seg + 3) / 4);
+        } else if (banded(j.win.type)) {
             if (j.use_mfma && !j.mfma_rows)
                 raise(TFSTAT_E_INVAL, "a batch runs no matrix-core shape windows (use tfstat_fmap)");
             shape[i] = job_shape(j);
@@ -1271,7 +1357,8 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
             max_chunks = std::max<int32_t>(max_chunks, (int32_t)std::min<int64_t>((mb + 255) / 256, 4096));
         } else {
             ridx[i] = n_rect++;
-            n_scan += 1 + (4 * j.at->n_bins + 63) / 64;
+            n_scan += (1 + (4 * j.at->n_bins + 63) / 64) * std::max(1, j.scan_blk);
+            b->scan_split = b->scan_split || j.scan_blk > 0;
         }
         b->res_off[i] = b->n_results;
         b->n_results += j.at->n_bins;
@@ -1301,13 +1388,13 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
             for (int q = 0; q < j.n_valu; q += step)
                 groups_e.push_back({i, q, (double)(j.lblk[j.order[q]] + 1) * j.R * per_step * step});
             n_tiles_total += per * ((j.n_valu + step - 1) / step);
-        } else {
+        } else if (ridx[i] >= 0) {
             const int ny = ((int)j.win.t0.size() + tfs::kRectRows - 1) / tfs::kRectRows;
             n_tiles_total += (size_t)ny * j.n_tiles_n * ((j.at->n_bins + tfs::kRectBins - 1) / tfs::kRectBins);
         }
     }
     if (n_tiles_total > (size_t)INT32_MAX / 2 || n_mfma_entries > (size_t)INT32_MAX / 2 ||
-        n_rabc > (size_t)INT32_MAX / 2)
+        n_rabc > (size_t)INT32_MAX / 2 || n_anchor > (size_t)INT32_MAX / 2 || n_srows > (size_t)INT32_MAX / 2)
         raise(TFSTAT_E_INVAL, "batch has too many tiles");
     std::stable_sort(groups_e.begin(), groups_e.end(),
                      [](const Group &a, const Group &c) { return a.cost > c.cost; });
@@ -1368,6 +1455,9 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     const size_t off_ment = take(sizeof(int32_t) * 4 * n_mfma_entries);
     const size_t off_rap = take(sizeof(tfs::AbcRecurParams) * n_rabc_maps);
     const size_t off_rent = take(sizeof(int32_t) * 2 * n_rabc);
+    const size_t off_slp = take(sizeof(tfs::SlideParams) * n_slide);
+    const size_t off_aent = take(sizeof(int32_t) * 4 * n_anchor);
+    const size_t off_sent = take(sizeof(int32_t) * 4 * n_srows);
     const size_t desc_end = o;
     const size_t off_counter = take(sizeof(int32_t));
     const size_t off_res = take(sizeof(tfs::BinResultDev) * b->n_results);
@@ -1409,6 +1499,9 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     auto *ment = reinterpret_cast<int32_t *>(hptr(off_ment));
     auto *rap = reinterpret_cast<tfs::AbcRecurParams *>(hptr(off_rap));
     auto *rent = reinterpret_cast<int32_t *>(hptr(off_rent));
+    auto *slp = reinterpret_cast<tfs::SlideParams *>(hptr(off_slp));
+    auto *aent = reinterpret_cast<int32_t *>(hptr(off_aent));
+    auto *sent = reinterpret_cast<int32_t *>(hptr(off_sent));
     size_t re = 0;
     int we = 0, se = 0, me = 0, ae = 0;
     size_t mfc = 0, mfe = n_cells_entries;   // next transposed-form and other matrix-core entry
@@ -1459,14 +1552,12 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
                             ++pos;
                         }
             }
+        } else if (sidx[i] >= 0) {
+            slp[sidx[i]] = slide_params(j);
         } else {
             rp[ridx[i]] = rect_params(j);
-            double *pabc = ws_ptr<double>(j, j.off_pabc);
-            double *px = ws_ptr<double>(j, j.off_px);
-            scan[se++] = tfs::ScanJob{j.at->abc, pabc, 4, j.at->K, 4, 0, 0};
-            const int32_t C = 4 * j.at->n_bins;
-            for (int c = 0; c < (C + 63) / 64; ++c)
-                scan[se++] = tfs::ScanJob{j.at->x64, px, (int64_t)C, j.at->K, C, c, 0};
+            for (int c = -1; c < (4 * j.at->n_bins + 63) / 64; ++c)
+                for (int blk = 0; blk < std::max(1, j.scan_blk); ++blk) scan[se++] = scan_job(j, c, blk);
         }
         mp[i] = merge_params(j);
         mp[i].out = reinterpret_cast<tfs::BinResultDev *>(dptr(off_res)) + b->res_off[i];
@@ -1477,6 +1568,37 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
         }
     }
     std::memcpy(tl, tiles.data(), sizeof(tfs::BatchTile) * tiles.size());
+    {
+        // sliding maps, the longest segments (in slots and rows) first
+        std::vector<int32_t> by;
+        for (int32_t i = 0; i < n; ++i)
+            if (sidx[i] >= 0) by.push_back(i);
+        auto cost = [&](int32_t i) {
+            const Job &j = *b->jobs[i];
+            const int64_t slots = j.rows.back().k0 - j.rows.front().k0;
+            return (double)j.bg * (slots / j.n_seg + 2.0 * j.seg_rows);
+        };
+        std::stable_sort(by.begin(), by.end(), [&](int32_t x, int32_t y) { return cost(x) > cost(y); });
+        size_t ae_ = 0, sr_ = 0;
+        for (int32_t i : by) {
+            const Job &j = *b->jobs[i];
+            const int cols = j.n_tt * j.n_bg;
+            for (int u = 0; u < j.n_sup; ++u)
+                for (int c = 0; c < cols; ++c, ++ae_) {
+                    aent[4 * ae_] = sidx[i];
+                    aent[4 * ae_ + 1] = c;
+                    aent[4 * ae_ + 2] = u;
+                    aent[4 * ae_ + 3] = 0;
+                }
+            for (int q = 0; q < (j.n_seg + 3) / 4; ++q)
+                for (int c = 0; c < cols; ++c, ++sr_) {
+                    sent[4 * sr_] = sidx[i];
+                    sent[4 * sr_ + 1] = c;
+                    sent[4 * sr_ + 2] = q;
+                    sent[4 * sr_ + 3] = 0;
+                }
+        }
+    }
 
     b->fp.exp_jobs = reinterpret_cast<const tfs::ExpValuParams *>(dptr(off_ep));
     b->fp.rect_jobs = reinterpret_cast<const tfs::RectParams *>(dptr(off_rp));
@@ -1498,6 +1620,11 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     b->rap.jobs = reinterpret_cast<const tfs::AbcRecurParams *>(dptr(off_rap));
     b->rap.entries = reinterpret_cast<const int32_t *>(dptr(off_rent));
     b->rap.n_entries = (int32_t)n_rabc;
+    b->slp.jobs = reinterpret_cast<const tfs::SlideParams *>(dptr(off_slp));
+    b->slp.anchors = reinterpret_cast<const int32_t *>(dptr(off_aent));
+    b->slp.rows = reinterpret_cast<const int32_t *>(dptr(off_sent));
+    b->slp.n_anchors = (int32_t)n_anchor;
+    b->slp.n_rows = (int32_t)n_srows;
     b->mfp.jobs = reinterpret_cast<const tfs::ExpMfmaRowsParams *>(dptr(off_mfp));
     b->mfp.entries = reinterpret_cast<const int32_t *>(dptr(off_ment));
     if (mfc != n_cells_entries || mfe != n_mfma_entries) raise(TFSTAT_E_INVAL, "internal: matrix-core entry count");
@@ -1555,13 +1682,17 @@ void batch_build(tfstat_ctx *ctx, tfstat_batch *b, int32_t n, const tfstat_atoms
                 raise(TFSTAT_E_INVAL, "tile shape does not match the precision");
             j.force_R = R;
             j.force_BG = BG;
+            j.forced = b->forced;
         }
         j.runs_min_spread = ctx->runs_min_spread.load();
         j.split_min_bins = ctx->split_min_bins.load();
         plan_job(j);
     }
-    if (!batch_layout(ctx, b, ctx->batch_stream, true, false))
-        raise(TFSTAT_E_NOMEM, "arena cannot hold the batch workspace");
+    while (!batch_layout(ctx, b, ctx->batch_stream, true, false)) {
+        bool smaller = false;
+        for (Job *j : b->jobs) smaller = plan_smaller(*j) || smaller;
+        if (!smaller) raise(TFSTAT_E_NOMEM, "arena cannot hold the batch workspace");
+    }
 }
 
 // One run of the batch on stream s: counter reset, weight tables, prefix
@@ -1570,7 +1701,7 @@ void batch_build(tfstat_ctx *ctx, tfstat_batch *b, int32_t n, const tfstat_atoms
 hipError_t batch_enqueue(tfstat_batch *b, hipStream_t s, bool timed) {
     hipError_t e = tfs::launch_fill_i32(b->fp.counter, 1, 0, s);
     if (e == hipSuccess) e = tfs::launch_weights_batch(b->wbp, s);
-    if (e == hipSuccess) e = tfs::launch_scan_batch(b->scan_jobs, b->n_scan, s);
+    if (e == hipSuccess) e = tfs::launch_scan_batch(b->scan_jobs, b->n_scan, b->scan_split, s);
     if (e == hipSuccess) e = tfs::launch_abc_batch(b->abp, s);
     if (e == hipSuccess) e = tfs::launch_abc_recur_batch(b->rap, s);
     if (e == hipSuccess && timed) e = hipEventRecord(b->evf0, s);
@@ -1578,6 +1709,7 @@ hipError_t batch_enqueue(tfstat_batch *b, hipStream_t s, bool timed) {
     if (e == hipSuccess && timed) e = hipEventRecord(b->evf1, s);
     if (e == hipSuccess) e = tfs::launch_mfma_batch(b->mfp, s);
     if (e == hipSuccess && timed) e = hipEventRecord(b->evm1, s);
+    if (e == hipSuccess) e = tfs::launch_slide_batch(b->slp, s);
     if (e == hipSuccess) e = tfs::launch_merge_batch(b->mbp, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->pin, b->res_dev, sizeof(tfs::BinResultDev) * b->n_results,
@@ -1670,6 +1802,11 @@ constexpr double kServeFuseMaxWork = 2e9;
 double est_work(const Job &j) {
     const double cells_bins = (double)j.win.t0.size() * (double)j.at->n_bins;
     if (!banded(j.win.type)) return cells_bins * (double)j.win.tau.size();
+    if (j.slide) {
+        // per tau three terms per slot, and a cell's finalize, about six
+        const double slots = (double)j.win.tau.size() * (double)j.at->K * (double)(j.at->n_bins + 1);
+        return 3.0 * slots + 6.0 * cells_bins * (double)j.win.tau.size();
+    }
     double band = 0.0;   // sum over taus of the band length, from the block tables
     for (int q = 0; q < j.NB; ++q) {
         // matrix-core blocks: about a quarter of the VALU time per term
@@ -1681,7 +1818,7 @@ double est_work(const Job &j) {
 
 bool fusable(const Job &j) {
     return (j.prec == TFSTAT_PREC_FP32 || j.prec == TFSTAT_PREC_FP64 || matrix_prec(j.prec)) &&
-           !(j.use_mfma && !j.mfma_rows) && !j.use_recur && est_work(j) <= kServeFuseMaxWork;
+           !(j.use_mfma && !j.mfma_rows) && !(j.slide && j.prec == TFSTAT_PREC_RECUR64) && est_work(j) <= kServeFuseMaxWork;
 }
 
 void worker_loop(tfstat_ctx *ctx) {
@@ -1942,7 +2079,7 @@ int tfstat_atoms_upload(tfstat_ctx *ctx, const tfstat_atoms_desc *d, tfstat_atom
         const size_t abc_b = round_up(sizeof(double) * 4 * rows, 256);
         const size_t x64_b = round_up(sizeof(double) * 4 * nb * rows, 256);
         const size_t x32_b = round_up(sizeof(float) * 4 * nb * rows, 256);
-        const size_t np_b = round_up(sizeof(int32_t) * rows, 256);
+        const size_t ri_b = 256;   // RangeInfo
         auto set = std::make_unique<AtomsSet>();
         set->K = K;
         set->n_bins = nb;
@@ -1951,19 +2088,19 @@ int tfstat_atoms_upload(tfstat_ctx *ctx, const tfstat_atoms_desc *d, tfstat_atom
         set->t_sft = T;
         {
             std::lock_guard<std::mutex> g(ctx->mu);
-            set->mem = ctx->arena.alloc(abc_b + x64_b + x32_b + np_b);
+            set->mem = ctx->arena.alloc(abc_b + x64_b + x32_b + ri_b);
         }
         if (!set->mem) raise(TFSTAT_E_NOMEM, "arena cannot hold the atoms");
-        set->bytes = abc_b + x64_b + x32_b + np_b;
+        set->bytes = abc_b + x64_b + x32_b + ri_b;
         char *base = static_cast<char *>(set->mem);
         set->abc = reinterpret_cast<double *>(base);
         set->x64 = reinterpret_cast<double *>(base + abc_b);
-        set->x32 = reinterpret_cast<float *>(base + abc_b + x64_b);
-        set->npref = reinterpret_cast<int32_t *>(base + abc_b + x64_b + x32_b);
+        auto *info = reinterpret_cast<tfs::RangeInfo *>(base + abc_b + x64_b);   // uploaded as zeros
+        set->x32 = reinterpret_cast<float *>(base + abc_b + x64_b + ri_b);
         size_t pin_bytes = 0;
-        void *pin = ctx->pinned.get(abc_b + x64_b + np_b, &pin_bytes);
+        void *pin = ctx->pinned.get(abc_b + x64_b + ri_b, &pin_bytes);
         try {
-            std::memset(pin, 0, abc_b + x64_b + np_b);
+            std::memset(pin, 0, abc_b + x64_b + ri_b);
             double *habc = static_cast<double *>(pin);
             double *hx = reinterpret_cast<double *>(static_cast<char *>(pin) + abc_b);
             for (int32_t i = 0; i < d->n_sft; ++i) {
@@ -1982,25 +2119,20 @@ int tfstat_atoms_upload(tfstat_ctx *ctx, const tfstat_atoms_desc *d, tfstat_atom
                 }
             }
             hip_check(hipSetDevice(ctx->device), "hipSetDevice");
-            // present-SFT prefix counts (exact integers)
-            int32_t *hnp = reinterpret_cast<int32_t *>(static_cast<char *>(pin) + abc_b + x64_b);
-            {
-                std::vector<char> present(K, 0);
-                for (int32_t i = 0; i < d->n_sft; ++i) present[(d->timestamps[i] - T0) / T] = 1;
-                hnp[0] = 0;
-                for (int32_t k = 0; k < K; ++k) hnp[k + 1] = hnp[k] + present[k];
-            }
-            hip_check(hipMemcpyAsync(set->mem, pin, abc_b + x64_b, hipMemcpyHostToDevice, ctx->stream),
+            auto *hinfo = reinterpret_cast<tfs::RangeInfo *>(static_cast<char *>(pin) + abc_b + x64_b);
+            hip_check(hipMemcpyAsync(set->mem, pin, abc_b + x64_b + ri_b, hipMemcpyHostToDevice, ctx->stream),
                       "upload atoms");
-            hip_check(hipMemcpyAsync(set->npref, hnp, sizeof(int32_t) * rows, hipMemcpyHostToDevice,
-                                     ctx->stream), "upload counts");
             Job dummy;
             record_kernel(ctx, dummy, TFSTAT_K_UPLOAD, ctx->stream, true);
-            hip_check(tfs::launch_build_x32(set->x64, set->x32, (int64_t)4 * nb * rows, ctx->stream),
-                      "x32 kernel");
+            hip_check(tfs::launch_atoms(set->x64, set->abc, set->x32, K, nb, info, ctx->stream), "atoms kernel");
             record_kernel(ctx, dummy, TFSTAT_K_UPLOAD, ctx->stream, false);
+            hip_check(hipMemcpyAsync(hinfo, info, sizeof(*info), hipMemcpyDeviceToHost, ctx->stream), "range");
             hip_check(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
             collect_timing(ctx, dummy);
+            set->slide_ok = hinfo->wide == 0;
+            set->exact32 = hinfo->inexact32 == 0;
+            std::memcpy(&set->amax, &hinfo->amax, sizeof(double));
+            std::memcpy(&set->bmax, &hinfo->bmax, sizeof(double));
         } catch (...) {
             ctx->pinned.put(pin, pin_bytes);
             std::lock_guard<std::mutex> g(ctx->mu);
@@ -2061,7 +2193,9 @@ int tfstat_fmap(tfstat_ctx *ctx, tfstat_atoms_id id, const tfstat_window *win, i
         plan_job(j);
         {
             std::lock_guard<std::mutex> g(ctx->mu);
-            if (!alloc_job(ctx, j)) raise(TFSTAT_E_NOMEM, "arena cannot hold the map workspace");
+            while (!alloc_job(ctx, j)) {
+                if (!plan_smaller(j)) raise(TFSTAT_E_NOMEM, "arena cannot hold the map workspace");
+            }
         }
         try {
             hip_check(hipSetDevice(ctx->device), "hipSetDevice");
@@ -2212,6 +2346,8 @@ int tfstat_submit(tfstat_ctx *ctx, tfstat_atoms_id id, const tfstat_window *win,
         // would wait forever: refuse it now.
         size_t resident = 0;
         for (auto &kv : ctx->atoms) resident += kv.second->bytes;
+        while (job->ws_bytes + resident > ctx->arena.capacity() && plan_smaller(*job)) {
+        }
         if (job->ws_bytes + resident > ctx->arena.capacity())
             raise(TFSTAT_E_NOMEM, "request workspace cannot fit beside the resident atoms");
         if (ctx->queue.size() >= tfstat_ctx::kMaxQueue) raise(TFSTAT_E_BUSY, "serving queue is full");
@@ -2370,6 +2506,7 @@ int tfstat_batch_create(tfstat_ctx *ctx, int32_t n_maps, const tfstat_atoms_id *
         auto b = std::make_unique<tfstat_batch>();
         b->prec = precision;
         b->variant = variant;
+        b->forced = tune < 0;
         b->groups = per_cu * ctx->n_cu;
         b->tune_ms = tune_ms;
         try {

@@ -213,21 +213,48 @@ struct ShiftTableParams {
     unsigned short *gsh;
 };
 
-// Exponential-window sums by the t0 recurrence (rows k0_first + m * stride,
-// one common delta).  Partials: one tile per tau column.
-struct RecurParams {
+// Exponential-window sums by sliding windows along t0 (kernels_slide.hip).  A
+// column is a tile of 64 taus x one group of bg bins; its rows run in n_seg
+// segments of seg_rows rows.  Anchors: H at the end of every range of
+// range_len slots (kSlideWaves ranges make a super-range).
+constexpr int kSlideWaves = 16;
+struct SlideParams {
     int32_t K, n_bins;
     int32_t n_t0, n_tau;
     int64_t t_sft;
-    int32_t k0_first, stride;
-    int32_t delta;
-    int32_t n_tiles;          // partial slots per bin (n_tau)
+    int32_t bg, n_bg;         // bins per group (1..4), groups
+    int32_t n_tt;             // ceil(n_tau / 64)
+    int32_t n_seg, seg_rows;
+    int32_t range_len, n_range, n_sup;   // n_range: most ranges of any tile, whole super-ranges
+    int32_t n_tiles;          // partial slots per bin (n_tt * n_seg)
+    int32_t exact32;          // x32 holds x64 exactly
+    double guard_a, guard_b;  // cells with A or B below these are summed directly
+    const RowPlan *rows;
     const int64_t *tau;
     const double *abc;        // [K+1][4]
     const double *x64;        // [K+1][n_bins][4]
-    const int32_t *npref;     // [K+1] SFTs present in slots [0, k)
+    const float *x32;         // [K+1][n_bins][4]
+    double *anc;              // [n_tt * n_bg][n_range][3 + 4 bg][64]
+    double *sup;              // [n_tt * n_bg][n_sup][3 + 4 bg][64]
     float *twoF;
-    Partial *part;
+    Partial *part;            // [n_bins][n_tiles], tile tt * n_seg + seg
+};
+
+// Sliding maps of a batch: entry = {map, column, super-range or quad of
+// segments, 0}.
+struct SlideBatchParams {
+    const SlideParams *jobs;
+    const int32_t *anchors;   // [n_anchors][4]
+    const int32_t *rows;      // [n_rows][4]
+    int32_t n_anchors, n_rows;
+};
+
+// What the sliding sums ask of the atoms, found once at upload.
+struct RangeInfo {
+    int32_t wide;             // non-finite values, or a 64-slot stretch of a data column
+                              // under 2^-20 of the column's largest value
+    int32_t inexact32;        // some datum is not a single-precision number
+    unsigned long long amax, bmax;   // largest |a^2|, |b^2| (bits of the double)
 };
 
 // Weight tables [blk][d][R] of a banded window: exponential g[d] =
@@ -371,13 +398,17 @@ struct WeightBatchParams {
     int32_t chunks;           // grid.x: 256-element chunks per block
 };
 
-// Compensated prefix sums of many channel sets: entry i scans 64 channels.
+// Compensated prefix sums of 64 channels: block blk of kScanBlock slots, or
+// every block in turn when tot is null.
+constexpr int kScanBlock = 256;
 struct ScanJob {
     const double *in;
     double *out;
+    double2 *tot;             // [n_blk][64] sums of this chunk's blocks (single map: of chunk 0)
     int64_t stride;
     int32_t K, C;
     int32_t chunk;            // first channel / 64
+    int32_t blk, n_blk;
     int32_t pad;
 };
 
@@ -400,7 +431,6 @@ struct MapReduceParams {
 
 // ---- launchers (kernels.hip) ------------------------------------------------
 // Each returns hipSuccess or the launch error.
-hipError_t launch_build_x32(const double *x64, float *x32, int64_t n, hipStream_t s);
 hipError_t launch_weights(const WeightParams &p, int64_t total_max_per_block,
                           hipStream_t s);
 // prec: 0 = FP64 sums, 1 = FP32 sums.  bins_per_group chosen by the caller
@@ -424,7 +454,11 @@ hipError_t launch_exp_abc(const ExpValuParams &p, hipStream_t s);
 hipError_t launch_exp_mfma(const ExpMfmaParams &p, hipStream_t s);
 hipError_t launch_exp_mfma_rows(const ExpMfmaRowsParams &p, hipStream_t s);
 hipError_t launch_mfma_batch(const MfmaBatchParams &p, hipStream_t s);
-hipError_t launch_exp_recur(const RecurParams &p, int BG, hipStream_t s);
+hipError_t launch_slide(const SlideParams &p, hipStream_t s);
+hipError_t launch_slide_batch(const SlideBatchParams &p, hipStream_t s);
+// The FP32 plane x32 and the atoms' RangeInfo (info zeroed by the caller).
+hipError_t launch_atoms(const double *x64, const double *abc, float *x32, int32_t K, int32_t n_bins, RangeInfo *info,
+                        hipStream_t s);
 hipError_t launch_shift_tables(const ShiftTableParams &p, int64_t max_entries, hipStream_t s);
 // Entries per shifted table (one tau, part and shift) for a band of lblk.
 // Matrix-core tile constants (compile-time tunables).
@@ -453,8 +487,8 @@ hipError_t launch_build_planes(const float *x32, int32_t K, int32_t n_bins, int3
                                hipStream_t s);
 hipError_t launch_build_cplanes(const float *x32, int32_t K, int32_t n_bins, int32_t bins16, int32_t kpc,
                                 const int32_t *colexp, unsigned short *chi, unsigned short *clo, hipStream_t s);
-hipError_t launch_scan(const double *in, int64_t in_row_stride, double *out,
-                       int32_t K, int32_t C, hipStream_t s);
+// Prefix sums of a map's antenna and data channels.
+hipError_t launch_scan(const ScanJob &abc, const ScanJob &x, hipStream_t s);
 hipError_t launch_rect(const RectParams &p, hipStream_t s);
 hipError_t launch_merge(const MergeParams &p, hipStream_t s);
 hipError_t launch_map_reduce(const MapReduceParams &p, hipStream_t s);
@@ -466,7 +500,8 @@ hipError_t noalloc_setup(int device);
 void *noalloc_scratch(int device);
 hipError_t launch_weights_batch(const WeightBatchParams &p, hipStream_t s);
 hipError_t launch_abc_batch(const AbcBatchParams &p, hipStream_t s);
-hipError_t launch_scan_batch(const ScanJob *jobs, int32_t n_jobs, hipStream_t s);
+// split: some job has more than one block (their totals first)
+hipError_t launch_scan_batch(const ScanJob *jobs, int32_t n_jobs, int32_t split, hipStream_t s);
 hipError_t launch_merge_batch(const MergeBatchParams &p, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *dst, int32_t n, int32_t value, hipStream_t s);
 // variant = shape + (kShapeMixed + 1) * m: shape is an ExpShape (every exp

@@ -91,23 +91,23 @@ def fit_paper(runs, short_max_sums: float = 100.0):
 
 
 def fit_with_offset(runs, short_max_sums: float = 100.0):
-    """The same three steps with a constant per-map cost c_0 fitted beside
-    c_SFTs in step 1 and held fixed afterwards."""
-    short = [r for r in runs if r["n_sums"] <= short_max_sums]
-    (c0, c_sft), (e0, e_sft) = _lstsq([[1.0, r["n_sft"]] for r in short], [r["t"] for r in short])
-    base = lambda r: c0 + c_sft * r["n_sft"]  # noqa: E731
-    runs = [r for r in runs if r["n_sums"] > short_max_sums]
-    rect = [r for r in runs if r["kind"] == "rect"]
-    (c_rs, c_f), (e_rs, e_f) = _lstsq([[r["n_sums"], r["n_cells"]] for r in rect],
-                                      [r["t"] - base(r) for r in rect],
-                                      w=1.0 / np.array([r["t"] for r in rect]))
-    ex = [r for r in runs if r["kind"] == "exp"]
-    (c_es,), (e_es,) = _lstsq([[r["n_sums"]] for r in ex],
-                              [r["t"] - base(r) - c_f * r["n_cells"] for r in ex],
-                              w=1.0 / np.array([r["t"] for r in ex]))
-    return {"c_0": (float(c0), float(e0)), "c_SFTs": (float(c_sft), float(e_sft)),
-            "c_sums_rect": (float(c_rs), float(e_rs)), "c_F": (float(c_f), float(e_f)),
-            "c_sums_exp": (float(c_es), float(e_es))}
+    """The model with a constant per-map cost c_0, all five constants in one
+    weighted fit; as in step 1 of the paper, the short runs (N_sums <=
+    short_max_sums) carry c_0 and c_SFTs only.  (Fitted on the short runs
+    alone, c_SFTs would be read off a span of about a hundred SFTs, where a
+    GPU call's time is all c_0: a microsecond of scatter there becomes 50 at
+    5000 SFTs, as much as the whole call.)"""
+    X, t = [], np.array([r["t"] for r in runs], dtype=np.float64)
+    for r in runs:
+        long = r["n_sums"] > short_max_sums
+        rect = r["kind"] == "rect"
+        X.append([1.0, r["n_sft"], r["n_sums"] if long and rect else 0.0, r["n_cells"] if long else 0.0,
+                  r["n_sums"] if long and not rect else 0.0])
+    X = np.asarray(X, dtype=np.float64)
+    scale = np.maximum(np.abs(X).max(axis=0), 1e-300)   # columns span many decades
+    coef, err = _lstsq(X / scale, t, w=1.0 / t)
+    return {k: (float(c / s), float(e / s))
+            for k, c, e, s in zip(("c_0", "c_SFTs", "c_sums_rect", "c_F", "c_sums_exp"), coef, err, scale)}
 
 
 def predict(fit, run) -> float:
