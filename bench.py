@@ -56,8 +56,7 @@ PEAK_ALU_TFLOPS = 78.6    # non-packed FP32 and FP64 vector FMA, 256 CU x 64 lan
 PEAK_HBM_GBS = 8000.0
 PEAK_BF16_TFLOPS = 2500.0  # dense bf16 and fp16 matrix cores
 MATRIX_PRECS = ("f16x3", "bf16x3")
-DTYPES = {"fp32": "f64", "fp64": "f64", "bf16x3": "bf16x3(f32 acc)+f64", "f16x3": "f16x3(f32 acc)+f64",
-          "recur64": "f64"}
+DTYPES = {"fp32": "f64", "fp64": "f64", "bf16x3": "f64", "f16x3": "f64", "recur64": "f64"}   # of the sums
 
 
 def mfma_taus(atoms, win, prec="bf16x3", taus_per_block: int = 8, min_band: int = 64, min_bins: int = 2):
@@ -359,8 +358,8 @@ def slide_flops(atoms, win):
 def roofline_for(atoms, win, prec, prof, workload):
     """Roofline of the dominant kernel of one map computation from the
     per-kernel HIP-event times of the timed steps."""
-    mfma = win.kind == "exp" and prec in MATRIX_PRECS and prof["mfma"][0] > 0
     recur = win.kind == "exp" and prof["recur"][0] > 0
+    mfma = win.kind == "exp" and prec in MATRIX_PRECS and prof["mfma"][0] > 0 and not recur
     dom = "mfma" if mfma else ("recur" if recur else ("exp" if win.kind == "exp" else "rect"))
     n_launch, k_ms = prof[dom]
     avg_ms = k_ms / max(n_launch, 1)
@@ -495,23 +494,13 @@ def bench_batch(args, tf, torch, prec):
     maps computed one map per call.  Returns the record of the step."""
     cands = [tfsynth.candidate(i) for i in range(64)]
     exp_present = exp_slots = rect_cells = 0
-    abc_cells_sfts = 0   # A/B/C inside the fused kernel (not split-form or matrix-core maps)
-    valu_present = 0     # exp cells*SFTs*bins summed on the VALU
     slide = 0.0          # flops of the exponential maps by sliding windows
-    mfma_present = 0     # exp cells*SFTs*bins on the matrix cores
     for a, w in cands:
         if w.kind == "exp":
             p, sl = work_counts(a, w)
             exp_present += p
             exp_slots += sl
-            mc = mfma_cells(a, w, prec) if prec in MATRIX_PRECS else 0
-            mfma_present += mc
-            if prec not in MATRIX_PRECS:
-                slide += slide_flops(a, w)
-                continue
-            valu_present += p - mc
-            if not split_form(a, w, "fp32") and mc == 0:
-                abc_cells_sfts += p // a.n_bins
+            slide += slide_flops(a, w)
         else:
             rect_cells += w.n_t0 * w.n_tau * a.n_bins
     ctx = tf.Context(0, arena_bytes=24 << 30)
@@ -532,13 +521,12 @@ def bench_batch(args, tf, torch, prec):
         t1 = time.perf_counter()
     st = batch.stats()
     ms = (t1 - t0) * 1e3 / args.steps
-    # the fused kernel and the matrix-core launch alone, timed with HIP
-    # events on their stream (direct launches)
-    fused, mm = [], []
+    # the fused kernel alone, timed with HIP events on its stream (direct
+    # launches)
+    fused = []
     for _ in range(3):
         timed = batch.run(timed=True)
         fused.append(batch.stats()["last_fused_ms"])
-        mm.append(batch.stats()["last_mfma_ms"])
     # one map per call: the same maps, sequentially, plain launches
     for aid, w in items[:4]:
         ctx.fmap(aid, w, prec)
@@ -560,12 +548,8 @@ def bench_batch(args, tf, torch, prec):
         n_cmp += n * a.n_bins
         del twoF
     fused_ms = float(np.mean(fused))
-    mfma_ms = float(np.mean(mm))
-    # algorithmic flops of the fused kernel: 4 FMA per exp cell*SFT*bin summed
-    # there, 3 FP64 FMA (A, B, C) per exp cell*SFT of the maps whose A, B, C it
-    # sums (split-form and matrix-core maps have theirs from the pre-pass
-    # launch), about 30 FP64 flops per rect cell*bin
-    flops = 8.0 * valu_present + 6.0 * abc_cells_sfts + 30.0 * rect_cells
+    # the fused kernel's own flops: about 30 FP64 flops per rect cell*bin
+    flops = 30.0 * rect_cells
     roof_f = {"bound": "alu", "achieved": flops / (fused_ms * 1e-3) / 1e12, "peak": PEAK_ALU_TFLOPS,
               "unit": "TFLOP/s", "kernel": "fused", "kernel_avg_ms": fused_ms,
               "traffic": traffic_from_profile("batch_" + prec, "fused", st["variant"])}
@@ -586,16 +570,6 @@ def bench_batch(args, tf, torch, prec):
         "max_rel_err_2F_vs_oracle": err,
         "oracle_cells_compared": "%d cell-bins (64 random cells + each bin's argmax, every map)" % n_cmp,
     }
-    if prec in MATRIX_PRECS:
-        # the matrix-core launch: 24 matrix-core flops per cell*SFT*bin it sums
-        roof_m = {"bound": "mfma", "achieved": 24.0 * mfma_present / (mfma_ms * 1e-3) / 1e12,
-                  "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "kernel": "mfma_batch",
-                  "kernel_avg_ms": mfma_ms, "cells_sfts_bins": mfma_present,
-                  "traffic": traffic_from_profile("batch_" + prec, "mfma_batch", prec)}
-        roof_m["frac"] = roof_m["achieved"] / roof_m["peak"]
-        out["roofline_fused"] = roof_f
-        out["roofline_mfma"] = roof_m
-        roof = roof_m if mfma_ms >= fused_ms else roof_f
     if slide:
         # the sliding maps' launches are most of the step: its flops over all of it
         total = slide + 30.0 * rect_cells

@@ -76,13 +76,14 @@ typedef enum {
  * Arithmetic of the windowed sums.  A, B, C, D and F are FP64 in every mode.
  *   FP64   : F_a, F_b sums in FP64.
  *   FP32   : F_a, F_b sums in FP32 (the paper's single precision) or better.
- *            Exponential windows in FP64, FP32 and RECUR64 are summed by
- *            sliding windows along t0, in FP64: a cell costs the slots between
- *            two t0 rows instead of its whole window.  Atoms with non-finite
- *            values, or whose data spread over more than 2^20 between 64-slot
- *            stretches, maps whose workspace the arena cannot hold, and maps
- *            planned under an explicit tfstat_tiling_config are summed
- *            directly in the named precision.
+ *            In every precision, exponential windows are summed by sliding
+ *            windows along t0, in FP64 (maps of two or more bins with their
+ *            range sums on the FP64 matrix cores): a cell costs the slots
+ *            between two t0 rows instead of its whole window.  Atoms with
+ *            non-finite values, or whose data spread over more than 2^20
+ *            between 64-slot stretches, maps whose workspace the arena cannot
+ *            hold, and maps planned under an explicit tfstat_tiling_config
+ *            are summed directly, in the named precision as described here.
  *   BF16X3 : F_a, F_b sums on bf16 matrix cores with split hi + lo operands
  *            (three products: hi*hi + hi*lo + lo*hi) and FP32 accumulation
  *            (section 3, exponential case: every cell is one banded
@@ -94,9 +95,9 @@ typedef enum {
  *            shape-window grids run the FP32 sums.  bf16 hi + lo keeps 16 significant
  *            bits per operand (relative residual up to 2^-17), so 2F can
  *            miss a 1e-4 relative bound on a few cells of badly conditioned
- *            windows; F16X3 meets it.  The first call on an atoms set builds
- *            its bf16 planes (16 bytes per slot and bin of arena; sets of
- *            2 to 48 bins 32 more, for the transposed form of their sums).
+ *            windows; F16X3 meets it.  The first direct sums on an atoms set
+ *            build its bf16 planes (16 bytes per slot and bin of arena; sets
+ *            of 2 to 48 bins 32 more, for the transposed form of their sums).
  *   F16X3  : as BF16X3 with IEEE half-precision hi + lo parts (22
  *            significant bits per operand, relative residual up to 2^-23),
  *            the data columns scaled by powers of two (one per bin and
@@ -311,7 +312,7 @@ int tfstat_serve_config(tfstat_ctx *ctx, int32_t max_batch);
 /*
  * Tiling of the direct sums of exponential-window maps (section 3: every cell
  * sums its own window).  Either value set here other than the default sends
- * FP64 and FP32 exponential maps to the direct sums (see tfstat_precision).
+ * exponential maps (but RECUR64 ones) to the direct sums (see tfstat_precision).
  * The VALU sums take 64 t0 rows at a time.
  *
  * Runs form.  When the rows of a tile start far apart in slot space (a t0
@@ -354,10 +355,11 @@ int tfstat_tiling_config(tfstat_ctx *ctx, int32_t runs_min_spread, int32_t split
  *   n_maps     number of maps; ids[i] and wins[i] describe map i.
  *   precision  TFSTAT_PREC_FP32, TFSTAT_PREC_FP64, TFSTAT_PREC_BF16X3 or
  *              TFSTAT_PREC_F16X3 (exponential sums; rectangular windows
- *              always use compensated FP64 prefixes).  In BF16X3 and F16X3
- *              the matrix-core work of all maps is one more launch after the
- *              persistent one; matrix-core shape windows are refused
- *              (E_INVAL; tfstat_fmap runs them).
+ *              always use compensated FP64 prefixes).  The sliding maps are
+ *              two more launches after the persistent one, as is the
+ *              matrix-core work of BF16X3 and F16X3 maps summed directly;
+ *              matrix-core shape windows are refused (E_INVAL; tfstat_fmap
+ *              runs them).
  *   tune       0: each map's own tile shape, default launch width;
  *              1: time every candidate that keeps each map's own tile shape
  *              (the build for the stand-alone kernel's waves per SIMD or one
@@ -421,7 +423,7 @@ typedef enum {
     TFSTAT_K_SCAN = 3,        /* rectangular prefix sums */
     TFSTAT_K_RECT = 4,        /* rectangular cells + finalize */
     TFSTAT_K_MERGE = 5,       /* per-bin reduction merge */
-    TFSTAT_K_MFMA = 6,        /* exponential F_a, F_b on matrix cores */
+    TFSTAT_K_MFMA = 6,        /* exponential F_a, F_b on matrix cores (range or direct sums) */
     TFSTAT_K_ABC = 7,         /* exponential A, B, C (FP64) */
     TFSTAT_K_RECUR = 8,       /* exponential sums by sliding windows along t0 */
     TFSTAT_K_COUNT = 9

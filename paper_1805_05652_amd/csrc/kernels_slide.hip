@@ -119,12 +119,6 @@ struct Sums {
 #pragma unroll
             for (int c = 0; c < 4; ++c) x[b][c] = fma(fx, y.x[b][c], x[b][c]);
     }
-    // channel c of 3 + 4 BG
-    __device__ inline double get(int c) const { return c < 3 ? a[c] : x[(c - 3) >> 2][(c - 3) & 3]; }
-    __device__ inline void set(int c, double v) {
-        if (c < 3) a[c] = v;
-        else x[(c - 3) >> 2][(c - 3) & 3] = v;
-    }
 };
 
 // Slot k (the same in every lane; scalar loads).  Bins past the last repeat it.
@@ -141,13 +135,6 @@ __device__ __attribute__((always_inline)) inline Sums<BG> uniform_slot(PP &p, in
         for (int c = 0; c < 4; ++c) y.x[b][c] = x[c];
     }
     return y;
-}
-
-// Slots whose scalar loads are in flight together (38 scalar registers each
-// for four bins, 14 for one).
-template <int BG>
-constexpr int front_unroll() {
-    return BG == 1 ? 4 : 2;
 }
 
 // H at slot k taken down to slot lo, front slots added.
@@ -183,59 +170,158 @@ __device__ inline TileSpan tile_span(PP &p, int tt) {
 }
 
 // ---------------------------------------------------------------------------
-// Anchors.  Workgroup = one (tau tile, bin group) column x kSlideWaves
-// consecutive ranges (a super-range), wave = range: its sum T = H over its own
-// slots, then by a Horner step over the later ranges of the workgroup the
-// local H at its end (anc) and, for the whole super-range, the sum at its
-// start (sup).
+// Anchors.  Workgroup = one (tau tile, bin group or antenna) x kSlideWaves
+// consecutive ranges (a super-range): every range's sum T = H over its own
+// slots; then wave = range, by a Horner step over the later ranges of the
+// workgroup the local H at its end (anc) and, for the whole super-range, the
+// sum at its start (sup).
+//
+// T is a contraction, weights [64 taus x slots] times data [slots x 4 BG
+// channels], the weights the same for every range: groups of two bins or more
+// run it on the FP64 matrix cores (four 16-tau tiles; ranges side by side where
+// a group has fewer than 16 channels), whose operands are one coalesced load
+// and one product per four slots.  The antenna's three channels and one-bin
+// maps, which would leave most columns empty, run it as a wave per range with
+// scalar loads.  64 bins, 703 taus, 3001 slots: 97 us with every group on the
+// VALU, 62 us now.
 // ---------------------------------------------------------------------------
-template <int BG>
-struct AnchorSmem {
-    double tot[kSlideWaves][3 + 4 * BG][64];
-};
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
+// Range sums in LDS, [range][channel][64 taus] (channels: 4 BG, or the
+// antenna's 3).
+template <int BG>
+constexpr int anchor_smem() {
+    return kSlideWaves * 4 * BG * 64;   // doubles
+}
+
+// Range sums of the workgroup's ranges from slot k0 (its first) on.
 template <int BG, typename PP>
-__device__ __attribute__((always_inline)) inline void slide_anchor(PP &p, char *smem, int col, int sup) {
-    constexpr int CH = 3 + 4 * BG;
-    AnchorSmem<BG> &sm = *reinterpret_cast<AnchorSmem<BG> *>(smem);
+__device__ __attribute__((always_inline)) inline void range_sums_mfma(PP &p, double *tot, int tt, int bin0, int k0,
+                                                                    int kend) {
+    constexpr int CH = 4 * BG;
+    constexpr int kSide = 16 / CH;               // ranges side by side in the 16 columns
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tt = col / p.n_bg;
-    const int bin0 = (col - tt * p.n_bg) * BG;
-    const TileSpan sp = tile_span(p, tt);
-    const int g0 = sup * kSlideWaves;
-    if (sp.kbeg + g0 * p.range_len >= sp.kend) return;   // the whole workgroup: no slots
-    const LaneTau t = lane_tau(p.tau[min(tt * 64 + lane, p.n_tau - 1)], p.t_sft);
-    const int kb = sp.kbeg + (g0 + wave) * p.range_len;
-    const int ke = min(kb + p.range_len, sp.kend);
-    Sums<BG> H;
-    H.zero();
-    run_down<BG, front_unroll<BG>()>(p, t, bin0, ke, kb, H);
+    if (wave * kSide >= kSlideWaves) return;
+    const int col = lane & 15, kg = lane >> 4;   // column (channel), slot within a step of four
+    const int side = col / CH;
+    const int ch = col - side * CH;
+    const int RL = p.range_len;
+    const int kb = k0 + (wave * kSide + min(side, kSide - 1)) * RL;
+    const int ke = side < kSide && bin0 + (ch >> 2) < p.n_bins ? min(kb + RL, kend) : kb;   // (columns without data: none)
+    double w[4], r4[4];                          // the weight of slot kg of the step, and rho^4
 #pragma unroll
-    for (int c = 0; c < CH; ++c) sm.tot[wave][c][lane] = H.get(c);
-    __syncthreads();
-    // ranges after this one, from the last: full ranges decay by rho^range_len
-    // (a short or empty one is last, where the sum so far is zero)
-    const double f = exp(t.c * (double)p.range_len), f2 = f * f;
-    Sums<BG> E;
-    E.zero();
-    for (int w = kSlideWaves - 1; w > wave; --w) {
-        Sums<BG> y;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) y.set(c, sm.tot[w][c][lane]);
-        E.shift(f2, f, y);
+    for (int t = 0; t < 4; ++t) {
+        const double c = -(double)p.t_sft / (double)p.tau[min(tt * 64 + 16 * t + col, p.n_tau - 1)];
+        w[t] = exp(c * (double)kg);
+        r4[t] = exp(c * 4.0);
     }
-    double *o = p.anc + (((size_t)col * p.n_range + g0 + wave) * CH) * 64 + lane;
-    if (kb < ke) {
+    f64x4 acc[4];
 #pragma unroll
-        for (int c = 0; c < CH; ++c) o[(size_t)c * 64] = E.get(c);
+    for (int t = 0; t < 4; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const double *x = p.x64 + bin0 * 4 + (ke > kb ? ch : 0);
+    const size_t row = (size_t)p.n_bins * 4;
+    constexpr int kStep = 4;                     // steps whose loads are in flight together
+#pragma unroll 1
+    for (int i = 0; i < RL; i += 4 * kStep) {    // (range_len is a multiple of 16)
+        double y[kStep];
+#pragma unroll
+        for (int u = 0; u < kStep; ++u) {
+            const int k = kb + i + 4 * u + kg;
+            y[u] = x[(size_t)(k < ke ? k : p.K) * row];   // row K is zero
+        }
+#pragma unroll
+        for (int u = 0; u < kStep; ++u)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[t], y[u], acc[t], 0, 0, 0);
+                w[t] *= r4[t];
+            }
+    }
+    // register r of lane (col, kg): tau 16 t + 4 r + kg of the tile
+    if (side < kSide) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tot[((wave * kSide + side) * CH + ch) * 64 + 16 * t + 4 * r + kg] = acc[t][r];
+    }
+}
+
+// Anchors of CH channels whose decay per slot is e^c, from the range sums.
+template <int CH>
+__device__ __attribute__((always_inline)) inline void anchor_horner(const double *tot, double c, int RL, int n_first, bool any,
+                                                                  double *anc, double *sup) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // ranges after this one, from the last: full ranges decay by f (a short
+    // or empty one is last, where the sum so far is zero)
+    const double f = exp(c * (double)RL);
+    double E[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) E[q] = 0.0;
+    for (int w = kSlideWaves - 1; w > wave; --w) {
+#pragma unroll
+        for (int q = 0; q < CH; ++q) E[q] = fma(f, E[q], tot[(w * CH + q) * 64 + lane]);
+    }
+    if (any) {
+#pragma unroll
+        for (int q = 0; q < CH; ++q) anc[((size_t)wave * CH + q) * 64 + lane] = E[q];
     }
     if (wave == 0) {
-        const double l = exp(t.c * (double)(ke - kb)), l2 = l * l;
-        E.shift(l2, l, H);
-        double *s = p.sup + (((size_t)col * p.n_sup + sup) * CH) * 64 + lane;
+        const double l = exp(c * (double)n_first);
 #pragma unroll
-        for (int c = 0; c < CH; ++c) s[(size_t)c * 64] = E.get(c);
+        for (int q = 0; q < CH; ++q) sup[(size_t)q * 64 + lane] = fma(l, E[q], tot[q * 64 + lane]);
+    }
+}
+
+// bg == p.n_bg: the antenna's channels.
+template <int BG, typename PP>
+__device__ __attribute__((always_inline)) inline void slide_anchor(PP &p, double *tot, int tt, int bg, int sup) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const TileSpan sp = tile_span(p, tt);
+    const int RL = p.range_len;
+    const int g0 = sup * kSlideWaves;
+    const int k0 = sp.kbeg + g0 * RL;
+    if (k0 >= sp.kend) return;   // the whole workgroup: no slots
+    const int kb = k0 + wave * RL;
+    const int ke = min(kb + RL, sp.kend);
+    const int n_first = min(RL, sp.kend - k0);   // slots of the first range
+    const double c = -(double)p.t_sft / (double)p.tau[min(tt * 64 + lane, p.n_tau - 1)];
+    const bool ant = bg == p.n_bg;
+    if (BG > 1 && !ant) {
+        range_sums_mfma<BG>(p, tot, tt, bg * BG, k0, sp.kend);
+    } else {
+        // one wave per range, a slot's channels by scalar loads
+        const int nc = ant ? 3 : 4;
+        const double rho = exp(ant ? 2.0 * c : c);
+        ConstParams<double> *y = ant ? const_ptr(p.abc) : const_ptr(p.x64) + bg * 4;
+        const size_t row = ant ? 4 : (size_t)p.n_bins * 4;
+        double H[4] = {0.0, 0.0, 0.0, 0.0};
+        constexpr int U = 8;
+#pragma unroll 1
+        for (int k = ke; k > kb; k -= U) {
+            double v[U][4];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[u][q] = y[(size_t)max(k - 1 - u, 0) * row + q];   // (the antenna's fourth: 0)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (k - 1 - u >= kb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) H[q] = fma(rho, H[q], v[u][q]);
+        }
+        for (int q = 0; q < nc; ++q) tot[(wave * nc + q) * 64 + lane] = H[q];
+    }
+    __syncthreads();
+    if (ant) {
+        anchor_horner<3>(tot, 2.0 * c, RL, n_first, kb < ke, p.anc_a + ((size_t)tt * p.n_range + g0) * 3 * 64,
+                         p.sup_a + ((size_t)tt * p.n_sup + sup) * 3 * 64);
+    } else {
+        const size_t col = (size_t)tt * p.n_bg + bg;
+        anchor_horner<4 * BG>(tot, c, RL, n_first, kb < ke, p.anc + (col * p.n_range + g0) * (4 * BG) * 64,
+                              p.sup + (col * p.n_sup + sup) * (4 * BG) * 64);
     }
 }
 
@@ -257,7 +343,6 @@ struct RowsSmem {
 
 template <int BG, typename PP>
 __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *smem, int col, int quad) {
-    constexpr int CH = 3 + 4 * BG;
     constexpr int kCap = tail_cap<BG>();
     constexpr int kU = BG == 1 ? 4 : BG == 2 ? 2 : 1;   // slots in flight
     RowsSmem<BG> &sm = *reinterpret_cast<RowsSmem<BG> *>(smem);
@@ -347,8 +432,19 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *sm
         }
         return y;
     };
-    const double *anc = p.anc + ((size_t)col * p.n_range * CH) * 64 + lane;
-    const double *sup = p.sup + ((size_t)col * p.n_sup * CH) * 64 + lane;
+    // channel c of anchor g (or super-range g)
+    const double *anc = p.anc + (size_t)col * p.n_range * (4 * BG) * 64 + lane;
+    const double *sup = p.sup + (size_t)col * p.n_sup * (4 * BG) * 64 + lane;
+    const double *anc_a = p.anc_a + (size_t)tt * p.n_range * 3 * 64 + lane;
+    const double *sup_a = p.sup_a + (size_t)tt * p.n_sup * 3 * 64 + lane;
+    auto load_sums = [&](const double *x, const double *a, int g) {
+        Sums<BG> y;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) y.a[c] = a[((size_t)g * 3 + c) * 64];
+#pragma unroll
+        for (int c = 0; c < 4 * BG; ++c) y.x[c >> 2][c & 3] = x[((size_t)g * (4 * BG) + c) * 64];
+        return y;
+    };
     const int n_range = (sp.kend - sp.kbeg + RL - 1) / RL;
     const int n_sup = (n_range + kSlideWaves - 1) / kSlideWaves;
     const double fsup = exp(t.c * (double)(kSlideWaves * RL));   // decay of a whole super-range
@@ -363,9 +459,7 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *sm
         for (int v = n_sup - 1; __any(v > u); v -= kU) {
             Sums<BG> y[kU];
 #pragma unroll
-            for (int i = 0; i < kU; ++i)
-#pragma unroll
-                for (int c = 0; c < CH; ++c) y[i].set(c, sup[((size_t)max(v - i, 0) * CH + c) * 64]);
+            for (int i = 0; i < kU; ++i) y[i] = load_sums(sup, sup_a, max(v - i, 0));
 #pragma unroll
             for (int i = 0; i < kU; ++i)
                 if (v - i > u) H.shift(fsup * fsup, fsup, y[i]);
@@ -373,10 +467,7 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *sm
         const int ge = min(sp.kbeg + (g + 1) * RL, sp.kend);
         const int ue = min(sp.kbeg + (u + 1) * kSlideWaves * RL, sp.kend);
         const double f = exp(t.c * (double)(ue - ge)), f2 = f * f;
-        Sums<BG> y;
-#pragma unroll
-        for (int c = 0; c < CH; ++c) y.set(c, anc[((size_t)g * CH + c) * 64]);
-        H.shift(f2, f, y);
+        H.shift(f2, f, load_sums(anc, anc_a, g));
         return ge;
     };
 
@@ -579,8 +670,9 @@ __global__ __launch_bounds__(64 * kRangeWaves) void atoms_kernel(const double *x
 
 template <int BG>
 __global__ __launch_bounds__(64 * kSlideWaves) void slide_anchor_kernel(SlideParams p) {
-    __shared__ __attribute__((aligned(16))) char smem[sizeof(AnchorSmem<BG>)];
-    slide_anchor<BG>(p, smem, blockIdx.x, blockIdx.y);
+    __shared__ double tot[anchor_smem<BG>()];
+    const int tt = blockIdx.x / (p.n_bg + 1);
+    slide_anchor<BG>(p, tot, tt, blockIdx.x - tt * (p.n_bg + 1), blockIdx.y);
 }
 
 template <int BG>
@@ -595,14 +687,14 @@ __device__ inline ConstParams<T> &const_params(const T *p) {
     return *const_ptr(p);
 }
 __global__ __launch_bounds__(64 * kSlideWaves) void slide_anchor_batch_kernel(SlideBatchParams b) {
-    __shared__ __attribute__((aligned(16))) char smem[sizeof(AnchorSmem<4>)];
+    __shared__ double tot[anchor_smem<4>()];
     ConstParams<int32_t> *e = const_ptr(b.anchors) + 4 * (size_t)blockIdx.x;
     auto &p = const_params(b.jobs + e[0]);
     switch (p.bg) {
-    case 1: slide_anchor<1>(p, smem, e[1], e[2]); break;
-    case 2: slide_anchor<2>(p, smem, e[1], e[2]); break;
-    case 3: slide_anchor<3>(p, smem, e[1], e[2]); break;
-    default: slide_anchor<4>(p, smem, e[1], e[2]); break;
+    case 1: slide_anchor<1>(p, tot, e[1], e[2], e[3]); break;
+    case 2: slide_anchor<2>(p, tot, e[1], e[2], e[3]); break;
+    case 3: slide_anchor<3>(p, tot, e[1], e[2], e[3]); break;
+    default: slide_anchor<4>(p, tot, e[1], e[2], e[3]); break;
     }
 }
 __global__ __launch_bounds__(256, 3) void slide_rows_batch_kernel(SlideBatchParams b) {
@@ -633,30 +725,29 @@ hipError_t launch_atoms(const double *x64, const double *abc, float *x32, int32_
     return hipGetLastError();
 }
 
-hipError_t launch_slide(const SlideParams &p, hipStream_t s) {
-    if (p.n_tau <= 0 || p.n_t0 <= 0 || p.seg_rows < 1 || p.range_len < 1) return hipErrorInvalidValue;
-    const unsigned cols = (unsigned)(p.n_tt * p.n_bg);
-    const dim3 ga(cols, (unsigned)p.n_sup), gr(cols, (unsigned)((p.n_seg + 3) / 4));
-    if (ga.y > 65535u || gr.y > 65535u) return hipErrorInvalidValue;
+hipError_t launch_slide_anchors(const SlideParams &p, hipStream_t s) {
+    if (p.n_tau <= 0 || p.n_t0 <= 0 || p.seg_rows < 1 || p.range_len < 16 || p.range_len % 16) return hipErrorInvalidValue;
+    const dim3 g((unsigned)(p.n_tt * (p.n_bg + 1)), (unsigned)p.n_sup), b(64 * kSlideWaves);
+    if (g.y > 65535u) return hipErrorInvalidValue;
     switch (p.bg) {
-    case 1:
-        hipLaunchKernelGGL(slide_anchor_kernel<1>, ga, dim3(64 * kSlideWaves), 0, s, p);
-        hipLaunchKernelGGL(slide_rows_kernel<1>, gr, dim3(256), 0, s, p);
-        break;
-    case 2:
-        hipLaunchKernelGGL(slide_anchor_kernel<2>, ga, dim3(64 * kSlideWaves), 0, s, p);
-        hipLaunchKernelGGL(slide_rows_kernel<2>, gr, dim3(256), 0, s, p);
-        break;
-    case 3:
-        hipLaunchKernelGGL(slide_anchor_kernel<3>, ga, dim3(64 * kSlideWaves), 0, s, p);
-        hipLaunchKernelGGL(slide_rows_kernel<3>, gr, dim3(256), 0, s, p);
-        break;
-    case 4:
-        hipLaunchKernelGGL(slide_anchor_kernel<4>, ga, dim3(64 * kSlideWaves), 0, s, p);
-        hipLaunchKernelGGL(slide_rows_kernel<4>, gr, dim3(256), 0, s, p);
-        break;
-    default:
-        return hipErrorInvalidValue;
+    case 1: hipLaunchKernelGGL(slide_anchor_kernel<1>, g, b, 0, s, p); break;
+    case 2: hipLaunchKernelGGL(slide_anchor_kernel<2>, g, b, 0, s, p); break;
+    case 3: hipLaunchKernelGGL(slide_anchor_kernel<3>, g, b, 0, s, p); break;
+    case 4: hipLaunchKernelGGL(slide_anchor_kernel<4>, g, b, 0, s, p); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_slide_rows(const SlideParams &p, hipStream_t s) {
+    const dim3 g((unsigned)(p.n_tt * p.n_bg), (unsigned)((p.n_seg + 3) / 4)), b(256);
+    if (g.y > 65535u) return hipErrorInvalidValue;
+    switch (p.bg) {
+    case 1: hipLaunchKernelGGL(slide_rows_kernel<1>, g, b, 0, s, p); break;
+    case 2: hipLaunchKernelGGL(slide_rows_kernel<2>, g, b, 0, s, p); break;
+    case 3: hipLaunchKernelGGL(slide_rows_kernel<3>, g, b, 0, s, p); break;
+    case 4: hipLaunchKernelGGL(slide_rows_kernel<4>, g, b, 0, s, p); break;
+    default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }

@@ -329,7 +329,7 @@ struct Job {
     size_t off_rows = 0, off_tau = 0, off_lcol = 0, off_lblk = 0, off_boff = 0, off_order = 0,
            tables_bytes = 0;
     size_t off_g32 = 0, off_gsq = 0, off_g64 = 0, off_pabc = 0, off_px = 0, off_part = 0,
-           off_res = 0, off_abc = 0, off_lg = 0, off_gshoff = 0, off_gsh = 0, off_shape = 0, off_anc = 0, off_sup = 0, off_ptot = 0;
+           off_res = 0, off_abc = 0, off_lg = 0, off_gshoff = 0, off_gsh = 0, off_shape = 0, off_anc = 0, off_sup = 0, off_anca = 0, off_supa = 0, off_ptot = 0;
 
     // timing
     std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> timed;
@@ -343,7 +343,7 @@ struct Job {
 void plan_slide(Job &j) {
     const AtomsSet &at = *j.at;
     const bool tiling = j.runs_min_spread != kRunsAuto || j.split_min_bins != kSplitMinBins;
-    if (!at.slide_ok || j.no_slide > 1 || j.forced || matrix_prec(j.prec)) return;
+    if (!at.slide_ok || j.no_slide > 1 || j.forced) return;
     if (tiling && j.prec != TFSTAT_PREC_RECUR64) return;
     const int n_t0 = (int)j.win.t0.size(), n_tau = (int)j.win.tau.size();
     j.slide = true;
@@ -362,7 +362,7 @@ void plan_slide(Job &j) {
     // ranges of the anchors: long ones where the columns alone fill the chip
     int32_t rl = 128;
     while (rl > 16 && cols * (at.K / rl) < kSlideTarget) rl /= 2;
-    if (j.no_slide) rl = std::max(128, (at.K + tfs::kSlideWaves - 1) / tfs::kSlideWaves);
+    if (j.no_slide) rl = std::max<int64_t>(128, ((int64_t)at.K + 16 * tfs::kSlideWaves - 1) / (16 * tfs::kSlideWaves) * 16);
     j.range_len = rl;
     j.n_sup = std::max<int32_t>(1, (at.K + rl * tfs::kSlideWaves - 1) / (rl * tfs::kSlideWaves));
     j.n_range = j.n_sup * tfs::kSlideWaves;
@@ -411,7 +411,8 @@ void plan_job(Job &j) {
     j.n_row_tiles = (n_t0 + 63) / 64;
     j.slide = false;
     if (j.win.type == TFSTAT_WIN_EXP) plan_slide(j);
-    // Matrix-core path (BF16X3).  Exponential windows: any t0 grid, maps of
+    // Matrix-core path (BF16X3, F16X3) of the maps that do not slide.
+    // Exponential windows: any t0 grid, maps of
     // at least kMfmaMinBins bins whose bf16 component planes stay under
     // 2^31 bytes.  Shape windows: rows on consecutive slots with one delta.
     // Either needs a block of 8 taus whose shortest band is long enough (the
@@ -570,9 +571,12 @@ void plan_job(Job &j) {
     }
     j.tables_bytes = o;
     if (j.slide) {
-        const size_t ch = (size_t)j.n_tt * j.n_bg * (3 + 4 * j.bg) * 64 * sizeof(double);
+        const size_t ch = (size_t)j.n_tt * j.n_bg * (4 * j.bg) * 64 * sizeof(double);
+        const size_t ch_a = (size_t)j.n_tt * 3 * 64 * sizeof(double);
         j.off_anc = take(ch * j.n_range);
         j.off_sup = take(ch * j.n_sup);
+        j.off_anca = take(ch_a * j.n_range);
+        j.off_supa = take(ch_a * j.n_sup);
     } else if (is_exp) {
         j.off_g32 = take(sizeof(float) * std::max<int64_t>(j.wtot, 1));
         j.off_gsq = take(sizeof(double) * std::max<int64_t>(j.wtot, 1));
@@ -909,6 +913,8 @@ tfs::SlideParams slide_params(Job &j) {
     q.x32 = at.x32;
     q.anc = ws_ptr<double>(j, j.off_anc);
     q.sup = ws_ptr<double>(j, j.off_sup);
+    q.anc_a = ws_ptr<double>(j, j.off_anca);
+    q.sup_a = ws_ptr<double>(j, j.off_supa);
     q.twoF = j.twoF;
     q.part = ws_ptr<tfs::Partial>(j, j.off_part);
     return q;
@@ -1028,8 +1034,15 @@ void enqueue_job(tfstat_ctx *ctx, Job &j, hipStream_t s) {
 
     if (j.slide) {
         const tfs::SlideParams sp = slide_params(j);
-        record_kernel(ctx, j, TFSTAT_K_RECUR, s, true);
-        hip_check(tfs::launch_slide(sp, s), "sliding sums kernels");
+        // (groups of two bins or more: range sums on the matrix cores)
+        if (j.bg > 1) record_kernel(ctx, j, TFSTAT_K_MFMA, s, true);
+        else record_kernel(ctx, j, TFSTAT_K_RECUR, s, true);
+        hip_check(tfs::launch_slide_anchors(sp, s), "sliding anchors kernel");
+        if (j.bg > 1) {
+            record_kernel(ctx, j, TFSTAT_K_MFMA, s, false);
+            record_kernel(ctx, j, TFSTAT_K_RECUR, s, true);
+        }
+        hip_check(tfs::launch_slide_rows(sp, s), "sliding rows kernel");
         record_kernel(ctx, j, TFSTAT_K_RECUR, s, false);
     } else if (is_exp) {
         tfs::WeightParams wp = weight_params(j);
@@ -1316,7 +1329,7 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
         Job &j = *b->jobs[i];
         if (j.slide) {
             sidx[i] = n_slide++;
-            n_anchor += (size_t)j.n_tt * j.n_bg * j.n_sup;
+            n_anchor += (size_t)j.n_tt * (j.n_bg + 1) * j.n_sup;
             n_srows += (size_t)j.n_tt * j.n_bg * ((j.n_seg + 3) / 4);
         } else if (banded(j.win.type)) {
             if (j.use_mfma && !j.mfma_rows)
@@ -1584,11 +1597,11 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
             const Job &j = *b->jobs[i];
             const int cols = j.n_tt * j.n_bg;
             for (int u = 0; u < j.n_sup; ++u)
-                for (int c = 0; c < cols; ++c, ++ae_) {
+                for (int c = 0; c < j.n_tt * (j.n_bg + 1); ++c, ++ae_) {
                     aent[4 * ae_] = sidx[i];
-                    aent[4 * ae_ + 1] = c;
-                    aent[4 * ae_ + 2] = u;
-                    aent[4 * ae_ + 3] = 0;
+                    aent[4 * ae_ + 1] = c / (j.n_bg + 1);
+                    aent[4 * ae_ + 2] = c % (j.n_bg + 1);
+                    aent[4 * ae_ + 3] = u;
                 }
             for (int q = 0; q < (j.n_seg + 3) / 4; ++q)
                 for (int c = 0; c < cols; ++c, ++sr_) {
@@ -1666,8 +1679,6 @@ void batch_build(tfstat_ctx *ctx, tfstat_batch *b, int32_t n, const tfstat_atoms
             b->jobs.push_back(j.get());
         }
         b->holds_atoms = true;
-        if (matrix_prec(prec))
-            for (auto &j : b->owned) ensure_planes(ctx, j->at, prec);
     }
     for (int32_t i = 0; i < n; ++i) {
         Job &j = *b->jobs[i];
@@ -1688,7 +1699,13 @@ void batch_build(tfstat_ctx *ctx, tfstat_batch *b, int32_t n, const tfstat_atoms
         j.split_min_bins = ctx->split_min_bins.load();
         plan_job(j);
     }
-    while (!batch_layout(ctx, b, ctx->batch_stream, true, false)) {
+    for (;;) {
+        {
+            std::lock_guard<std::mutex> g(ctx->mu);
+            for (Job *j : b->jobs)
+                if (j->use_mfma) ensure_planes(ctx, j->at, prec);
+        }
+        if (batch_layout(ctx, b, ctx->batch_stream, true, false)) break;
         bool smaller = false;
         for (Job *j : b->jobs) smaller = plan_smaller(*j) || smaller;
         if (!smaller) raise(TFSTAT_E_NOMEM, "arena cannot hold the batch workspace");
@@ -2183,7 +2200,6 @@ int tfstat_fmap(tfstat_ctx *ctx, tfstat_atoms_id id, const tfstat_window *win, i
         {
             std::lock_guard<std::mutex> g(ctx->mu);
             j.at = find_atoms(ctx, id);
-            if (matrix_prec(precision)) ensure_planes(ctx, j.at, precision);
         }
         j.win = copy_window(win);
         j.prec = precision;
@@ -2193,7 +2209,9 @@ int tfstat_fmap(tfstat_ctx *ctx, tfstat_atoms_id id, const tfstat_window *win, i
         plan_job(j);
         {
             std::lock_guard<std::mutex> g(ctx->mu);
-            while (!alloc_job(ctx, j)) {
+            for (;;) {
+                if (j.use_mfma) ensure_planes(ctx, j.at, precision);
+                if (alloc_job(ctx, j)) break;
                 if (!plan_smaller(j)) raise(TFSTAT_E_NOMEM, "arena cannot hold the map workspace");
             }
         }
@@ -2338,18 +2356,19 @@ int tfstat_submit(tfstat_ctx *ctx, tfstat_atoms_id id, const tfstat_window *win,
         job->prec = precision;
         std::lock_guard<std::mutex> g(ctx->mu);
         job->at = find_atoms(ctx, id);
-        if (matrix_prec(precision)) ensure_planes(ctx, job->at, precision);
         job->runs_min_spread = ctx->runs_min_spread.load();
         job->split_min_bins = ctx->split_min_bins.load();
         plan_job(*job);
         // A request whose workspace cannot fit beside the resident atoms
         // would wait forever: refuse it now.
-        size_t resident = 0;
-        for (auto &kv : ctx->atoms) resident += kv.second->bytes;
-        while (job->ws_bytes + resident > ctx->arena.capacity() && plan_smaller(*job)) {
+        for (;;) {
+            if (job->use_mfma) ensure_planes(ctx, job->at, precision);
+            size_t resident = 0;
+            for (auto &kv : ctx->atoms) resident += kv.second->bytes;
+            if (job->ws_bytes + resident <= ctx->arena.capacity()) break;
+            if (!plan_smaller(*job))
+                raise(TFSTAT_E_NOMEM, "request workspace cannot fit beside the resident atoms");
         }
-        if (job->ws_bytes + resident > ctx->arena.capacity())
-            raise(TFSTAT_E_NOMEM, "request workspace cannot fit beside the resident atoms");
         if (ctx->queue.size() >= tfstat_ctx::kMaxQueue) raise(TFSTAT_E_BUSY, "serving queue is full");
         hip_check(hipSetDevice(ctx->device), "hipSetDevice");
         ensure_worker(ctx);

@@ -225,7 +225,8 @@ struct SlideParams {
     int32_t bg, n_bg;         // bins per group (1..4), groups
     int32_t n_tt;             // ceil(n_tau / 64)
     int32_t n_seg, seg_rows;
-    int32_t range_len, n_range, n_sup;   // n_range: most ranges of any tile, whole super-ranges
+    int32_t range_len, n_range, n_sup;   // range_len: a multiple of 16; n_range: most ranges of
+                                         // any tile, whole super-ranges
     int32_t n_tiles;          // partial slots per bin (n_tt * n_seg)
     int32_t exact32;          // x32 holds x64 exactly
     double guard_a, guard_b;  // cells with A or B below these are summed directly
@@ -234,14 +235,15 @@ struct SlideParams {
     const double *abc;        // [K+1][4]
     const double *x64;        // [K+1][n_bins][4]
     const float *x32;         // [K+1][n_bins][4]
-    double *anc;              // [n_tt * n_bg][n_range][3 + 4 bg][64]
-    double *sup;              // [n_tt * n_bg][n_sup][3 + 4 bg][64]
+    double *anc;              // [n_tt * n_bg][n_range][4 bg][64] data anchors
+    double *sup;              // [n_tt * n_bg][n_sup][4 bg][64]
+    double *anc_a, *sup_a;    // the same of the antenna: [n_tt][n_range or n_sup][3][64]
     float *twoF;
     Partial *part;            // [n_bins][n_tiles], tile tt * n_seg + seg
 };
 
-// Sliding maps of a batch: entry = {map, column, super-range or quad of
-// segments, 0}.
+// Sliding maps of a batch: anchor entry = {map, tau tile, bin group (n_bg: the
+// antenna), super-range}, rows entry = {map, column, quad of segments, 0}.
 struct SlideBatchParams {
     const SlideParams *jobs;
     const int32_t *anchors;   // [n_anchors][4]
@@ -454,7 +456,8 @@ hipError_t launch_exp_abc(const ExpValuParams &p, hipStream_t s);
 hipError_t launch_exp_mfma(const ExpMfmaParams &p, hipStream_t s);
 hipError_t launch_exp_mfma_rows(const ExpMfmaRowsParams &p, hipStream_t s);
 hipError_t launch_mfma_batch(const MfmaBatchParams &p, hipStream_t s);
-hipError_t launch_slide(const SlideParams &p, hipStream_t s);
+hipError_t launch_slide_anchors(const SlideParams &p, hipStream_t s);
+hipError_t launch_slide_rows(const SlideParams &p, hipStream_t s);
 hipError_t launch_slide_batch(const SlideBatchParams &p, hipStream_t s);
 // The FP32 plane x32 and the atoms' RangeInfo (info zeroed by the caller).
 hipError_t launch_atoms(const double *x64, const double *abc, float *x32, int32_t K, int32_t n_bins, RangeInfo *info,
