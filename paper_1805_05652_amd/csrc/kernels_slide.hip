@@ -88,6 +88,12 @@ __device__ inline int end_slot(int k0, int delta, int q, int r, int K) {
     return clamp_slot(k0 + q + (r > delta ? 1 : 0), K);
 }
 
+// h <- f h + y with y in scalar registers (the compiler would copy y to vector
+// registers first, two moves a double).
+__device__ __attribute__((always_inline)) inline void fma_scalar(double &h, double f, double y) {
+    asm("v_fma_f64 %0, %1, %0, %2" : "+v"(h) : "v"(f), "s"(y));
+}
+
 // Channel sums of BG bins and the antenna.
 template <int BG>
 struct Sums {
@@ -109,6 +115,15 @@ struct Sums {
         for (int b = 0; b < BG; ++b)
 #pragma unroll
             for (int c = 0; c < 4; ++c) x[b][c] = fma(fx, x[b][c], y.x[b][c]);
+    }
+    // the same for a slot that is uniform over the wave
+    __device__ inline void shift_uniform(double fa, double fx, const Sums &y) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) fma_scalar(a[c], fa, y.a[c]);
+#pragma unroll
+        for (int b = 0; b < BG; ++b)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) fma_scalar(x[b][c], fx, y.x[b][c]);
     }
     // this <- this + (fa, fx) y
     __device__ inline void add(double fa, double fx, const Sums &y) {
@@ -148,25 +163,8 @@ __device__ __attribute__((always_inline)) inline void run_down(PP &p, const Lane
         for (int u = 0; u < U; ++u) y[u] = uniform_slot<BG>(p, max(k - 1 - u, 0), bin0);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (k - 1 - u >= lo) H.shift(t.rho2, t.rho, y[u]);
+            if (k - 1 - u >= lo) H.shift_uniform(t.rho2, t.rho, y[u]);
     }
-}
-
-// Slots [kbeg, kend) that the windows of a tau tile's segment heads reach;
-// ranges of range_len slots from kbeg.
-struct TileSpan {
-    int kbeg, kend;
-};
-template <typename PP>
-__device__ inline TileSpan tile_span(PP &p, int tt) {
-    ConstParams<RowPlan> *rows = const_ptr(p.rows);
-    TileSpan s;
-    const int m0 = min(p.seg_rows, p.n_t0) - 1;
-    s.kbeg = clamp_slot(rows[m0].k0, p.K);
-    int q, r;
-    tau_qr(const_ptr(p.tau)[min(tt * 64 + 63, p.n_tau - 1)], p.t_sft, q, r);
-    s.kend = max(end_slot(rows[p.n_t0 - 1].k0, rows[p.n_t0 - 1].delta, q, r, p.K), s.kbeg);
-    return s;
 }
 
 // ---------------------------------------------------------------------------
@@ -177,13 +175,14 @@ __device__ inline TileSpan tile_span(PP &p, int tt) {
 // sum at its start (sup).
 //
 // T is a contraction, weights [64 taus x slots] times data [slots x 4 BG
-// channels], the weights the same for every range: groups of two bins or more
+// channels], the weights the same for every range: maps of two bins or more
 // run it on the FP64 matrix cores (four 16-tau tiles; ranges side by side where
 // a group has fewer than 16 channels), whose operands are one coalesced load
 // and one product per four slots.  The antenna's three channels and one-bin
-// maps, which would leave most columns empty, run it as a wave per range with
-// scalar loads.  64 bins, 703 taus, 3001 slots: 97 us with every group on the
-// VALU, 62 us now.
+// maps, which would leave most of the chip idle, run it as a wave per range
+// with scalar loads.  64 bins, 703 taus, 3001 slots: 97 us with every group on
+// the VALU, 56 us now, of which the writes of H (45 MB) are about 10 us and the
+// rest is waits of the chain over a range's slots.
 // ---------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -221,15 +220,21 @@ __device__ __attribute__((always_inline)) inline void range_sums_mfma(PP &p, dou
     for (int t = 0; t < 4; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
     const double *x = p.x64 + bin0 * 4 + (ke > kb ? ch : 0);
     const size_t row = (size_t)p.n_bins * 4;
-    constexpr int kStep = 4;                     // steps whose loads are in flight together
-#pragma unroll 1
-    for (int i = 0; i < RL; i += 4 * kStep) {    // (range_len is a multiple of 16)
-        double y[kStep];
+    // four steps (range_len is a multiple of 16) at a time, the next four's
+    // loads in flight
+    constexpr int kStep = 4;
+    auto load = [&](int i, double *y) {
 #pragma unroll
         for (int u = 0; u < kStep; ++u) {
             const int k = kb + i + 4 * u + kg;
             y[u] = x[(size_t)(k < ke ? k : p.K) * row];   // row K is zero
         }
+    };
+    double y[kStep], nx[kStep];
+    load(0, y);
+#pragma unroll 1
+    for (int i = 0; i < RL; i += 4 * kStep) {
+        load(i + 4 * kStep, nx);
 #pragma unroll
         for (int u = 0; u < kStep; ++u)
 #pragma unroll
@@ -237,6 +242,8 @@ __device__ __attribute__((always_inline)) inline void range_sums_mfma(PP &p, dou
                 acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[t], y[u], acc[t], 0, 0, 0);
                 w[t] *= r4[t];
             }
+#pragma unroll
+        for (int u = 0; u < kStep; ++u) y[u] = nx[u];
     }
     // register r of lane (col, kg): tau 16 t + 4 r + kg of the tile
     if (side < kSide) {
@@ -279,18 +286,18 @@ template <int BG, typename PP>
 __device__ __attribute__((always_inline)) inline void slide_anchor(PP &p, double *tot, int tt, int bg, int sup) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const TileSpan sp = tile_span(p, tt);
+    const int kend = const_ptr(p.tiles)[tt].kend;
     const int RL = p.range_len;
     const int g0 = sup * kSlideWaves;
-    const int k0 = sp.kbeg + g0 * RL;
-    if (k0 >= sp.kend) return;   // the whole workgroup: no slots
+    const int k0 = p.kbeg + g0 * RL;
+    if (k0 >= kend) return;   // the whole workgroup: no slots
     const int kb = k0 + wave * RL;
-    const int ke = min(kb + RL, sp.kend);
-    const int n_first = min(RL, sp.kend - k0);   // slots of the first range
+    const int ke = min(kb + RL, kend);
+    const int n_first = min(RL, kend - k0);   // slots of the first range
     const double c = -(double)p.t_sft / (double)p.tau[min(tt * 64 + lane, p.n_tau - 1)];
     const bool ant = bg == p.n_bg;
-    if (BG > 1 && !ant) {
-        range_sums_mfma<BG>(p, tot, tt, bg * BG, k0, sp.kend);
+    if (!ant && (BG > 1 || p.n_bins > 1)) {
+        range_sums_mfma<BG>(p, tot, tt, bg * BG, k0, kend);
     } else {
         // one wave per range, a slot's channels by scalar loads
         const int nc = ant ? 3 : 4;
@@ -325,114 +332,109 @@ __device__ __attribute__((always_inline)) inline void slide_anchor(PP &p, double
     }
 }
 
-// ---------------------------------------------------------------------------
-// Rows.
-// ---------------------------------------------------------------------------
-// Back slots of a workgroup's four segments, staged once; entry kTailCap is
-// zero (lanes without a slot to drop read it).
-template <int BG>
-constexpr int tail_cap() {
-    return BG == 1 ? 1023 : BG == 2 ? 767 : 607;
+// The super-ranges' sums of one (tau tile, bin group or antenna) into H at
+// their ends, in place: thread = (channel, tau), from the last down.
+template <typename PP>
+__device__ __attribute__((always_inline)) inline void slide_supers(PP &p, int tt, int bg) {
+    const bool ant = bg == p.n_bg;
+    const int CH = ant ? 3 : 4 * p.bg;
+    const int len = kSlideWaves * p.range_len;
+    const int n = (const_ptr(p.tiles)[tt].kend - p.kbeg + len - 1) / len;
+    const int lane = threadIdx.x & 63;
+    const double c = -(double)p.t_sft / (double)p.tau[min(tt * 64 + lane, p.n_tau - 1)] * (double)len;
+    const double f = exp(ant ? 2.0 * c : c);
+    for (int q = threadIdx.x >> 6; q < CH; q += 4) {
+        double *s = ant ? p.sup_a + (size_t)tt * p.n_sup * 3 * 64 : p.sup + ((size_t)tt * p.n_bg + bg) * p.n_sup * CH * 64;
+        s += q * 64 + lane;
+        double H = 0.0;   // (a short super-range is the last: nothing comes after it)
+#pragma unroll 8
+        for (int u = n - 1; u >= 0; --u) {
+            const double v = s[(size_t)u * CH * 64];
+            s[(size_t)u * CH * 64] = H;
+            H = fma(f, H, v);
+        }
+    }
 }
-template <int BG>
-struct RowsSmem {
-    double2 ab[tail_cap<BG>() + 1];
-    double c[tail_cap<BG>() + 1];
-    float4 x[BG][tail_cap<BG>() + 1];
-};
 
-template <int BG, typename PP>
-__device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *smem, int col, int quad) {
-    constexpr int kCap = tail_cap<BG>();
-    constexpr int kU = BG == 1 ? 4 : BG == 2 ? 2 : 1;   // slots in flight
-    RowsSmem<BG> &sm = *reinterpret_cast<RowsSmem<BG> *>(smem);
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tt = col / p.n_bg;
-    const int bin0 = (col - tt * p.n_bg) * BG;
+// ---------------------------------------------------------------------------
+// Rows.  Bound by VALU issue: a row of a wave of four bins is about 220
+// instructions plus 30 a front and 50 a back slot, nearly all FP64 (counters at
+// 256 bins x 500 x 500: VALU busy 77 %, 250 instructions a row).  What it took
+// to get there: G changed in place (branches around its update cost a move of
+// all its registers a row), four waves per SIMD, the first front slot and the
+// next row's plan loaded a row ahead, back slots from LDS.  Rows kernel at 64
+// bins x 611 x 703 on 3001 slots: 464 us with the back slots through the
+// caches, 268 us staged, 196 us now; 256 bins x 500 x 500: 481, 340, 199 us.
+// ---------------------------------------------------------------------------
+// The segment's rows, from the last down, on one wave.  STAGED: the back slots
+// are in LDS from slot w_lo on.
+template <int BG, bool STAGED, typename PP>
+__device__ __attribute__((always_inline)) inline void slide_segment(PP &p, double *lds, int tt, int col, int bin0, int seg,
+                                                                  int w_lo) {
+    const int lane = threadIdx.x & 63;
     const int n_bins = p.n_bins;
     const int K = p.K;
     const int RL = p.range_len;
+    const int cap = p.stage;
     ConstParams<RowPlan> *rows = const_ptr(p.rows);
-    const TileSpan sp = tile_span(p, tt);
+    const int kbeg = p.kbeg, kend = const_ptr(p.tiles)[tt].kend;
     const int n = tt * 64 + lane;
     const bool n_ok = n < p.n_tau;
+    const double2 *const s_ab = reinterpret_cast<const double2 *>(lds);
+    const float4 *const s_x = reinterpret_cast<const float4 *>(s_ab + cap + 1);
+    const double *const s_c = reinterpret_cast<const double *>(s_x + BG * (cap + 1));
     const LaneTau t = lane_tau(p.tau[min(n, p.n_tau - 1)], p.t_sft);
 
-    // stage the back slots the four segments drop, and those between their
-    // last ends and the next range boundary
-    const int s0 = quad * 4;
-    int w_lo, w_hi;
-    {
-        const int m_a = s0 * p.seg_rows, m_b = min((s0 + 4) * p.seg_rows, p.n_t0) - 1;
-        int q, r;
-        tau_qr(const_ptr(p.tau)[tt * 64], p.t_sft, q, r);
-        w_lo = end_slot(rows[m_a].k0, rows[m_a].delta, q, r, K);
-        tau_qr(const_ptr(p.tau)[min(tt * 64 + 63, p.n_tau - 1)], p.t_sft, q, r);
-        w_hi = max(end_slot(rows[m_b].k0, rows[m_b].delta, q, r, K), sp.kbeg);
-        w_hi = min(sp.kbeg + (w_hi - sp.kbeg + RL - 1) / RL * RL, sp.kend);
-    }
-    const int n_w = w_hi - w_lo;
-    const bool staged = p.exact32 && n_w <= kCap;
-    if (staged) {
-        for (int i = tid; i < n_w; i += 256) {
-            const double *ab = p.abc + (size_t)(w_lo + i) * 4;
-            sm.ab[i] = *reinterpret_cast<const double2 *>(ab);
-            sm.c[i] = ab[2];
-#pragma unroll
-            for (int b = 0; b < BG; ++b)
-                sm.x[b][i] = *reinterpret_cast<const float4 *>(
-                    p.x32 + ((size_t)(w_lo + i) * n_bins + min(bin0 + b, n_bins - 1)) * 4);
-        }
-        if (tid == 0) {
-            sm.ab[kCap] = double2{0.0, 0.0};
-            sm.c[kCap] = 0.0;
-#pragma unroll
-            for (int b = 0; b < BG; ++b) sm.x[b][kCap] = float4{0.f, 0.f, 0.f, 0.f};
-        }
-        __syncthreads();
-    }
-    const int seg = s0 + wave;
-    if (seg >= p.n_seg) return;
-
-    // the lane's back slot k, zero where !on
+    // the lane's back slot k, zero where !on (byte offsets fit 32 bits: the
+    // plan's limit)
     auto lane_slot = [&](int k, bool on) {
         Sums<BG> y;
-        if (staged) {
-            const int i = on ? k - w_lo : kCap;
-            const double2 ab = sm.ab[i];
+        float4 v[BG];
+        if constexpr (STAGED) {
+            const int i = on ? k - w_lo : cap;
+            const double2 ab = s_ab[i];
             y.a[0] = ab.x;
             y.a[1] = ab.y;
-            y.a[2] = sm.c[i];
+            y.a[2] = s_c[i];
 #pragma unroll
-            for (int b = 0; b < BG; ++b) {
-                const float4 v = sm.x[b][i];
-                y.x[b][0] = v.x;
-                y.x[b][1] = v.y;
-                y.x[b][2] = v.z;
-                y.x[b][3] = v.w;
-            }
+            for (int b = 0; b < BG; ++b) v[b] = s_x[b * (cap + 1) + i];
         } else {
-            const size_t kk = on ? k : K;   // row K is zero
-            const double2 ab = *reinterpret_cast<const double2 *>(p.abc + kk * 4);
-            y.a[0] = ab.x;
-            y.a[1] = ab.y;
-            y.a[2] = p.abc[kk * 4 + 2];
+            const unsigned kk = on ? k : K;   // row K is zero
+            const char *ab = reinterpret_cast<const char *>(p.abc);
+            const double2 u = *reinterpret_cast<const double2 *>(ab + kk * 32u);
+            y.a[0] = u.x;
+            y.a[1] = u.y;
+            y.a[2] = *reinterpret_cast<const double *>(ab + 16 + kk * 32u);
+            const unsigned e = (kk * (unsigned)n_bins + (unsigned)bin0) * 4u;
+            if (!p.exact32) {
+                const char *x = reinterpret_cast<const char *>(p.x64);
 #pragma unroll
-            for (int b = 0; b < BG; ++b) {
-                const double *x = p.x64 + (kk * n_bins + min(bin0 + b, n_bins - 1)) * 4;
-                const double2 u = *reinterpret_cast<const double2 *>(x);
-                const double2 v = *reinterpret_cast<const double2 *>(x + 2);
-                y.x[b][0] = u.x;
-                y.x[b][1] = u.y;
-                y.x[b][2] = v.x;
-                y.x[b][3] = v.y;
+                for (int b = 0; b < BG; ++b) {
+                    const char *xb = x + 32 * min(b, n_bins - 1 - bin0);
+                    const double2 u0 = *reinterpret_cast<const double2 *>(xb + e * 8u);
+                    const double2 u1 = *reinterpret_cast<const double2 *>(xb + 16 + e * 8u);
+                    y.x[b][0] = u0.x;
+                    y.x[b][1] = u0.y;
+                    y.x[b][2] = u1.x;
+                    y.x[b][3] = u1.y;
+                }
+                return y;
             }
+            const char *x = reinterpret_cast<const char *>(p.x32);
+#pragma unroll
+            for (int b = 0; b < BG; ++b)
+                v[b] = *reinterpret_cast<const float4 *>(x + 16 * min(b, n_bins - 1 - bin0) + e * 4u);
+        }
+#pragma unroll
+        for (int b = 0; b < BG; ++b) {
+            y.x[b][0] = v[b].x;
+            y.x[b][1] = v[b].y;
+            y.x[b][2] = v[b].z;
+            y.x[b][3] = v[b].w;
         }
         return y;
     };
-    // channel c of anchor g (or super-range g)
+    // channel c of anchor g, or of H at the end of super-range g
     const double *anc = p.anc + (size_t)col * p.n_range * (4 * BG) * 64 + lane;
     const double *sup = p.sup + (size_t)col * p.n_sup * (4 * BG) * 64 + lane;
     const double *anc_a = p.anc_a + (size_t)tt * p.n_range * 3 * 64 + lane;
@@ -445,29 +447,20 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *sm
         for (int c = 0; c < 4 * BG; ++c) y.x[c >> 2][c & 3] = x[((size_t)g * (4 * BG) + c) * 64];
         return y;
     };
-    const int n_range = (sp.kend - sp.kbeg + RL - 1) / RL;
-    const int n_sup = (n_range + kSlideWaves - 1) / kSlideWaves;
-    const double fsup = exp(t.c * (double)(kSlideWaves * RL));   // decay of a whole super-range
+    const int n_range = (kend - kbeg + RL - 1) / RL;
+    constexpr int kU = BG == 1 ? 4 : BG == 2 ? 2 : 1;   // slots in flight
     // H at the first range end at or after slot k (kbeg <= k < kend; lanes with
-    // !on get zero), and that end
+    // !on: anything finite), and that end
     auto range_end = [&](int k, bool on, Sums<BG> &H) {
-        const int g = on ? max((k - sp.kbeg + RL - 1) / RL - 1, 0) : n_range - 1;
+        const int g = on ? max((k - kbeg + RL - 1) / RL - 1, 0) : n_range - 1;
         const int u = g / kSlideWaves;
-        H.zero();
-        // (a short super-range is the last: nothing comes after it)
-#pragma unroll 1
-        for (int v = n_sup - 1; __any(v > u); v -= kU) {
-            Sums<BG> y[kU];
-#pragma unroll
-            for (int i = 0; i < kU; ++i) y[i] = load_sums(sup, sup_a, max(v - i, 0));
-#pragma unroll
-            for (int i = 0; i < kU; ++i)
-                if (v - i > u) H.shift(fsup * fsup, fsup, y[i]);
+        H = load_sums(anc, anc_a, g);
+        const int ge = min(kbeg + (g + 1) * RL, kend);
+        const int ue = kbeg + (u + 1) * kSlideWaves * RL;
+        if (__any(ue < kend)) {   // super-ranges follow
+            const double f = ue < kend ? exp(t.c * (double)(ue - ge)) : 0.0;
+            H.add(f * f, f, load_sums(sup, sup_a, u));
         }
-        const int ge = min(sp.kbeg + (g + 1) * RL, sp.kend);
-        const int ue = min(sp.kbeg + (u + 1) * kSlideWaves * RL, sp.kend);
-        const double f = exp(t.c * (double)(ue - ge)), f2 = f * f;
-        H.shift(f2, f, load_sums(anc, anc_a, g));
         return ge;
     };
 
@@ -481,19 +474,14 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *sm
     if (__any(hi > lo)) {
         Sums<BG> H;
         // G = H(lo) - rho^(hi - lo) H(hi)
-        const bool back = hi > lo && hi < sp.kend;
+        const bool back = hi > lo && hi < kend;
         if (__any(back)) {
             int k = range_end(hi, back, H);
 #pragma unroll 1
-            for (; __any(back && k > hi); k -= kU) {
-                Sums<BG> y[kU];
-#pragma unroll
-                for (int u = 0; u < kU; ++u) y[u] = lane_slot(k - 1 - u, back && k - 1 - u >= hi);
-#pragma unroll
-                for (int u = 0; u < kU; ++u) {
-                    const bool on = back && k - 1 - u >= hi;
-                    H.shift(on ? t.rho2 : 1.0, on ? t.rho : 1.0, y[u]);
-                }
+            for (; __any(back && k > hi); --k) {
+                const bool on = back && k > hi;
+                const Sums<BG> y = lane_slot(k - 1, on);
+                H.shift(on ? t.rho2 : 1.0, on ? t.rho : 1.0, y);
             }
             const double w = back ? -exp(t.c * (double)(hi - lo)) : 0.0;
             const double w2 = -w * w;
@@ -508,6 +496,10 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *sm
     // rho^q and rho^(q + 1): weights of the first slot past a window
     const double wq = exp(t.c * (double)t.q), wq1 = wq * t.rho;
     const double ga = p.guard_a, gb = p.guard_b;
+    const size_t bin_cells = (size_t)p.n_t0 * p.n_tau;
+    float *out = p.twoF ? p.twoF + (size_t)bin0 * bin_cells + (size_t)m * p.n_tau + tt * 64 : nullptr;   // row m, bin bin0
+    const int nb = min(BG, n_bins - bin0);
+    const bool write = out && n_ok;
 
     double fm[BG], fs[BG];
     int im[BG];
@@ -517,71 +509,101 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *sm
         fs[b] = 0.0;
         im[b] = 0;
     }
+    // The loop below changes G in place, without branches around a change:
+    // where paths with a changed and an unchanged G meet, the compiler moves
+    // all its registers.
 #pragma unroll 1
     for (;;) {
-        // the cell (m, n)
-        auto cell = [&](const Sums<BG> &S) {
-            const double A = S.a[0], B = S.a[1], C = S.a[2];
-            const double D = A * B - C * C;
-            const double kD = hi > lo && D > kDegenerateRtol * A * B ? 2.0 / D : 0.0;
-            const double kA = kD * A, kB = kD * B, kC = 2.0 * kD * C;
-#pragma unroll
-            for (int b = 0; b < BG; ++b) {
-                const double *f = S.x[b];
-                const double v = kB * (f[0] * f[0] + f[1] * f[1]) + kA * (f[2] * f[2] + f[3] * f[3]) -
-                                 kC * (f[0] * f[2] + f[1] * f[3]);
-                if (p.twoF && n_ok && bin0 + b < n_bins)
-                    p.twoF[((size_t)(bin0 + b) * p.n_t0 + m) * p.n_tau + n] = (float)v;
-                // running maximum (the earlier row on a tie) and sum of exp(F - max)
-                const double F = 0.5 * v;
-                const double d = F - fm[b];
-                const bool up = d >= 0.0;
-                const double e = (double)__expf(-(float)fabs(d));
-                fs[b] = up ? fma(fs[b], e, 1.0) : fs[b] + e;
-                fm[b] = up ? F : fm[b];
-                im[b] = up ? m : im[b];
-            }
-        };
+        // the next row and its first front slot (row K of the atoms, zeros, if
+        // none enters), on their way while this row is finished
+        const int mn = max(m - 1, m_lo);
+        const int k0_n = rows[mn].k0, delta_n = rows[mn].delta;
+        const int lo_n = clamp_slot(k0_n, K);
+        int k = lo_n < lo ? lo - 1 : K;
+        Sums<BG> y = uniform_slot<BG>(p, k, bin0);
         const bool direct = hi > lo && (G.a[0] < ga || G.a[1] < gb);
         if (__any(direct)) {
-            // too weak beside what has left the window: the plain sum
-            Sums<BG> S;
-            S.zero();
-            double w = 1.0;
+            // too weak beside what has left the window: the plain sums, a bin
+            // at a time
+#pragma unroll
+            for (int b = 0; b < BG; ++b) {
+                Sums<1> S;
+                S.zero();
+                double w = 1.0;
 #pragma unroll 1
-            for (int k = lo; __any(direct && k < hi); ++k) {
-                const double ww = k < hi ? w : 0.0;
-                S.add(ww * ww, ww, uniform_slot<BG>(p, k, bin0));
-                w *= t.rho;
+                for (int j = lo; __any(direct && j < hi); ++j) {
+                    const double ww = j < hi ? w : 0.0;
+                    S.add(ww * ww, ww, uniform_slot<1>(p, j, bin0 + b));
+                    w *= t.rho;
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) G.x[b][c] = direct ? S.x[0][c] : G.x[b][c];
+                if (b == BG - 1) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) G.a[c] = direct ? S.a[c] : G.a[c];
+                }
             }
-            if (direct) cell(S);
         }
-        if (!direct) cell(G);
+        // the cell (m, n): 1 / D by two Newton steps (the plan keeps D's range
+        // normal), then each bin's F = 2F / 2
+        const double A = G.a[0], B = G.a[1], C = G.a[2];
+        const double AB = A * B;
+        const double D = fma(-C, C, AB);
+        double r = __builtin_amdgcn_rcp(D);
+        r = fma(r, fma(-D, r, 1.0), r);
+        r = fma(r, fma(-D, r, 1.0), r);
+        r = hi > lo && D > kDegenerateRtol * AB ? r : 0.0;
+        const double qa = r * A, qb = r * B, qc = -2.0 * r * C;
+        float F2[BG];
+#pragma unroll
+        for (int b = 0; b < BG; ++b) {
+            const double *f = G.x[b];
+            const double F = fma(qb, fma(f[0], f[0], f[1] * f[1]),
+                                 fma(qa, fma(f[2], f[2], f[3] * f[3]), qc * fma(f[0], f[2], f[1] * f[3])));
+            F2[b] = 2.f * (float)F;
+            // running maximum (the earlier row on a tie) and sum of
+            // exp(F - max), one FP32 exponential
+            const double d = F - fm[b];
+            const bool up = d >= 0.0;
+            const float e = __expf(-fabsf((float)d));
+            fs[b] = fma(fs[b], (double)(up ? e : 1.f), (double)(up ? 1.f : e));
+            fm[b] = up ? F : fm[b];
+            im[b] = up ? m : im[b];
+        }
+        if (write) {
+#pragma unroll
+            for (int b = 0; b < BG; ++b)
+                if (b < nb) out[b * bin_cells + lane] = F2[b];
+        }
         if (m == m_lo) break;
         --m;
-        k0 = rows[m].k0;
-        delta = rows[m].delta;
-        const int lo_n = clamp_slot(k0, K);
-        const int hi_n = max(end_slot(k0, delta, t.q, t.r, K), lo_n);
+        if (out) out -= p.n_tau;
+        k0 = k0_n;
+        delta = delta_n;
         // slots that enter at the front
-        if (lo - lo_n == 1)
-            G.shift(t.rho2, t.rho, uniform_slot<BG>(p, lo_n, bin0));
-        else
-            run_down<BG, kU>(p, t, bin0, lo, lo_n, G);
+        const double u = lo_n < lo ? t.rho : 1.0, u2 = lo_n < lo ? t.rho2 : 1.0;
         lo = lo_n;
-        // slots that leave at the back: weight rho^(k - lo)
-        if (__any(hi > hi_n)) {
-            double w = hi_n - lo_n == t.q ? wq : wq1;
-            if (__any(hi > hi_n && (unsigned)(hi_n - lo_n - t.q) > 1u)) w = exp(t.c * (double)(hi_n - lo_n));
-            w = -w;
 #pragma unroll 1
-            for (int k = hi_n; __any(k < hi); ++k) {
-                const Sums<BG> y = lane_slot(k, k < hi);
-                G.add(-w * w, w, y);
-                w *= t.rho;
-            }
-            hi = hi_n;
+        for (;;) {
+            G.shift_uniform(u2, u, y);
+            if (--k < lo || k >= K - 1) break;
+            y = uniform_slot<BG>(p, k, bin0);
         }
+        // slots that leave at the back: weight rho^(k - lo)
+        const int hi_n = max(end_slot(k0, delta, t.q, t.r, K), lo);
+        double w = hi_n - lo == t.q ? wq : wq1;
+        // (rows that start before the data: a shorter window)
+        if (k0 < 0) w = exp(t.c * (double)(hi_n - lo));
+        w = -w;
+        int j = hi_n;
+#pragma unroll 1
+        do {
+            const Sums<BG> v = lane_slot(j, j < hi);
+            G.add(-w * w, w, v);
+            w *= t.rho;
+            ++j;
+        } while (__any(j < hi));
+        hi = hi_n;
     }
 
     // the wave's lanes: maximum with its first cell, sum rescaled to it
@@ -601,13 +623,67 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, char *sm
         double sv = n_ok ? fs[b] * (double)__expf((float)(fm[b] - mx)) : 0.0;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) sv += __shfl_xor(sv, o, 64);
-        if (lane == 0 && bin0 + b < n_bins) {
+        if (lane == 0 && b < nb) {
             Partial &o = p.part[(size_t)(bin0 + b) * p.n_tiles + (size_t)tt * p.n_seg + seg];
             o.fmax = mx;
             o.s = sv;
             o.idx = ix;
         }
     }
+}
+
+// Workgroup = up to kRowsWaves segments of one column.  The back slots that
+// its segments drop, and those between their last ends and the next range
+// boundary, are staged in LDS once (sized by the plan): [a^2, b^2], ab, then
+// each bin's data; the last entry is zero (lanes without a slot to drop read
+// it).  Maps whose tiles' taus span more slots than fit (or whose data are not
+// single-precision numbers) read them through the caches, a line per lane and
+// slot.
+template <int BG, bool STAGED, typename PP>
+__device__ __attribute__((always_inline)) inline void slide_rows(PP &p, double *lds, int col, int group) {
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tt = col / p.n_bg;
+    const int bin0 = (col - tt * p.n_bg) * BG;
+    const int n_bins = p.n_bins;
+    const int K = p.K;
+    const int RL = p.range_len;
+    const int W = p.waves;
+    const int cap = p.stage;
+    ConstParams<RowPlan> *rows = const_ptr(p.rows);
+    auto &tile = const_ptr(p.tiles)[tt];
+    const int kbeg = p.kbeg, kend = tile.kend;
+    double2 *const s_ab = reinterpret_cast<double2 *>(lds);
+    float4 *const s_x = reinterpret_cast<float4 *>(s_ab + cap + 1);
+    double *const s_c = reinterpret_cast<double *>(s_x + BG * (cap + 1));
+
+    const int s0 = group * W;
+    int w_lo = 0;
+    if constexpr (STAGED) {
+        const int m_a = s0 * p.seg_rows, m_b = min((s0 + W) * p.seg_rows, p.n_t0) - 1;
+        w_lo = end_slot(rows[m_a].k0, rows[m_a].delta, tile.q0, tile.r0, K);
+        int w_hi = max(end_slot(rows[m_b].k0, rows[m_b].delta, tile.q1, tile.r1, K), kbeg);
+        w_hi = min(kbeg + (w_hi - kbeg + RL - 1) / RL * RL, kend);
+        const int n_w = min(w_hi - w_lo, cap);   // (the plan's stage holds them all)
+        for (int i = tid; i < n_w; i += 64 * W) {
+            const double *ab = p.abc + (size_t)(w_lo + i) * 4;
+            s_ab[i] = *reinterpret_cast<const double2 *>(ab);
+            s_c[i] = ab[2];
+#pragma unroll
+            for (int b = 0; b < BG; ++b)
+                s_x[b * (cap + 1) + i] = *reinterpret_cast<const float4 *>(
+                    p.x32 + ((size_t)(w_lo + i) * n_bins + min(bin0 + b, n_bins - 1)) * 4);
+        }
+        if (tid == 0) {
+            s_ab[cap] = double2{0.0, 0.0};
+            s_c[cap] = 0.0;
+#pragma unroll
+            for (int b = 0; b < BG; ++b) s_x[b * (cap + 1) + cap] = float4{0.f, 0.f, 0.f, 0.f};
+        }
+        __syncthreads();
+    }
+    const int seg = s0 + wave;
+    if (seg < p.n_seg) slide_segment<BG, STAGED>(p, lds, tt, col, bin0, seg, w_lo);
 }
 
 // ---------------------------------------------------------------------------
@@ -675,10 +751,15 @@ __global__ __launch_bounds__(64 * kSlideWaves) void slide_anchor_kernel(SlidePar
     slide_anchor<BG>(p, tot, tt, blockIdx.x - tt * (p.n_bg + 1), blockIdx.y);
 }
 
-template <int BG>
-__global__ __launch_bounds__(256, 3) void slide_rows_kernel(SlideParams p) {
-    __shared__ __attribute__((aligned(16))) char smem[sizeof(RowsSmem<BG>)];
-    slide_rows<BG>(p, smem, blockIdx.x, blockIdx.y);
+template <int BG, bool STAGED>
+__global__ __launch_bounds__(64 * kRowsWaves) void slide_rows_kernel(SlideParams p) {
+    extern __shared__ __attribute__((aligned(16))) double lds[];
+    slide_rows<BG, STAGED>(p, lds, blockIdx.x, blockIdx.y);
+}
+
+__global__ __launch_bounds__(256) void slide_supers_kernel(SlideParams p) {
+    const int tt = blockIdx.x / (p.n_bg + 1);
+    slide_supers(p, tt, blockIdx.x - tt * (p.n_bg + 1));
 }
 
 // Many maps, one workgroup per entry; the bins per group are the map's.
@@ -697,15 +778,28 @@ __global__ __launch_bounds__(64 * kSlideWaves) void slide_anchor_batch_kernel(Sl
     default: slide_anchor<4>(p, tot, e[1], e[2], e[3]); break;
     }
 }
-__global__ __launch_bounds__(256, 3) void slide_rows_batch_kernel(SlideBatchParams b) {
-    __shared__ __attribute__((aligned(16))) char smem[sizeof(RowsSmem<4>)];
+// (an anchor entry's first super-range stands for its column)
+__global__ __launch_bounds__(256) void slide_supers_batch_kernel(SlideBatchParams b) {
+    ConstParams<int32_t> *e = const_ptr(b.anchors) + 4 * (size_t)blockIdx.x;
+    if (e[3] == 0) slide_supers(const_params(b.jobs + e[0]), e[1], e[2]);
+}
+__global__ __launch_bounds__(64 * kRowsWaves) void slide_rows_batch_kernel(SlideBatchParams b) {
+    extern __shared__ __attribute__((aligned(16))) double lds[];
     ConstParams<int32_t> *e = const_ptr(b.rows) + 4 * (size_t)blockIdx.x;
     auto &p = const_params(b.jobs + e[0]);
-    switch (p.bg) {
-    case 1: slide_rows<1>(p, smem, e[1], e[2]); break;
-    case 2: slide_rows<2>(p, smem, e[1], e[2]); break;
-    case 3: slide_rows<3>(p, smem, e[1], e[2]); break;
-    default: slide_rows<4>(p, smem, e[1], e[2]); break;
+    if ((int)threadIdx.x >= 64 * p.waves) return;
+    if (p.stage > 0) {
+        switch (p.bg) {
+        case 1: slide_rows<1, true>(p, lds, e[1], e[2]); break;
+        case 2: slide_rows<2, true>(p, lds, e[1], e[2]); break;
+        case 3: slide_rows<3, true>(p, lds, e[1], e[2]); break;
+        default: slide_rows<4, true>(p, lds, e[1], e[2]); break;
+        }
+    } else {
+        switch (p.bg) {
+        case 1: slide_rows<1, false>(p, lds, e[1], e[2]); break;
+        default: slide_rows<2, false>(p, lds, e[1], e[2]); break;   // (the plan's limit)
+        }
     }
 }
 
@@ -714,7 +808,8 @@ __global__ __launch_bounds__(256, 3) void slide_rows_batch_kernel(SlideBatchPara
 hipError_t launch_slide_batch(const SlideBatchParams &p, hipStream_t s) {
     if (p.n_rows <= 0) return hipSuccess;
     hipLaunchKernelGGL(slide_anchor_batch_kernel, dim3((unsigned)p.n_anchors), dim3(64 * kSlideWaves), 0, s, p);
-    hipLaunchKernelGGL(slide_rows_batch_kernel, dim3((unsigned)p.n_rows), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(slide_supers_batch_kernel, dim3((unsigned)p.n_anchors), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(slide_rows_batch_kernel, dim3((unsigned)p.n_rows), dim3(64 * kRowsWaves), p.lds_bytes, s, p);
     return hipGetLastError();
 }
 
@@ -736,17 +831,22 @@ hipError_t launch_slide_anchors(const SlideParams &p, hipStream_t s) {
     case 4: hipLaunchKernelGGL(slide_anchor_kernel<4>, g, b, 0, s, p); break;
     default: return hipErrorInvalidValue;
     }
+    if (p.n_sup > 1) hipLaunchKernelGGL(slide_supers_kernel, dim3(g.x), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
 hipError_t launch_slide_rows(const SlideParams &p, hipStream_t s) {
-    const dim3 g((unsigned)(p.n_tt * p.n_bg), (unsigned)((p.n_seg + 3) / 4)), b(256);
+    const unsigned lds = slide_stage_bytes(p.bg, p.stage);
+    if (p.waves < 1 || p.waves > kRowsWaves || p.stage < 0 || lds > kSlideStageBytes) return hipErrorInvalidValue;
+    const dim3 g((unsigned)(p.n_tt * p.n_bg), (unsigned)((p.n_seg + p.waves - 1) / p.waves)), b(64u * p.waves);
     if (g.y > 65535u) return hipErrorInvalidValue;
-    switch (p.bg) {
-    case 1: hipLaunchKernelGGL(slide_rows_kernel<1>, g, b, 0, s, p); break;
-    case 2: hipLaunchKernelGGL(slide_rows_kernel<2>, g, b, 0, s, p); break;
-    case 3: hipLaunchKernelGGL(slide_rows_kernel<3>, g, b, 0, s, p); break;
-    case 4: hipLaunchKernelGGL(slide_rows_kernel<4>, g, b, 0, s, p); break;
+    switch (2 * p.bg + (p.stage > 0)) {
+    case 2: hipLaunchKernelGGL((slide_rows_kernel<1, false>), g, b, 0, s, p); break;
+    case 3: hipLaunchKernelGGL((slide_rows_kernel<1, true>), g, b, lds, s, p); break;
+    case 4: hipLaunchKernelGGL((slide_rows_kernel<2, false>), g, b, 0, s, p); break;
+    case 5: hipLaunchKernelGGL((slide_rows_kernel<2, true>), g, b, lds, s, p); break;
+    case 7: hipLaunchKernelGGL((slide_rows_kernel<3, true>), g, b, lds, s, p); break;
+    case 9: hipLaunchKernelGGL((slide_rows_kernel<4, true>), g, b, lds, s, p); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

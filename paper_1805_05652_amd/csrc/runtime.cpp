@@ -274,8 +274,11 @@ constexpr int32_t kRunsAuto = -1;
 // FP32 maps with at least this many bins (and rows close enough for the band
 // stage) take the split form: A/B/C pass, then F_a/F_b-only tiles.
 constexpr int32_t kSplitMinBins = 8;
-// Waves a sliding map aims at (1024 SIMDs, three waves each).
-constexpr int64_t kSlideTarget = 3072;
+// Compute units; waves that a sliding map's rows take at most (some rounds of
+// the chip); column ranges that its anchors take at least.
+constexpr int64_t kCus = 256;
+constexpr int64_t kSlideMost = 16384;
+constexpr int64_t kSlideRanges = 1536;
 
 // ---------------------------------------------------------------------------
 // One map computation: plan (host, integer), workspace, launches, results.
@@ -308,6 +311,9 @@ struct Job {
     int no_slide = 0;          // 1: smallest workspace, 2: the direct forms (the arena is short)
     bool forced = false;       // tile shape forced by the caller: the direct forms
     int32_t bg = 1, n_bg = 1, n_tt = 1, n_seg = 1, seg_rows = 1, range_len = 1, n_range = 1, n_sup = 1;
+    int32_t kbeg = 0, waves = 1, stage = 0;
+    int64_t tau_spread = 0;      // slots that 64 taus' window ends span at most
+    std::vector<tfs::SlideTile> tiles;
     bool use_mfma = false;     // BF16X3 on matrix cores for long bands
     // matrix-core form: true = weights computed per row (exponential
     // windows, any t0 grid); false = shifted weight tables (shape windows
@@ -329,12 +335,22 @@ struct Job {
     size_t off_rows = 0, off_tau = 0, off_lcol = 0, off_lblk = 0, off_boff = 0, off_order = 0,
            tables_bytes = 0;
     size_t off_g32 = 0, off_gsq = 0, off_g64 = 0, off_pabc = 0, off_px = 0, off_part = 0,
-           off_res = 0, off_abc = 0, off_lg = 0, off_gshoff = 0, off_gsh = 0, off_shape = 0, off_anc = 0, off_sup = 0, off_anca = 0, off_supa = 0, off_ptot = 0;
+           off_res = 0, off_abc = 0, off_lg = 0, off_gshoff = 0, off_gsh = 0, off_shape = 0, off_tiles = 0, off_anc = 0, off_sup = 0, off_anca = 0, off_supa = 0, off_ptot = 0;
 
     // timing
     std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>> timed;
     hipEvent_t done = nullptr;
 };
+
+// Slots that a workgroup of rows_wg rows stages at most: its taus' span, its
+// rows' and one anchor range.
+int64_t slide_stage(const Job &j, int64_t rows_wg, int64_t range_len) {
+    const int64_t n_t0 = (int64_t)j.win.t0.size();
+    int64_t span = 0;
+    for (int64_t m = 0; m < n_t0; m += rows_wg)
+        span = std::max<int64_t>(span, (int64_t)j.rows[std::min(m + rows_wg, n_t0) - 1].k0 - j.rows[m].k0);
+    return std::min<int64_t>(j.tau_spread + span + range_len + 2, (int64_t)j.at->K + 2);
+}
 
 // Sliding sums of an exponential map (kernels_slide.hip), from the map alone
 // (its results may not depend on what it is batched with).  They cost a
@@ -348,22 +364,92 @@ void plan_slide(Job &j) {
     const int n_t0 = (int)j.win.t0.size(), n_tau = (int)j.win.tau.size();
     j.slide = true;
     j.n_tt = (n_tau + 63) / 64;
-    j.n_bg = (at.n_bins + 3) / 4;
-    j.bg = (at.n_bins + j.n_bg - 1) / j.n_bg;
-    const int64_t cols = (int64_t)j.n_tt * j.n_bg;
-    // segments for about kSlideTarget waves.  A segment starts from anchors,
-    // about 32 slots away: of rows that lie closer it takes at least 4
+    // tau tiles, and the slots that 64 taus' window ends span
+    auto qr = [&](int64_t tau, int32_t &q, int32_t &r) {
+        const int64_t qq = 3 * tau / at.t_sft;
+        q = (int32_t)std::min<int64_t>(qq, 1342177280);
+        r = qq > q ? 0 : (int32_t)(3 * tau - qq * at.t_sft);
+    };
+    j.tau_spread = 0;
+    j.tiles.assign(j.n_tt, tfs::SlideTile{});
+    for (int tt = 0; tt < j.n_tt; ++tt) {
+        tfs::SlideTile &t = j.tiles[tt];
+        qr(j.win.tau[tt * 64], t.q0, t.r0);
+        qr(j.win.tau[std::min(tt * 64 + 63, n_tau - 1)], t.q1, t.r1);
+        if (t.q0 < at.K) j.tau_spread = std::max<int64_t>(j.tau_spread, std::min<int64_t>(t.q1, at.K) - t.q0 + 2);
+    }
+    // A segment starts from anchors, about 32 slots away: of rows that lie
+    // closer it takes at least 4.
     const int64_t apart = n_t0 > 1 ? ((int64_t)j.rows[n_t0 - 1].k0 - j.rows[0].k0) / (n_t0 - 1) : 1;
     const int64_t least = apart >= 8 ? 1 : (apart >= 4 ? 2 : 4);
-    int64_t n_seg = j.no_slide ? 1 : std::min<int64_t>((kSlideTarget + cols - 1) / cols, (n_t0 + least - 1) / least);
-    n_seg = std::max<int64_t>(n_seg, 1);
+    int64_t n_seg = 1, w = 1;
+    int32_t rl = 64;
+    // Bins per group: four share a row's A, B, C and D; fewer, of equal size,
+    // when that wastes none.
+    const int bg_full = (at.n_bins + (at.n_bins + 3) / 4 - 1) / ((at.n_bins + 3) / 4);
+    auto columns = [&](int bg) { return (int64_t)j.n_tt * ((at.n_bins + bg - 1) / bg); };
+    // anchor ranges: long where the columns alone fill the chip
+    while (rl > 16 && columns(bg_full) * (at.K / rl) < kSlideRanges) rl /= 2;
+    // Bins per group, segments and segments per workgroup by an estimate of
+    // the rows kernel's time in VALU instructions: a cell's, a front and a back
+    // slot's (counted in its loop), a segment's start (latencies, half a range
+    // at the front and one at the back).  A compute unit's four SIMDs share
+    // them; a wave alone issues 1 / 2.8 of what a SIMD can (measured: 2.0 and
+    // 4.0 choose slower splits).  The stage
+    // limits the workgroups per compute unit; where not even one bin's fits
+    // (or the data are no single-precision numbers), the back slots come
+    // through the caches, for one or two bins.
+    j.stage = 0;
+    j.bg = at.exact32 && !j.no_slide ? bg_full : std::min(bg_full, 2);
+    if (j.no_slide) {
+        rl = (int32_t)std::max<int64_t>(128, ((int64_t)at.K + 16 * tfs::kSlideWaves - 1) / (16 * tfs::kSlideWaves) * 16);
+    } else {
+        double best = 0.0;
+        for (int bg = j.bg; bg >= 1; bg = bg > 2 ? 2 : bg - 1) {
+            const int64_t cols = columns(bg);
+            const double front = 13.0 + 4 * bg, back = 20.0 + 8 * bg;
+            const double start = 1000.0 + rl * (front / 2 + back);
+            const double row = 45.0 + 27 * bg + (double)apart * (front + back);
+            const int64_t fit = at.exact32 ? tfs::kSlideStageBytes / tfs::slide_stage_bytes(bg, 0) - 1 : 0;
+            for (int waves = 4; waves <= tfs::kRowsWaves; waves += 4) {
+                int64_t last = 0;
+                for (int64_t groups = 1;; groups += (groups + 3) / 4) {
+                    const int64_t rows = (n_t0 + groups * waves - 1) / (groups * waves);   // of a segment
+                    if (groups > 1 && (rows < least || rows == last || cols * groups * waves > kSlideMost)) break;
+                    last = rows;
+                    const int64_t seg = (n_t0 + std::max(rows, least) - 1) / std::max(rows, least);
+                    const int64_t wv = std::min<int64_t>(waves, seg);
+                    const int64_t stage = fit ? slide_stage(j, wv * std::max(rows, least), rl) : 0;
+                    if (fit && stage > fit) continue;
+                    const int64_t lds = fit ? tfs::slide_stage_bytes(bg, (int)stage) : 1;
+                    const int64_t both = std::min<int64_t>(tfs::kRowsWaves / wv, tfs::kSlideStageBytes / lds);
+                    const int64_t per_cu = (cols * ((seg + wv - 1) / wv) + kCus - 1) / kCus;
+                    const double est = std::max((double)(per_cu * wv) / 4, 2.8 * (double)((per_cu + both - 1) / both)) *
+                                       (start + row * (double)std::max(rows, least));
+                    if (best > 0.0 && est >= best) continue;
+                    best = est;
+                    j.bg = bg;
+                    j.stage = (int32_t)stage;
+                    n_seg = seg;
+                    w = wv;
+                }
+            }
+        }
+        if (best == 0.0) {
+            j.bg = std::min(bg_full, 2);
+            n_seg = std::max<int64_t>(1, std::min(kSlideMost / 4 / columns(j.bg), (n_t0 + least - 1) / least));
+            w = std::min<int64_t>(n_seg, tfs::kRowsWaves / 2);
+        }
+    }
+    j.n_bg = (at.n_bins + j.bg - 1) / j.bg;
     j.seg_rows = (int32_t)((n_t0 + n_seg - 1) / n_seg);
     j.n_seg = (n_t0 + j.seg_rows - 1) / j.seg_rows;
-    // ranges of the anchors: long ones where the columns alone fill the chip
-    int32_t rl = 128;
-    while (rl > 16 && cols * (at.K / rl) < kSlideTarget) rl /= 2;
-    if (j.no_slide) rl = std::max<int64_t>(128, ((int64_t)at.K + 16 * tfs::kSlideWaves - 1) / (16 * tfs::kSlideWaves) * 16);
+    j.waves = (int32_t)std::min<int64_t>(w, j.n_seg);
     j.range_len = rl;
+    j.kbeg = std::min(std::max(j.rows[std::min<int32_t>(j.seg_rows, n_t0) - 1].k0, 0), at.K);
+    const tfs::RowPlan &last = j.rows[n_t0 - 1];
+    for (tfs::SlideTile &t : j.tiles)
+        t.kend = std::max(std::min(std::max(last.k0 + t.q1 + (t.r1 > last.delta ? 1 : 0), 0), at.K), j.kbeg);
     j.n_sup = std::max<int32_t>(1, (at.K + rl * tfs::kSlideWaves - 1) / (rl * tfs::kSlideWaves));
     j.n_range = j.n_sup * tfs::kSlideWaves;
 }
@@ -569,6 +655,7 @@ void plan_job(Job &j) {
         }
         if (is_shape) j.off_shape = take(sizeof(double) * j.win.shape.size());
     }
+    if (j.slide) j.off_tiles = take(sizeof(tfs::SlideTile) * j.n_tt);
     j.tables_bytes = o;
     if (j.slide) {
         const size_t ch = (size_t)j.n_tt * j.n_bg * (4 * j.bg) * 64 * sizeof(double);
@@ -749,6 +836,7 @@ void fill_tables(const Job &j, char *h) {
     std::memcpy(h + j.off_rows, j.rows.data(), sizeof(tfs::RowPlan) * n_t0);
     std::memcpy(h + j.off_tau, j.win.tau.data(), sizeof(int64_t) * n_tau);
     std::memcpy(h + j.off_lcol, j.lcol.data(), sizeof(int32_t) * n_tau);
+    if (j.slide) std::memcpy(h + j.off_tiles, j.tiles.data(), sizeof(tfs::SlideTile) * j.n_tt);
     if (banded(j.win.type) && !j.slide) {
         if (j.win.type == TFSTAT_WIN_SHAPE)
             std::memcpy(h + j.off_shape, j.win.shape.data(), sizeof(double) * j.win.shape.size());
@@ -904,6 +992,10 @@ tfs::SlideParams slide_params(Job &j) {
     q.n_sup = j.n_sup;
     q.n_tiles = j.n_tiles;
     q.exact32 = at.exact32;
+    q.kbeg = j.kbeg;
+    q.waves = j.waves;
+    q.stage = j.stage;
+    q.tiles = ws_ptr<tfs::SlideTile>(j, j.off_tiles);
     q.guard_a = at.amax * 0x1p-13;
     q.guard_b = at.bmax * 0x1p-13;
     q.rows = ws_ptr<tfs::RowPlan>(j, j.off_rows);
@@ -1034,11 +1126,13 @@ void enqueue_job(tfstat_ctx *ctx, Job &j, hipStream_t s) {
 
     if (j.slide) {
         const tfs::SlideParams sp = slide_params(j);
-        // (groups of two bins or more: range sums on the matrix cores)
-        if (j.bg > 1) record_kernel(ctx, j, TFSTAT_K_MFMA, s, true);
+        // (the anchors' range sums are on the matrix cores; a one-bin map's
+        // two launches are one entry)
+        const bool apart = j.at->n_bins > 1;
+        if (apart) record_kernel(ctx, j, TFSTAT_K_MFMA, s, true);
         else record_kernel(ctx, j, TFSTAT_K_RECUR, s, true);
         hip_check(tfs::launch_slide_anchors(sp, s), "sliding anchors kernel");
-        if (j.bg > 1) {
+        if (apart) {
             record_kernel(ctx, j, TFSTAT_K_MFMA, s, false);
             record_kernel(ctx, j, TFSTAT_K_RECUR, s, true);
         }
@@ -1325,12 +1419,22 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     b->res_off.assign(n, 0);
     b->n_results = 0;
     b->scan_split = false;
+    b->slp.lds_bytes = 0;
     for (int32_t i = 0; i < n; ++i) {
         Job &j = *b->jobs[i];
         if (j.slide) {
             sidx[i] = n_slide++;
+            // (one workgroup size for all maps: as many of its waves as fill
+            // evenly and as the stage holds)
+            int64_t wv = tfs::kRowsWaves;
+            do {
+                const int64_t wgs = (j.n_seg + wv - 1) / wv;
+                j.waves = (int32_t)((j.n_seg + wgs - 1) / wgs);
+                if (j.stage > 0) j.stage = (int32_t)slide_stage(j, (int64_t)j.waves * j.seg_rows, j.range_len);
+            } while (tfs::slide_stage_bytes(j.bg, j.stage) > tfs::kSlideStageBytes && --wv >= 1);
             n_anchor += (size_t)j.n_tt * (j.n_bg + 1) * j.n_sup;
-            n_srows += (size_t)j.n_tt * j.n_bg * ((j.n_seg + 3) / 4);
+            n_srows += (size_t)j.n_tt * j.n_bg * ((j.n_seg + j.waves - 1) / j.waves);
+            b->slp.lds_bytes = std::max(b->slp.lds_bytes, tfs::slide_stage_bytes(j.bg, j.stage));
         } else if (banded(j.win.type)) {
             if (j.use_mfma && !j.mfma_rows)
                 raise(TFSTAT_E_INVAL, "a batch runs no matrix-core shape windows (use tfstat_fmap)");
@@ -1603,7 +1707,7 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
                     aent[4 * ae_ + 2] = c % (j.n_bg + 1);
                     aent[4 * ae_ + 3] = u;
                 }
-            for (int q = 0; q < (j.n_seg + 3) / 4; ++q)
+            for (int q = 0; q < (j.n_seg + j.waves - 1) / j.waves; ++q)
                 for (int c = 0; c < cols; ++c, ++sr_) {
                     sent[4 * sr_] = sidx[i];
                     sent[4 * sr_ + 1] = c;
@@ -2146,10 +2250,13 @@ int tfstat_atoms_upload(tfstat_ctx *ctx, const tfstat_atoms_desc *d, tfstat_atom
             hip_check(hipMemcpyAsync(hinfo, info, sizeof(*info), hipMemcpyDeviceToHost, ctx->stream), "range");
             hip_check(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
             collect_timing(ctx, dummy);
-            set->slide_ok = hinfo->wide == 0;
+            // (products of two antenna sums and their inverses stay normal)
+            set->slide_ok = hinfo->wide == 0 && (int64_t)rows * nb * 32 < ((int64_t)1 << 31);
             set->exact32 = hinfo->inexact32 == 0;
             std::memcpy(&set->amax, &hinfo->amax, sizeof(double));
             std::memcpy(&set->bmax, &hinfo->bmax, sizeof(double));
+            for (double v : {set->amax, set->bmax})
+                if (v != 0.0 && !(v > 0x1p-200 && v < 0x1p+200)) set->slide_ok = false;
         } catch (...) {
             ctx->pinned.put(pin, pin_bytes);
             std::lock_guard<std::mutex> g(ctx->mu);

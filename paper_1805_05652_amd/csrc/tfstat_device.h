@@ -217,7 +217,19 @@ struct ShiftTableParams {
 // column is a tile of 64 taus x one group of bg bins; its rows run in n_seg
 // segments of seg_rows rows.  Anchors: H at the end of every range of
 // range_len slots (kSlideWaves ranges make a super-range).
-constexpr int kSlideWaves = 16;
+constexpr int kSlideWaves = 8;
+// The rows kernel: up to kRowsWaves segments per workgroup (four waves per
+// SIMD; the FP32 maps' 25 spilled registers cost less than a fourth wave
+// gives: 193 against 256 us at 256 bins), the back slots they drop staged in
+// LDS.
+constexpr int kRowsWaves = 16;
+constexpr unsigned kSlideStageBytes = 160 * 1024;
+inline unsigned slide_stage_bytes(int bg, int stage) { return (24u + 16u * bg) * (unsigned)(stage + 1); }
+// A tau tile: the end of the slots its windows reach, and 3 tau of its first
+// and last tau in slots (q) and seconds (r).
+struct SlideTile {
+    int32_t kend, q0, r0, q1, r1, pad;
+};
 struct SlideParams {
     int32_t K, n_bins;
     int32_t n_t0, n_tau;
@@ -229,9 +241,13 @@ struct SlideParams {
                                          // any tile, whole super-ranges
     int32_t n_tiles;          // partial slots per bin (n_tt * n_seg)
     int32_t exact32;          // x32 holds x64 exactly
+    int32_t kbeg;             // first slot of the anchors' ranges
+    int32_t waves, stage;     // rows kernel: segments per workgroup, slots its stage holds
+    int32_t pad;
     double guard_a, guard_b;  // cells with A or B below these are summed directly
     const RowPlan *rows;
     const int64_t *tau;
+    const SlideTile *tiles;   // [n_tt]
     const double *abc;        // [K+1][4]
     const double *x64;        // [K+1][n_bins][4]
     const float *x32;         // [K+1][n_bins][4]
@@ -243,12 +259,14 @@ struct SlideParams {
 };
 
 // Sliding maps of a batch: anchor entry = {map, tau tile, bin group (n_bg: the
-// antenna), super-range}, rows entry = {map, column, quad of segments, 0}.
+// antenna), super-range}, rows entry = {map, column, group of segments, 0}.
 struct SlideBatchParams {
     const SlideParams *jobs;
     const int32_t *anchors;   // [n_anchors][4]
     const int32_t *rows;      // [n_rows][4]
     int32_t n_anchors, n_rows;
+    uint32_t lds_bytes;       // the largest stage
+    int32_t pad;
 };
 
 // What the sliding sums ask of the atoms, found once at upload.

@@ -81,6 +81,21 @@ def test_slide_against_oracle_and_direct(ctx, n_bins, grid):
     check_map(direct, ref, TOL["fp32"])
 
 
+@pytest.mark.parametrize("n_bins,last_tau", [(1, 1000), (1, 1400), (3, 900), (3, 1000), (4, 500), (5, 700), (6, 1500)])
+def test_slide_window_ends_past_the_stage(ctx, n_bins, last_tau):
+    """Window ends of one tau tile spread over 3 * last_tau slots: at the edge
+    of what a workgroup's LDS holds at 4, 3, 2 and 1 bins (1860, 2274, 2924 and
+    4095 slots), and past it, where the ends come through the caches."""
+    print("case: spread %d bins, tau to %d" % (n_bins, last_tau), flush=True)
+    atoms = tfsynth.make_atoms(9350 + n_bins, 4600, 0.1, n_bins=n_bins)
+    win = tfsynth.list_window("exp", 3 + 5 * T * np.arange(30), np.unique(np.linspace(2, last_tau, 50).astype(np.int64) * T))
+    ref = oracle.fmap_atoms(atoms, win)
+    res, got, n = _maps(ctx, atoms, win, "fp32")
+    assert n == 1, "not by sliding windows"
+    check_map(got, ref, TOL["fp64"])
+    check_results(res, ref, win, TOL["fp64"])
+
+
 @pytest.mark.parametrize("slots", [1, 2, 31, 32, 33, 255, 256, 257, 513])
 @pytest.mark.parametrize("kind", ["exp", "rect"])
 def test_slot_count_edges(ctx, kind, slots):
