@@ -1049,9 +1049,9 @@ __global__ __launch_bounds__(256) void weights_batch_kernel(WeightBatchParams p)
 // double-double pairs so that a window's difference keeps full FP64 accuracy
 // relative to the window sum itself, however long the prefix.  Channels come
 // in groups of four (a^2, b^2, ab, 0; or the four data components of one
-// bin); group g's prefixes are laid out [g][K+1][8]: the four hi terms,
-// then the four lo terms, hi + lo = sum_{j<k} in[j][c], so that one window
-// end of one group is one contiguous 64-byte read.
+// bin); group g's prefixes are laid out [g][K+1][4][2], (hi, lo) with hi + lo
+// = sum_{j<k} in[j][c], so that one window end of one group is one contiguous
+// 64-byte read.
 // Lane = channel, wave = kScanSlots consecutive slots held in registers,
 // workgroup = kScanBlock slots of 64 channels.  The chain of dependent
 // double-double sums bounds this, not its bytes, so the slots are spread over
@@ -1116,11 +1116,8 @@ __device__ __attribute__((always_inline)) inline void scan_blocks(const ScanJob 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int c = j.chunk * 64 + lane;
-    double *o = j.out + (size_t)(c >> 2) * ((size_t)j.K + 1) * 8 + (c & 3);   // this channel's hi terms
-    if (blk == 0 && wave == 0 && c < j.C) {
-        o[0] = 0.0;
-        o[4] = 0.0;
-    }
+    double *o = j.out + (size_t)(c >> 2) * ((size_t)j.K + 1) * 8 + 2 * (c & 3);   // this channel's pairs
+    if (blk == 0 && wave == 0 && c < j.C) *reinterpret_cast<double2 *>(o) = double2{0.0, 0.0};
     DD base{0.0, 0.0};   // the blocks before this one
     for (int b = 0; b < blk; ++b) {
         const double2 t = j.tot[(size_t)b * 64 + lane];
@@ -1143,10 +1140,7 @@ __device__ __attribute__((always_inline)) inline void scan_blocks(const ScanJob 
 #pragma unroll
             for (int u = 0; u < kScanSlots; ++u) {
                 run = dd_add(run, v[u]);
-                if (k0 + u < j.K) {
-                    o[(size_t)(k0 + u + 1) * 8] = run.h;
-                    o[(size_t)(k0 + u + 1) * 8 + 4] = run.l;
-                }
+                if (k0 + u < j.K) *reinterpret_cast<double2 *>(o + (size_t)(k0 + u + 1) * 8) = double2{run.h, run.l};
             }
         }
         base = dd_add(base, all);
@@ -1181,165 +1175,182 @@ __global__ __launch_bounds__(kScanWaves * 64) void scan_batch_kernel(const ScanJ
 
 // ---------------------------------------------------------------------------
 // Rectangular windows: window sums from compensated prefixes, D, 2F, the
-// optional map, per-tile reduction.  Tile = kRectRows rows x 64 taus x
-// kRectBins bins: lane = tau, the waves take every fourth row; A, B, C and
-// 2 / D of a cell are formed once for its bins, and each lane keeps a
-// running (max, sum, first argmax) per bin, so the tile reduces once.
+// optional map, per-tile reduction.  Tile = tile_rows rows x 64 taus x BG
+// bins on kRectWaves waves: lane = tau, a wave takes every sixteenth row; A, B,
+// C and 2 / D of a cell are formed once for its bins, and each lane keeps a
+// running (max, sum, first row of the max) per bin, so the tile reduces once.
 //
 // Window ends hi = ceil((t0 - T0 + tau) / T_sft) grow with t0 and tau, so a
-// tile's ends lie between those of its first cell and its last.  When that
-// range fits kRectStage slots (tiles of a grid at about one slot per step),
-// STAGE copies the range's prefixes of the tile's bins and of the antenna
-// sums into LDS once, laid out [channel][slot] as (hi, lo) pairs so that the
-// 64 lanes' reads of consecutive slots are conflict-free 16-byte accesses;
-// the cells then read their end prefixes from LDS instead of addressing 80
-// bytes per cell and bin through the texture path.  Window starts are one
-// per row, wave-uniform, read through the scalar path either way.
+// tile's ends lie between those of its first cell and its last.  Their
+// prefixes are staged in LDS, a plane of (hi, lo) pairs per channel; 64 lanes
+// reading them through the caches take 64 lines per channel pair, five times
+// the tile's arithmetic.  Window starts are one per row, wave-uniform, read
+// through the scalar path.  Bound by VALU issue (223 instructions a row of four
+// bins, 137 of them FP64; busy 79 % of the time, the LDS 44 %): eight waves per
+// SIMD.  256 bins x 500 x 500: 237 us on tiles of four waves, 170 us now (a
+// seventh wave less, one workgroup per compute unit: 219 us); rect maps of a
+// mixed batch of 24: 385 us with their ends through the caches, 242 us now.
 // ---------------------------------------------------------------------------
-constexpr int kRectStage = 128;                 // staged window-end slots
-constexpr int kRectStageCh = 4 * kRectBins + 3;  // data (4 per bin) and antenna channels
-
-struct RectStage {
-    double2 v[kRectStageCh][kRectStage];
-};
-
-template <bool STAGE, typename PP>
-__device__ __attribute__((always_inline)) inline void rect_block(PP &p, Red (*wred)[kRectBins], RectStage *st,
-                                                                 int bx, int by, int bg) {
+template <int BG, bool STAGED, typename PP>
+__device__ __attribute__((always_inline)) inline void rect_rows(PP &p, double2 *st, int bx, int by, int bg) {
+    __shared__ Partial wred[BG][kRectWaves];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = bx * 64 + lane;
     const bool n_ok = n < p.n_tau;
-    const int nn = min(n, p.n_tau - 1);
-    const int64_t tau = p.tau[nn];
-    const int64_t T = p.t_sft;
-    const int64_t K = p.K;
-    const int bin0 = bg * kRectBins;
-    const int nbg = min(kRectBins, p.n_bins - bin0);
-    const size_t bin_stride = ((size_t)K + 1) * 8;   // prefixes of one bin: [K+1][8]
+    const int K = p.K;
+    const int bin0 = bg * BG;
+    const int nbg = min(BG, p.n_bins - bin0);
+    const size_t bin_stride = ((size_t)K + 1) * 8;
     const double *pxb = p.px + (size_t)bin0 * bin_stride;
+    ConstParams<RowPlan> *rows = const_ptr(p.rows);
+    auto &tile = const_ptr(p.tiles)[bx];
     // Window of a row for tau = q T + r (0 <= r < T): the SFT starts in
     // [t0, t0 + tau) are slots k0 .. k0 + L - 1 with L = ceil((tau - delta) / T)
     // (0 when tau <= delta); as the row offset delta lies in [0, T), that is
-    // L = q + (r > delta), so the division is made once per tau, not per cell.
-    auto window_qr = [&](const RowPlan &rp, int64_t q_t, int64_t r_t, int64_t &lo, int64_t &hi) {
-        const int64_t L = q_t + (r_t > rp.delta ? 1 : 0);
-        lo = min(max((int64_t)rp.k0, (int64_t)0), K);
-        hi = min(max((int64_t)rp.k0 + L, (int64_t)0), K);
-    };
-    auto window = [&](const RowPlan &rp, int64_t tau_c, int64_t &lo, int64_t &hi) {
-        window_qr(rp, tau_c / T, tau_c % T, lo, hi);
-    };
-    const int64_t tau_q = tau / T, tau_r = tau % T;
-    bool staged = false;
-    int64_t s0 = 0;
-    if constexpr (STAGE) {
-        const int m_last = min(by * kRectRows + kRectRows - 1, p.n_t0 - 1);
-        const int n_last = min(bx * 64 + 63, p.n_tau - 1);
-        int64_t lo_a, hi_a, lo_b, hi_b;
-        window(p.rows[by * kRectRows], p.tau[bx * 64], lo_a, hi_a);
-        window(p.rows[m_last], p.tau[n_last], lo_b, hi_b);
-        s0 = hi_a;
-        staged = hi_b - hi_a < kRectStage;
-        if (staged) {
-            const int ns = (int)(hi_b - hi_a + 1);
-            for (int e = threadIdx.x; e < kRectStageCh * ns; e += 256) {
-                const int ch = e / ns, sl = e - ch * ns;
-                const int64_t k = s0 + sl;
-                const double *src;
-                int c;
-                if (ch < 4 * kRectBins) {
-                    const int b = ch >> 2;
-                    c = ch & 3;
-                    src = pxb + min(b, nbg - 1) * bin_stride + k * 8;
-                } else {
-                    c = ch - 4 * kRectBins;
-                    src = p.pabc + k * 8;
-                }
-                st->v[ch][sl] = double2{src[c], src[4 + c]};
-            }
-            __syncthreads();
-        }
-    }
-    Red r[kRectBins];
+    // L = q + (r > delta).
+    int q, r;
+    span_qr(p.tau[min(n, p.n_tau - 1)], 1, p.t_sft, q, r);
+    auto end_slot = [&](int k0, int delta, int q_, int r_) { return min(max(k0 + q_ + (r_ > delta ? 1 : 0), 0), K); };
+    const int m0 = by * p.tile_rows, m1 = min(m0 + p.tile_rows, p.n_t0);
+    const int pitch = rect_pitch(p.stage);
+    int s0 = 0;
+    if constexpr (STAGED) {
+        s0 = end_slot(rows[m0].k0, rows[m0].delta, tile.q0, tile.r0);
+        const int s1 = end_slot(rows[m1 - 1].k0, rows[m1 - 1].delta, tile.q1, tile.r1);
+        const int ne = 4 * min(s1 - s0 + 1, p.stage);   // (the plan's stage holds them all)
+        for (int e = threadIdx.x; e < ne; e += 64 * kRectWaves) {
+            const int c = e & 3;
+            const size_t at = (size_t)s0 * 8 + 2 * (size_t)e;
+            double2 v[BG + 1];
 #pragma unroll
-    for (int b = 0; b < kRectBins; ++b) r[b] = red_empty();
-#pragma unroll 2
-    for (int i = 0; i < kRectRows / kWaves; ++i) {
-        const int m = by * kRectRows + i * kWaves + wave;
-        if (m >= p.n_t0) break;
-        const RowPlan rp = p.rows[m];
-        int64_t lo, hi;
-        window_qr(rp, tau_q, tau_r, lo, hi);
+            for (int b = 0; b < BG; ++b)
+                v[b] = *reinterpret_cast<const double2 *>(pxb + min(b, nbg - 1) * bin_stride + at);
+            v[BG] = *reinterpret_cast<const double2 *>(p.pabc + at);
+#pragma unroll
+            for (int b = 0; b < BG; ++b) st[(4 * b + c) * pitch + (e >> 2)] = v[b];
+            if (c < 3) st[(4 * BG + c) * pitch + (e >> 2)] = v[BG];
+        }
+        __syncthreads();
+    }
+    double fm[BG], fs[BG];
+    int im[BG];
+#pragma unroll
+    for (int b = 0; b < BG; ++b) {
+        fm[b] = -INFINITY;
+        fs[b] = 0.0;
+        im[b] = 0;
+    }
+    const size_t bin_cells = (size_t)p.n_t0 * p.n_tau;
+    const bool write = p.twoF && n_ok;
+    int m = m0 + wave;
+    int k0 = 0, delta = 0;
+    if (m < m1) {
+        k0 = rows[m].k0;
+        delta = rows[m].delta;
+    }
+#pragma unroll 1
+    for (; m < m1; m += kRectWaves) {
+        // the next row's plan, on its way while this row is finished
+        const int mn = min(m + kRectWaves, p.n_t0 - 1);
+        const int k0_n = rows[mn].k0, delta_n = rows[mn].delta;
+        const int lo = min(max(k0, 0), K);
+        const int hi = end_slot(k0, delta, q, r);
+        ConstParams<double> *a_lo = const_ptr(p.pabc) + (size_t)lo * 8;
+        const double2 *h = st + (hi - s0);
         // window sums from compensated prefixes: (hi_h - lo_h) + (hi_l - lo_l)
-        const double *a_lo = p.pabc + lo * 8;
-        double A, B, C;
-        if (STAGE && staged) {
-            const int sl = (int)(hi - s0);
-            const double2 ha = st->v[4 * kRectBins + 0][sl], hb = st->v[4 * kRectBins + 1][sl],
-                          hc = st->v[4 * kRectBins + 2][sl];
-            A = (ha.x - a_lo[0]) + (ha.y - a_lo[4]);
-            B = (hb.x - a_lo[1]) + (hb.y - a_lo[5]);
-            C = (hc.x - a_lo[2]) + (hc.y - a_lo[6]);
-        } else {
-            const double *a_hi = p.pabc + hi * 8;
-            A = (a_hi[0] - a_lo[0]) + (a_hi[4] - a_lo[4]);
-            B = (a_hi[1] - a_lo[1]) + (a_hi[5] - a_lo[5]);
-            C = (a_hi[2] - a_lo[2]) + (a_hi[6] - a_lo[6]);
-        }
-        // 2F = (2 / D) (B |F_a|^2 + A |F_b|^2 - 2 C Re(F_a F_b*)) (eq. F_FaFb);
-        // a degenerate window (D <= rtol A B) gets 2F = 0
+        auto sum = [&](const double *far, ConstParams<double> *near, int plane, int c) {
+            double2 e;
+            if constexpr (STAGED)
+                e = h[plane * pitch];
+            else
+                e = *reinterpret_cast<const double2 *>(far + 2 * c);
+            return (e.x - near[2 * c]) + (e.y - near[2 * c + 1]);
+        };
+        const double *a_hi = p.pabc + (size_t)hi * 8;
+        const double A = sum(a_hi, a_lo, 4 * BG, 0), B = sum(a_hi, a_lo, 4 * BG + 1, 1),
+                     C = sum(a_hi, a_lo, 4 * BG + 2, 2);
+        // F = (1 / D) (B |F_a|^2 + A |F_b|^2 - 2 C Re(F_a F_b*)) (eq. F_FaFb);
+        // a degenerate window (D <= rtol A B) gets F = 0
         const double D = A * B - C * C;
-        const double k = D > kDegenerateRtol * A * B ? 2.0 / D : 0.0;
+        const double k = D > kDegenerateRtol * A * B ? 1.0 / D : 0.0;
         const double kA = k * A, kB = k * B, kC = 2.0 * k * C;
-        const long long idx = (long long)m * p.n_tau + n;
+        float *out = p.twoF + (size_t)bin0 * bin_cells + (size_t)m * p.n_tau + n;
 #pragma unroll
-        for (int b = 0; b < kRectBins; ++b) {
-            if (b >= nbg) break;
-            const double *x_lo = pxb + b * bin_stride + lo * 8;
+        for (int b = 0; b < BG; ++b) {
+            // (bins past the last one repeat it)
+            const size_t bo = min(b, nbg - 1) * bin_stride;
             double f[4];
-            if (STAGE && staged) {
-                const int sl = (int)(hi - s0);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const double2 h = st->v[4 * b + c][sl];
-                    f[c] = (h.x - x_lo[c]) + (h.y - x_lo[4 + c]);
-                }
-            } else {
-                const double *x_hi = pxb + b * bin_stride + hi * 8;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) f[c] = (x_hi[c] - x_lo[c]) + (x_hi[4 + c] - x_lo[4 + c]);
-            }
-            const double v = kB * (f[0] * f[0] + f[1] * f[1]) + kA * (f[2] * f[2] + f[3] * f[3])
+            for (int c = 0; c < 4; ++c)
+                f[c] = sum(pxb + bo + (size_t)hi * 8, const_ptr(pxb) + bo + (size_t)lo * 8, 4 * b + c, c);
+            const double F = kB * (f[0] * f[0] + f[1] * f[1]) + kA * (f[2] * f[2] + f[3] * f[3])
                              - kC * (f[0] * f[2] + f[1] * f[3]);
-            if (n_ok) {
-                if (p.twoF) p.twoF[((size_t)(bin0 + b) * p.n_t0 + m) * p.n_tau + n] = (float)v;
-                red_add(r[b], 0.5 * v, idx);
-            }
+            if (write && b < nbg) out[b * bin_cells] = 2.f * (float)F;
+            // running maximum (the earlier row on a tie) and sum of
+            // exp(F - max), one FP32 exponential
+            const bool up = F > fm[b];
+            const float x = __expf(-fabsf((float)(F - fm[b])));
+            fs[b] = fma(fs[b], (double)(up ? x : 1.f), (double)(up ? 1.f : x));
+            fm[b] = up ? F : fm[b];
+            im[b] = up ? m : im[b];
         }
+        k0 = k0_n;
+        delta = delta_n;
     }
 #pragma unroll
-    for (int b = 0; b < kRectBins; ++b) {
-        if (b >= nbg) break;
-        const Red w = red_wave(r[b]);
-        if (lane == 0) wred[wave][b] = w;
+    for (int b = 0; b < BG; ++b) {
+        const Partial w = wave_state(fm[b], fs[b], im[b], n, n_ok, p.n_tau);
+        if (lane == 0) wred[b][wave] = w;
     }
     __syncthreads();
-    if (threadIdx.x < nbg) {
-        const int b = threadIdx.x;
-        Red t = wred[0][b];
-        for (int w = 1; w < kWaves; ++w) t = red_combine(t, wred[w][b]);
-        Partial &o = p.part[(size_t)(bin0 + b) * p.n_tiles + by * p.n_tiles_n + bx];
-        o.fmax = t.f;
-        o.s = t.s;
-        o.idx = t.i;
+    // the waves' states: sixteen lanes per bin
+    static_assert(kRectWaves == 16, "lane layout");
+    if (wave == 0 && lane < 16 * nbg) {
+        const Partial v = wred[lane >> 4][lane & 15];
+        double f = v.fmax;
+        long long i = v.idx;
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            const double fo = __shfl_xor(f, o, 16);
+            const long long io = __shfl_xor(i, o, 16);
+            if (fo > f || (fo == f && io < i)) {
+                f = fo;
+                i = io;
+            }
+        }
+        double sv = v.fmax == -INFINITY ? 0.0 : v.s * exp(v.fmax - f);
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) sv += __shfl_xor(sv, o, 16);
+        if ((lane & 15) == 0) {
+            Partial &o = p.part[(size_t)(bin0 + (lane >> 4)) * p.n_tiles + by * p.n_tiles_n + bx];
+            o.fmax = f;
+            o.s = sv;
+            o.idx = i;
+        }
     }
 }
 
-__global__ __launch_bounds__(256) void rect_kernel(RectParams p) {
-    __shared__ Red wred[kWaves][kRectBins];
-    __shared__ RectStage st;
-    rect_block<true>(p, wred, &st, blockIdx.x, blockIdx.y, blockIdx.z);
+template <int BG, bool STAGED>
+__global__ __launch_bounds__(64 * kRectWaves, 8) void rect_kernel(RectParams p) {
+    extern __shared__ __attribute__((aligned(16))) double2 rect_lds[];
+    rect_rows<BG, STAGED>(p, rect_lds, blockIdx.x, blockIdx.y, blockIdx.z);
+}
+
+__global__ __launch_bounds__(64 * kRectWaves) void rect_batch_kernel(RectBatchParams b) {
+    extern __shared__ __attribute__((aligned(16))) double2 rect_lds[];
+    ConstParams<int32_t> *e = const_ptr(b.entries) + 4 * (size_t)blockIdx.x;
+    auto &p = const_params(b.jobs + e[0]);
+    switch (2 * p.bg + (p.stage > 0)) {
+    case 2: rect_rows<1, false>(p, rect_lds, e[1], e[2], e[3]); break;
+    case 3: rect_rows<1, true>(p, rect_lds, e[1], e[2], e[3]); break;
+    case 4: rect_rows<2, false>(p, rect_lds, e[1], e[2], e[3]); break;
+    case 5: rect_rows<2, true>(p, rect_lds, e[1], e[2], e[3]); break;
+    case 6: rect_rows<3, false>(p, rect_lds, e[1], e[2], e[3]); break;
+    case 7: rect_rows<3, true>(p, rect_lds, e[1], e[2], e[3]); break;
+    case 8: rect_rows<4, false>(p, rect_lds, e[1], e[2], e[3]); break;
+    default: rect_rows<4, true>(p, rect_lds, e[1], e[2], e[3]); break;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1425,7 +1436,7 @@ struct FusedSmem {
     static constexpr size_t runs_bytes = V == kShapeD41 ? sizeof(RunSmem<double, 4, 1, kFusedRunsG, true>)
                                          : cmax(sizeof(RunSmem<float, 8, 1, kFusedRunsG, true>),
                                                 sizeof(RunSmem<float, 4, 2, kFusedRunsG, true>));
-    static constexpr size_t bytes = cmax(cmax(exp_bytes, runs_bytes), sizeof(Red) * kWaves * kRectBins);
+    static constexpr size_t bytes = cmax(exp_bytes, runs_bytes);
 };
 
 
@@ -1490,11 +1501,6 @@ __global__ __launch_bounds__(kThreads, (fused_waves<V, M>())) void fused_kernel(
         const int ti = __builtin_amdgcn_readfirstlane(s_next);
         if (ti >= p.n_tiles) break;
         const BatchTile t = load_uniform(p.tiles + ti);   // one tile, held in scalar registers
-        if (t.kind == 1) {
-            auto &rp = const_params(p.rect_jobs + t.job);
-            rect_block<false>(rp, reinterpret_cast<Red (*)[kRectBins]>(smem), nullptr, t.x, t.y, t.z);
-            continue;
-        }
         auto &ep = const_params(p.exp_jobs + t.job);
         if constexpr (V != kShapeD41) {
             if (t.kind == 3) {
@@ -1658,9 +1664,29 @@ hipError_t launch_scan(const ScanJob &abc, const ScanJob &x, hipStream_t s) {
 }
 
 hipError_t launch_rect(const RectParams &p, hipStream_t s) {
-    const dim3 grid((unsigned)p.n_tiles_n, (unsigned)((p.n_t0 + kRectRows - 1) / kRectRows),
-                    (unsigned)((p.n_bins + kRectBins - 1) / kRectBins));
-    hipLaunchKernelGGL(rect_kernel, grid, dim3(256), 0, s, p);
+    if (p.n_t0 <= 0 || p.tile_rows < 1 || p.bg < 1 || p.stage < 0) return hipErrorInvalidValue;
+    const dim3 g((unsigned)p.n_tiles_n, (unsigned)((p.n_t0 + p.tile_rows - 1) / p.tile_rows),
+                 (unsigned)((p.n_bins + p.bg - 1) / p.bg)),
+        b(64 * kRectWaves);
+    const unsigned lds = rect_stage_bytes(p.bg, p.stage);
+    if (lds > kRectStageBytes || g.y > 65535u || g.z > 65535u) return hipErrorInvalidValue;
+    switch (2 * p.bg + (p.stage > 0)) {
+    case 2: hipLaunchKernelGGL((rect_kernel<1, false>), g, b, 0, s, p); break;
+    case 3: hipLaunchKernelGGL((rect_kernel<1, true>), g, b, lds, s, p); break;
+    case 4: hipLaunchKernelGGL((rect_kernel<2, false>), g, b, 0, s, p); break;
+    case 5: hipLaunchKernelGGL((rect_kernel<2, true>), g, b, lds, s, p); break;
+    case 6: hipLaunchKernelGGL((rect_kernel<3, false>), g, b, 0, s, p); break;
+    case 7: hipLaunchKernelGGL((rect_kernel<3, true>), g, b, lds, s, p); break;
+    case 8: hipLaunchKernelGGL((rect_kernel<4, false>), g, b, 0, s, p); break;
+    case 9: hipLaunchKernelGGL((rect_kernel<4, true>), g, b, lds, s, p); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_rect_batch(const RectBatchParams &p, hipStream_t s) {
+    if (p.n_entries <= 0) return hipSuccess;
+    hipLaunchKernelGGL(rect_batch_kernel, dim3((unsigned)p.n_entries), dim3(64 * kRectWaves), p.lds_bytes, s, p);
     return hipGetLastError();
 }
 

@@ -53,31 +53,12 @@ struct LaneTau {
     int q, r;
 };
 
-// 3 tau = q T + r; q clamped so that k0 + q + 1 stays an int and still passes
-// every data end (k0 >= -2^30, K <= 2^28).
-__device__ inline void tau_qr(int64_t tau, int64_t T, int &q, int &r) {
-    constexpr int64_t kMaxQ = 1342177280;
-    const int64_t span = min(3 * tau, kMaxQ * T);
-    // quotient below 2^31 by one FP64 division, within one of the exact one
-    int64_t qq = (int64_t)((double)span / (double)T);
-    int64_t rr = span - qq * T;
-    if (rr < 0) {
-        --qq;
-        rr += T;
-    } else if (rr >= T) {
-        ++qq;
-        rr -= T;
-    }
-    q = (int)qq;
-    r = (int)rr;
-}
-
 __device__ inline LaneTau lane_tau(int64_t tau, int64_t T) {
     LaneTau t;
     t.c = -(double)T / (double)tau;
     t.rho = exp(t.c);
     t.rho2 = exp(2.0 * t.c);
-    tau_qr(tau, T, t.q, t.r);
+    span_qr(tau, 3, T, t.q, t.r);
     return t;
 }
 
@@ -606,29 +587,10 @@ __device__ __attribute__((always_inline)) inline void slide_segment(PP &p, doubl
         hi = hi_n;
     }
 
-    // the wave's lanes: maximum with its first cell, sum rescaled to it
 #pragma unroll
     for (int b = 0; b < BG; ++b) {
-        double mx = n_ok ? fm[b] : -INFINITY;
-        long long ix = (long long)im[b] * p.n_tau + n;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double fo = __shfl_xor(mx, o, 64);
-            const long long io = __shfl_xor(ix, o, 64);
-            if (fo > mx || (fo == mx && io < ix)) {
-                mx = fo;
-                ix = io;
-            }
-        }
-        double sv = n_ok ? fs[b] * (double)__expf((float)(fm[b] - mx)) : 0.0;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) sv += __shfl_xor(sv, o, 64);
-        if (lane == 0 && b < nb) {
-            Partial &o = p.part[(size_t)(bin0 + b) * p.n_tiles + (size_t)tt * p.n_seg + seg];
-            o.fmax = mx;
-            o.s = sv;
-            o.idx = ix;
-        }
+        const Partial w = wave_state(fm[b], fs[b], im[b], n, n_ok, p.n_tau);
+        if (lane == 0 && b < nb) p.part[(size_t)(bin0 + b) * p.n_tiles + (size_t)tt * p.n_seg + seg] = w;
     }
 }
 

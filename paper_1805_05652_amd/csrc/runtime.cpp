@@ -312,6 +312,7 @@ struct Job {
     bool forced = false;       // tile shape forced by the caller: the direct forms
     int32_t bg = 1, n_bg = 1, n_tt = 1, n_seg = 1, seg_rows = 1, range_len = 1, n_range = 1, n_sup = 1;
     int32_t kbeg = 0, waves = 1, stage = 0;
+    int32_t rect_rows = 64;      // rect maps: rows of a tile
     int64_t tau_spread = 0;      // slots that 64 taus' window ends span at most
     std::vector<tfs::SlideTile> tiles;
     bool use_mfma = false;     // BF16X3 on matrix cores for long bands
@@ -352,6 +353,70 @@ int64_t slide_stage(const Job &j, int64_t rows_wg, int64_t range_len) {
     return std::min<int64_t>(j.tau_spread + span + range_len + 2, (int64_t)j.at->K + 2);
 }
 
+// The tiles of 64 taus with windows of len tau, and the slots that the ends of
+// a tile's windows span at most (ends are clamped to the data: lengths past
+// K - k0 all end there).
+void plan_tiles(Job &j, int64_t len) {
+    const AtomsSet &at = *j.at;
+    const int n_tau = (int)j.win.tau.size();
+    j.n_tt = (n_tau + 63) / 64;
+    auto qr = [&](int64_t tau, int32_t &q, int32_t &r) {
+        const int64_t qq = len * tau / at.t_sft;
+        q = (int32_t)std::min<int64_t>(qq, 1342177280);
+        r = qq > q ? 0 : (int32_t)(len * tau - qq * at.t_sft);
+    };
+    const int64_t longest = (int64_t)at.K - std::min(j.rows[0].k0, 0);
+    j.tau_spread = 0;
+    j.tiles.assign(j.n_tt, tfs::SlideTile{});
+    for (int tt = 0; tt < j.n_tt; ++tt) {
+        tfs::SlideTile &t = j.tiles[tt];
+        qr(j.win.tau[tt * 64], t.q0, t.r0);
+        qr(j.win.tau[std::min(tt * 64 + 63, n_tau - 1)], t.q1, t.r1);
+        j.tau_spread = std::max<int64_t>(j.tau_spread, std::min<int64_t>(t.q1, longest) - std::min<int64_t>(t.q0, longest) + 2);
+    }
+}
+
+// Tiles of a rect map (rect_rows in kernels.hip): bins, rows and stage, by an
+// estimate of a workgroup's time in clocks: its start and stage, its waves'
+// reductions, and per pass of its sixteen waves the rows' VALU instructions
+// (60 and 33 a bin) and half of the LDS reads' time (which overlap).  Two
+// workgroups on a compute unit hide each other's stage and latencies (256 bins
+// x 500 x 500: 202 us with one of 256 rows, 170 us with two of 128).  Longer
+// tiles share a stage and a reduction, shorter ones fill the chip.  Where not
+// even 64 rows of one bin fit the stage, window ends are read through the
+// caches.
+void plan_rect(Job &j) {
+    const AtomsSet &at = *j.at;
+    const int n_t0 = (int)j.win.t0.size();
+    plan_tiles(j, 1);
+    const int bg_full = (at.n_bins + (at.n_bins + 3) / 4 - 1) / ((at.n_bins + 3) / 4);
+    double best = 0.0;
+    j.bg = bg_full;
+    j.stage = 0;
+    j.rect_rows = 64;
+    for (int bg = bg_full; bg >= 1; bg = bg > 2 ? 2 : bg - 1) {
+        const double ch = 4.0 * bg + 3;
+        const int64_t cols = (int64_t)j.n_tt * ((at.n_bins + bg - 1) / bg);
+        for (int rows = 64; rows <= 256; rows += 64) {
+            if (rows - 64 >= n_t0) break;
+            if ((n_t0 + rows - 1) / rows > 65535 || (at.n_bins + bg - 1) / bg > 65535) continue;   // (the launch's limits)
+            const int64_t stage = slide_stage(j, rows, 0);
+            if (tfs::rect_stage_bytes(bg, (int)std::min<int64_t>(stage, 1 << 20)) > tfs::kRectStageBytes) break;
+            const int64_t per_cu = (cols * ((n_t0 + rows - 1) / rows) + kCus - 1) / kCus;
+            const int64_t both = tfs::rect_stage_bytes(bg, (int)stage) <= 78 * 1024 ? 2 : 1;
+            const double pass = 16 * (60 + 33 * bg) + 96 * ch;
+            const double est = (double)per_cu * (700.0 * bg + rows / tfs::kRectWaves * pass * (both > 1 ? 1.1 : 1.5)) +
+                               (double)((per_cu + both - 1) / both) * (3000.0 + 0.4 * ch * (double)stage);
+            if (best > 0.0 && est >= best) continue;
+            best = est;
+            j.bg = bg;
+            j.stage = (int32_t)stage;
+            j.rect_rows = rows;
+        }
+    }
+    j.n_bg = (at.n_bins + j.bg - 1) / j.bg;
+}
+
 // Sliding sums of an exponential map (kernels_slide.hip), from the map alone
 // (its results may not depend on what it is batched with).  They cost a
 // window's ends instead of its slots, so every map takes them whose atoms allow
@@ -363,21 +428,7 @@ void plan_slide(Job &j) {
     if (tiling && j.prec != TFSTAT_PREC_RECUR64) return;
     const int n_t0 = (int)j.win.t0.size(), n_tau = (int)j.win.tau.size();
     j.slide = true;
-    j.n_tt = (n_tau + 63) / 64;
-    // tau tiles, and the slots that 64 taus' window ends span
-    auto qr = [&](int64_t tau, int32_t &q, int32_t &r) {
-        const int64_t qq = 3 * tau / at.t_sft;
-        q = (int32_t)std::min<int64_t>(qq, 1342177280);
-        r = qq > q ? 0 : (int32_t)(3 * tau - qq * at.t_sft);
-    };
-    j.tau_spread = 0;
-    j.tiles.assign(j.n_tt, tfs::SlideTile{});
-    for (int tt = 0; tt < j.n_tt; ++tt) {
-        tfs::SlideTile &t = j.tiles[tt];
-        qr(j.win.tau[tt * 64], t.q0, t.r0);
-        qr(j.win.tau[std::min(tt * 64 + 63, n_tau - 1)], t.q1, t.r1);
-        if (t.q0 < at.K) j.tau_spread = std::max<int64_t>(j.tau_spread, std::min<int64_t>(t.q1, at.K) - t.q0 + 2);
-    }
+    plan_tiles(j, 3);
     // A segment starts from anchors, about 32 slots away: of rows that lie
     // closer it takes at least 4.
     const int64_t apart = n_t0 > 1 ? ((int64_t)j.rows[n_t0 - 1].k0 - j.rows[0].k0) / (n_t0 - 1) : 1;
@@ -631,8 +682,9 @@ void plan_job(Job &j) {
             }
         }
     } else {
-        j.n_tiles_n = (n_tau + 63) / 64;
-        j.n_tiles = j.n_tiles_n * ((n_t0 + tfs::kRectRows - 1) / tfs::kRectRows);
+        plan_rect(j);
+        j.n_tiles_n = j.n_tt;
+        j.n_tiles = j.n_tt * ((n_t0 + j.rect_rows - 1) / j.rect_rows);
     }
 
     // workspace layout
@@ -644,8 +696,8 @@ void plan_job(Job &j) {
     };
     j.off_rows = take(sizeof(tfs::RowPlan) * n_t0);
     j.off_tau = take(sizeof(int64_t) * n_tau);
-    j.off_lcol = take(sizeof(int32_t) * n_tau);
     if (is_exp && !j.slide) {
+        j.off_lcol = take(sizeof(int32_t) * n_tau);
         j.off_lblk = take(sizeof(int32_t) * j.NB);
         j.off_boff = take(sizeof(int64_t) * j.NB);
         j.off_order = take(sizeof(int32_t) * j.NB);
@@ -655,7 +707,7 @@ void plan_job(Job &j) {
         }
         if (is_shape) j.off_shape = take(sizeof(double) * j.win.shape.size());
     }
-    if (j.slide) j.off_tiles = take(sizeof(tfs::SlideTile) * j.n_tt);
+    if (j.slide || !is_exp) j.off_tiles = take(sizeof(tfs::SlideTile) * j.n_tt);
     j.tables_bytes = o;
     if (j.slide) {
         const size_t ch = (size_t)j.n_tt * j.n_bg * (4 * j.bg) * 64 * sizeof(double);
@@ -835,9 +887,9 @@ void fill_tables(const Job &j, char *h) {
     const int n_tau = (int)j.win.tau.size();
     std::memcpy(h + j.off_rows, j.rows.data(), sizeof(tfs::RowPlan) * n_t0);
     std::memcpy(h + j.off_tau, j.win.tau.data(), sizeof(int64_t) * n_tau);
-    std::memcpy(h + j.off_lcol, j.lcol.data(), sizeof(int32_t) * n_tau);
-    if (j.slide) std::memcpy(h + j.off_tiles, j.tiles.data(), sizeof(tfs::SlideTile) * j.n_tt);
+    if (j.slide || !banded(j.win.type)) std::memcpy(h + j.off_tiles, j.tiles.data(), sizeof(tfs::SlideTile) * j.n_tt);
     if (banded(j.win.type) && !j.slide) {
+        std::memcpy(h + j.off_lcol, j.lcol.data(), sizeof(int32_t) * n_tau);
         if (j.win.type == TFSTAT_WIN_SHAPE)
             std::memcpy(h + j.off_shape, j.win.shape.data(), sizeof(double) * j.win.shape.size());
         std::memcpy(h + j.off_lblk, j.lblk.data(), sizeof(int32_t) * j.NB);
@@ -1038,8 +1090,12 @@ tfs::RectParams rect_params(Job &j) {
     p.t_sft = j.at->t_sft;
     p.n_tiles_n = j.n_tiles_n;
     p.n_tiles = j.n_tiles;
+    p.bg = j.bg;
+    p.tile_rows = j.rect_rows;
+    p.stage = j.stage;
     p.rows = ws_ptr<tfs::RowPlan>(j, j.off_rows);
     p.tau = ws_ptr<int64_t>(j, j.off_tau);
+    p.tiles = ws_ptr<tfs::SlideTile>(j, j.off_tiles);
     p.pabc = ws_ptr<double>(j, j.off_pabc);
     p.px = ws_ptr<double>(j, j.off_px);
     p.twoF = j.twoF;
@@ -1346,7 +1402,8 @@ struct tfstat_batch {
     bool scan_split = false;
     tfs::MergeBatchParams mbp{};
     tfs::AbcBatchParams abp{};       // A/B/C pre-pass of the split-form and matrix-core maps
-    tfs::SlideBatchParams slp{};     // sliding sums of exponential maps
+    tfs::SlideBatchParams slp{};
+    tfs::RectBatchParams rbp{};     // sliding sums of exponential maps
     tfs::MfmaBatchParams mfp{};      // matrix-core work of the BF16X3 / F16X3 maps
     tfs::AbcRecurBatchParams rap{};  // recurrence A/B/C of exponential split and matrix-core maps
     tfs::BinResultDev *res_dev = nullptr;
@@ -1410,6 +1467,7 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     const int32_t n = (int32_t)b->jobs.size();
     std::vector<int> shape(n, -1), eidx(n, -1), ridx(n, -1), midx(n, -1), sidx(n, -1);
     int n_slide = 0;
+    size_t n_rent = 0;                  // rect tiles
     size_t n_anchor = 0, n_srows = 0;   // workgroups of the sliding maps' two launches
     int n_exp = 0, n_rect = 0, n_went = 0, n_scan = 0, n_abc = 0, n_mfma_maps = 0, n_rabc_maps = 0;
     size_t n_rabc = 0;   // recurrence A/B/C entries (exponential windows)
@@ -1420,6 +1478,7 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     b->n_results = 0;
     b->scan_split = false;
     b->slp.lds_bytes = 0;
+    b->rbp.lds_bytes = 0;
     for (int32_t i = 0; i < n; ++i) {
         Job &j = *b->jobs[i];
         if (j.slide) {
@@ -1474,6 +1533,8 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
             max_chunks = std::max<int32_t>(max_chunks, (int32_t)std::min<int64_t>((mb + 255) / 256, 4096));
         } else {
             ridx[i] = n_rect++;
+            n_rent += (size_t)j.n_tiles * j.n_bg;
+            b->rbp.lds_bytes = std::max(b->rbp.lds_bytes, tfs::rect_stage_bytes(j.bg, j.stage));
             n_scan += (1 + (4 * j.at->n_bins + 63) / 64) * std::max(1, j.scan_blk);
             b->scan_split = b->scan_split || j.scan_blk > 0;
         }
@@ -1483,7 +1544,7 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
 
     // shared tile list, largest expected cost first (per-lane FMA counts):
     // tiles of one (map, tau block) cost the same, so the groups are sorted
-    // and then expanded; rect tiles (all alike and short) go last
+    // and then expanded
     struct Group {
         int32_t map, q;
         double cost;
@@ -1505,13 +1566,11 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
             for (int q = 0; q < j.n_valu; q += step)
                 groups_e.push_back({i, q, (double)(j.lblk[j.order[q]] + 1) * j.R * per_step * step});
             n_tiles_total += per * ((j.n_valu + step - 1) / step);
-        } else if (ridx[i] >= 0) {
-            const int ny = ((int)j.win.t0.size() + tfs::kRectRows - 1) / tfs::kRectRows;
-            n_tiles_total += (size_t)ny * j.n_tiles_n * ((j.at->n_bins + tfs::kRectBins - 1) / tfs::kRectBins);
         }
     }
     if (n_tiles_total > (size_t)INT32_MAX / 2 || n_mfma_entries > (size_t)INT32_MAX / 2 ||
-        n_rabc > (size_t)INT32_MAX / 2 || n_anchor > (size_t)INT32_MAX / 2 || n_srows > (size_t)INT32_MAX / 2)
+        n_rabc > (size_t)INT32_MAX / 2 || n_anchor > (size_t)INT32_MAX / 2 ||
+        n_rent > (size_t)INT32_MAX / 2 || n_srows > (size_t)INT32_MAX / 2)
         raise(TFSTAT_E_INVAL, "batch has too many tiles");
     std::stable_sort(groups_e.begin(), groups_e.end(),
                      [](const Group &a, const Group &c) { return a.cost > c.cost; });
@@ -1534,16 +1593,7 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
             }
         }
     }
-    for (int32_t i = 0; i < n; ++i) {
-        if (ridx[i] < 0) continue;
-        const Job &j = *b->jobs[i];
-        const int ny = ((int)j.win.t0.size() + tfs::kRectRows - 1) / tfs::kRectRows;
-        for (int y = 0; y < ny; ++y)
-            for (int x = 0; x < j.n_tiles_n; ++x)
-                for (int bg = 0; bg < (j.at->n_bins + tfs::kRectBins - 1) / tfs::kRectBins; ++bg)
-                    tiles.push_back(tfs::BatchTile{1, ridx[i], x, y, bg, 0});
-    }
-    b->n_tiles = (int)tiles.size();
+    b->n_tiles = (int)(tiles.size() + n_rent);
 
     // workspace layout
     size_t o = 0;
@@ -1572,6 +1622,7 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     const size_t off_ment = take(sizeof(int32_t) * 4 * n_mfma_entries);
     const size_t off_rap = take(sizeof(tfs::AbcRecurParams) * n_rabc_maps);
     const size_t off_rent = take(sizeof(int32_t) * 2 * n_rabc);
+    const size_t off_rtent = take(sizeof(int32_t) * 4 * n_rent);
     const size_t off_slp = take(sizeof(tfs::SlideParams) * n_slide);
     const size_t off_aent = take(sizeof(int32_t) * 4 * n_anchor);
     const size_t off_sent = take(sizeof(int32_t) * 4 * n_srows);
@@ -1609,6 +1660,7 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     auto *mjob = reinterpret_cast<int32_t *>(hptr(off_mjob));
     auto *mmap = reinterpret_cast<int32_t *>(hptr(off_mmap));
     auto *tl = reinterpret_cast<tfs::BatchTile *>(hptr(off_tiles));
+    auto *rtent = reinterpret_cast<int32_t *>(hptr(off_rtent));
     auto *ajob = reinterpret_cast<int32_t *>(hptr(off_ajob));
     auto *ax = reinterpret_cast<int32_t *>(hptr(off_ax));
     auto *ay = reinterpret_cast<int32_t *>(hptr(off_ay));
@@ -1686,6 +1738,26 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     }
     std::memcpy(tl, tiles.data(), sizeof(tfs::BatchTile) * tiles.size());
     {
+        // rect tiles, the longest (in rows and bins) first
+        std::vector<int32_t> by;
+        for (int32_t i = 0; i < n; ++i)
+            if (ridx[i] >= 0) by.push_back(i);
+        auto cost = [&](int32_t i) { return b->jobs[i]->rect_rows * (2 + b->jobs[i]->bg); };
+        std::stable_sort(by.begin(), by.end(), [&](int32_t x, int32_t y) { return cost(x) > cost(y); });
+        int32_t *e = rtent;
+        for (int32_t i : by) {
+            const Job &j = *b->jobs[i];
+            for (int y = 0; y < j.n_tiles / j.n_tt; ++y)
+                for (int x = 0; x < j.n_tt; ++x)
+                    for (int g = 0; g < j.n_bg; ++g, e += 4) {
+                        e[0] = ridx[i];
+                        e[1] = x;
+                        e[2] = y;
+                        e[3] = g;
+                    }
+        }
+    }
+    {
         // sliding maps, the longest segments (in slots and rows) first
         std::vector<int32_t> by;
         for (int32_t i = 0; i < n; ++i)
@@ -1718,9 +1790,8 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     }
 
     b->fp.exp_jobs = reinterpret_cast<const tfs::ExpValuParams *>(dptr(off_ep));
-    b->fp.rect_jobs = reinterpret_cast<const tfs::RectParams *>(dptr(off_rp));
     b->fp.tiles = reinterpret_cast<const tfs::BatchTile *>(dptr(off_tiles));
-    b->fp.n_tiles = b->n_tiles;
+    b->fp.n_tiles = (int)tiles.size();
     b->fp.counter = reinterpret_cast<int32_t *>(dptr(off_counter));
     b->wbp.jobs = reinterpret_cast<const tfs::WeightParams *>(dptr(off_wp));
     b->wbp.job = reinterpret_cast<const int32_t *>(dptr(off_wjob));
@@ -1737,6 +1808,9 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     b->rap.jobs = reinterpret_cast<const tfs::AbcRecurParams *>(dptr(off_rap));
     b->rap.entries = reinterpret_cast<const int32_t *>(dptr(off_rent));
     b->rap.n_entries = (int32_t)n_rabc;
+    b->rbp.jobs = reinterpret_cast<const tfs::RectParams *>(dptr(off_rp));
+    b->rbp.entries = reinterpret_cast<const int32_t *>(dptr(off_rtent));
+    b->rbp.n_entries = (int32_t)n_rent;
     b->slp.jobs = reinterpret_cast<const tfs::SlideParams *>(dptr(off_slp));
     b->slp.anchors = reinterpret_cast<const int32_t *>(dptr(off_aent));
     b->slp.rows = reinterpret_cast<const int32_t *>(dptr(off_sent));
@@ -1827,6 +1901,7 @@ hipError_t batch_enqueue(tfstat_batch *b, hipStream_t s, bool timed) {
     if (e == hipSuccess) e = tfs::launch_abc_recur_batch(b->rap, s);
     if (e == hipSuccess && timed) e = hipEventRecord(b->evf0, s);
     if (e == hipSuccess) e = tfs::launch_fused(b->fp, b->variant, b->groups, s);
+    if (e == hipSuccess) e = tfs::launch_rect_batch(b->rbp, s);
     if (e == hipSuccess && timed) e = hipEventRecord(b->evf1, s);
     if (e == hipSuccess) e = tfs::launch_mfma_batch(b->mfp, s);
     if (e == hipSuccess && timed) e = hipEventRecord(b->evm1, s);

@@ -305,12 +305,73 @@ struct RectParams {
     int64_t t_sft;
     int32_t n_tiles_n;        // ceil(n_tau / 64)
     int32_t n_tiles;          // per bin
+    int32_t bg;               // bins per tile (1..4)
+    int32_t tile_rows;        // rows per tile, a multiple of kRectWaves
+    int32_t stage;            // slots of window ends staged in LDS (0: none)
+    int32_t pad;
     const RowPlan *rows;
     const int64_t *tau;
-    const double *pabc;       // [K+1][8] exclusive prefix: 4 hi then 4 lo terms
-    const double *px;         // [n_bins][K+1][8]: per bin, 4 hi then 4 lo terms
+    const SlideTile *tiles;   // [n_tiles_n]; q, r of tau
+    const double *pabc;       // [K+1][4][2] exclusive prefixes (hi, lo)
+    const double *px;         // [n_bins][K+1][4][2]
     float *twoF;
     Partial *part;
+};
+// len tau = q T + r (0 <= r < T); q clamped so that k0 + q + 1 stays an int and
+// still passes every data end (k0 >= -2^30, K <= 2^28).
+__device__ inline void span_qr(int64_t tau, int64_t len, int64_t T, int &q, int &r) {
+    constexpr int64_t kMaxQ = 1342177280;
+    const int64_t span = min(len * tau, kMaxQ * T);
+    // quotient below 2^31 by one FP64 division, within one of the exact one
+    int64_t qq = (int64_t)((double)span / (double)T);
+    int64_t rr = span - qq * T;
+    if (rr < 0) {
+        --qq;
+        rr += T;
+    } else if (rr >= T) {
+        ++qq;
+        rr -= T;
+    }
+    q = (int)qq;
+    r = (int)rr;
+}
+
+// A wave's (max, sum of exp(F - max), first cell of the max) from its lanes'
+// running states: each lane has tau n (lanes ok only) and found its maximum
+// first in row m.  The cell index is row-major, so the first cell is the lowest
+// lane of the lowest row.  One FP32 exponential per lane; fmax -INFINITY, s 0
+// where no lane has a maximum.
+__device__ inline Partial wave_state(double f, double s, int m, int n, bool ok, int n_tau) {
+    if (!ok) f = -INFINITY;
+    double mx = f;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
+    if (mx == -INFINITY) return Partial{mx, 0.0, INT64_MAX};
+    double sv = f == -INFINITY ? 0.0 : s * (double)__expf((float)(f - mx));
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) sv += __shfl_xor(sv, o, 64);
+    int mm = f == mx ? m : INT32_MAX;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) mm = min(mm, __shfl_xor(mm, o, 64));
+    const int first = __ffsll((unsigned long long)__ballot(f == mx && m == mm)) - 1;
+    const int nn = __builtin_amdgcn_readlane(n, first);
+    return Partial{mx, sv, (int64_t)mm * n_tau + nn};
+}
+
+// Rect tiles: waves of a workgroup; LDS for the staged window ends, a plane of
+// (hi, lo) per channel, a plane's slots padded to 4 past a multiple of 16 (the
+// four channels of a slot are written by four lanes: different banks).
+constexpr int kRectWaves = 16;
+constexpr unsigned kRectStageBytes = 150 * 1024;
+inline __host__ __device__ int rect_pitch(int stage) { return (stage + 11) / 16 * 16 + 4; }
+inline unsigned rect_stage_bytes(int bg, int stage) {
+    return stage > 0 ? 16u * (4u * bg + 3u) * (unsigned)rect_pitch(stage) : 0u;
+}
+struct RectBatchParams {
+    const RectParams *jobs;
+    const int32_t *entries;   // [n_entries][4]: job, tau tile, row tile, bin group
+    int32_t n_entries;
+    uint32_t lds_bytes;       // the largest stage
 };
 
 struct MergeParams {
@@ -346,23 +407,20 @@ inline void shape_dims(int shape, int *prec, int *R, int *BG) {
     *BG = t[shape][2];
 }
 
-constexpr int kRectRows = 64;   // rows per rect tile (x 64 taus x kRectBins bins)
-constexpr int kRectBins = 4;    // bins per rect tile
 
 struct BatchTile {
-    int32_t kind;    // 0: exponential, 1: rectangular, 2: exponential, rows far apart,
+    int32_t kind;    // 0: exponential, 2: exponential, rows far apart,
                      // 3: exponential F_a/F_b only (A, B, C from the A/B/C pre-pass;
                      //    z counts bin pairs)
-    int32_t job;     // index into FusedParams::exp_jobs or ::rect_jobs
-    int32_t x;       // exp: position in blk_list (kind 2: first of four); rect: tau tile (64 taus)
-    int32_t y;       // exp: 64-row tile; rect: kRectRows-row tile
-    int32_t z;       // exp: bin group; rect: group of kRectBins bins
-    int32_t shape;   // exp: ExpShape of the job (a four-bin map's tail: kShapeF42, kShapeF41)
+    int32_t job;     // index into FusedParams::exp_jobs
+    int32_t x;       // exp: position in blk_list (kind 2: first of four)
+    int32_t y;       // 64-row tile
+    int32_t z;       // bin group
+    int32_t shape;   // ExpShape of the job (a four-bin map's tail: kShapeF42, kShapeF41)
 };
 
 struct FusedParams {
     const ExpValuParams *exp_jobs;
-    const RectParams *rect_jobs;
     const BatchTile *tiles;   // largest expected cost first
     int32_t n_tiles;
     int32_t pad;
@@ -511,6 +569,7 @@ hipError_t launch_build_cplanes(const float *x32, int32_t K, int32_t n_bins, int
 // Prefix sums of a map's antenna and data channels.
 hipError_t launch_scan(const ScanJob &abc, const ScanJob &x, hipStream_t s);
 hipError_t launch_rect(const RectParams &p, hipStream_t s);
+hipError_t launch_rect_batch(const RectBatchParams &p, hipStream_t s);
 hipError_t launch_merge(const MergeParams &p, hipStream_t s);
 hipError_t launch_map_reduce(const MapReduceParams &p, hipStream_t s);
 hipError_t launch_abc_recur(const AbcRecurParams &p, hipStream_t s);

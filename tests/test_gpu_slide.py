@@ -88,12 +88,52 @@ def test_slide_window_ends_past_the_stage(ctx, n_bins, last_tau):
     4095 slots), and past it, where the ends come through the caches."""
     print("case: spread %d bins, tau to %d" % (n_bins, last_tau), flush=True)
     atoms = tfsynth.make_atoms(9350 + n_bins, 4600, 0.1, n_bins=n_bins)
-    win = tfsynth.list_window("exp", 3 + 5 * T * np.arange(30), np.unique(np.linspace(2, last_tau, 50).astype(np.int64) * T))
+    tau = np.unique(np.linspace(2, last_tau, 50).astype(np.int64) * T)
+    for first in (0, -1500):   # (windows longer than the data whose ends lie inside)
+        win = tfsynth.list_window("exp", 3 + first * T + 5 * T * np.arange(30), tau)
+        ref = oracle.fmap_atoms(atoms, win)
+        res, got, n = _maps(ctx, atoms, win, "fp32")
+        assert n == 1, "not by sliding windows"
+        check_map(got, ref, TOL["fp64"])
+        check_results(res, ref, win, TOL["fp64"])
+
+
+@pytest.mark.parametrize("n_bins", [1, 2, 3, 4, 5, 9])
+@pytest.mark.parametrize("grid", ["slots", "rows17", "off", "tau_wide", "tau_far", "outside", "same_slot"])
+def test_rect_tiles(ctx, n_bins, grid):
+    """Every group size; tau tiles one tau short of, at and past 64; rows one
+    short of, at and past a pass of sixteen waves and a tile; window ends at
+    and past what the LDS stage holds at 4, 2 and 1 bins (505, 863 and 1333
+    slots); windows from before the data, longer than it and empty.  A batch
+    gives the same numbers."""
+    print("case: rect %s %d bins" % (grid, n_bins), flush=True)
+    atoms = tfsynth.make_atoms(9500 + n_bins, 2300, 0.15, n_bins=n_bins,
+                               injections=[tfsynth.Injection(n_bins - 1, "rect", 300 * T, 60 * T, 1.0)])
+    if grid == "slots":
+        win = tfsynth.regular_window("rect", 0, T, 255 + n_bins % 3, T, T, 63 + n_bins % 3)
+    elif grid == "rows17":
+        win = tfsynth.regular_window("rect", 7, 3 * T, 15 + n_bins % 3, T, 5 * T + 9, 130)
+    elif grid == "off":
+        win = tfsynth.linspace_grid(atoms, "rect", 101, 65)
+    elif grid == "tau_wide":
+        win = tfsynth.regular_window("rect", 3 * T, 2 * T, 40, 2 * T, (7 + 4 * (n_bins % 4)) * T, 64)
+    elif grid == "tau_far":
+        win = tfsynth.regular_window("rect", 3, 2 * T, 33, 2 * T, 30 * T, 64)
+    elif grid == "same_slot":
+        win = tfsynth.regular_window("rect", 40 * T + 1, 111, 50, T // 2, 2 * T - 1, 70)
+    else:
+        t0 = np.concatenate([-2600 * T + 137 * T * np.arange(18), np.arange(3, 2500, 99) * T + 9])
+        win = tfsynth.list_window("rect", np.unique(t0), [1, T - 1, T, 5 * T + 3, 40 * T, 900 * T, 2000 * T, 6000 * T])
     ref = oracle.fmap_atoms(atoms, win)
-    res, got, n = _maps(ctx, atoms, win, "fp32")
-    assert n == 1, "not by sliding windows"
-    check_map(got, ref, TOL["fp64"])
-    check_results(res, ref, win, TOL["fp64"])
+    aid = ctx.upload_atoms(atoms)
+    try:
+        res, twoF = ctx.fmap(aid, win, "fp32", want_map=True)
+        check_map(twoF.cpu().numpy(), ref, TOL["fp64"])
+        check_results(res, ref, win, TOL["fp64"])
+        with ctx.batch([(aid, win), (aid, win)], "fp32") as b:
+            assert b.run() == [res, res]
+    finally:
+        ctx.free(aid)
 
 
 @pytest.mark.parametrize("slots", [1, 2, 31, 32, 33, 255, 256, 257, 513])
