@@ -339,15 +339,17 @@ __device__ inline void span_qr(int64_t tau, int64_t len, int64_t T, int &q, int 
 // A wave's (max, sum of exp(F - max), first cell of the max) from its lanes'
 // running states: each lane has tau n (lanes ok only) and found its maximum
 // first in row m.  The cell index is row-major, so the first cell is the lowest
-// lane of the lowest row.  One FP32 exponential per lane; fmax -INFINITY, s 0
-// where no lane has a maximum.
+// lane of the lowest row.  One exponential per lane (FP32 argument unless
+// EXACT); fmax -INFINITY, s 0 where no lane has a maximum.
+template <bool EXACT = false>
 __device__ inline Partial wave_state(double f, double s, int m, int n, bool ok, int n_tau) {
     if (!ok) f = -INFINITY;
     double mx = f;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
     if (mx == -INFINITY) return Partial{mx, 0.0, INT64_MAX};
-    double sv = f == -INFINITY ? 0.0 : s * (double)__expf((float)(f - mx));
+    const double e = EXACT ? exp(f - mx) : (double)__expf((float)(f - mx));
+    double sv = f == -INFINITY ? 0.0 : s * e;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) sv += __shfl_xor(sv, o, 64);
     int mm = f == mx ? m : INT32_MAX;

@@ -236,3 +236,28 @@ def test_slide_in_a_short_arena():
         _, m = small.fmap(aid, exp, "fp32", want_map=True)
         check_map(m.cpu().numpy(), ref, TOL["fp32"])
         assert small.fmap(aid, rect, "fp64")[0] == want_rect
+
+
+@pytest.mark.parametrize("cells", [1, 63, 255, 257, 2047, 2048, 2049, 16383, 16385, 18433])
+@pytest.mark.parametrize("kind", ["chi2", "wide", "equal", "inf"])
+def test_map_reduction_edges(ctx, cells, kind):
+    """logB of a stored map at the edges of a thread's chunk (8 cells 256
+    apart) and of a tile (16384 cells); values up to 2000 apart, where a power
+    underflows, and -inf.  logB is a sum of at most 18433 exponentials, each to
+    a few 2^-53, so 1e-12 holds whatever their order."""
+    import torch
+    print("case: map %s %d cells" % (kind, cells), flush=True)
+    rng = np.random.default_rng(cells)
+    maps = rng.chisquare(4, size=(2, 1, cells)).astype(np.float32)
+    if kind == "wide":
+        maps *= rng.choice(np.float32([0.0, 1.0, 200.0]), size=maps.shape)
+    elif kind == "equal":
+        maps[:] = maps[:, :, :1]
+    elif kind == "inf" and cells > 1:
+        maps[:, :, ::3] = -np.inf
+        maps[:, :, -1] = 30.0
+    got = ctx.logB(torch.from_numpy(maps).to("cuda:0"))
+    F = maps.reshape(2, -1).astype(np.float64) / 2
+    mx = F.max(axis=1)
+    want = mx + np.log(np.exp(F - mx[:, None]).sum(axis=1)) - np.log(cells)
+    assert np.allclose(got, want, atol=1e-12, rtol=1e-14)
