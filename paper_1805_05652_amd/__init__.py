@@ -12,6 +12,7 @@ kernels; appendix A footnote: the marginalised Bayes factor).
 from __future__ import annotations
 
 import ctypes
+import struct
 from typing import List, Optional
 
 import numpy as np
@@ -65,9 +66,15 @@ class _WindowArgs:
                    getattr(win, "support", (1, 1)))
 
 
+_RESULT = struct.Struct("=ddqqii")   # the fields of _abi.BinResult
+assert _RESULT.size == ctypes.sizeof(_abi.BinResult)
+
+
 def _results(arr) -> List[dict]:
-    return [dict(max2F=r.max2F, logB=r.logB, t0=int(r.t0), tau=int(r.tau), m=int(r.m), n=int(r.n))
-            for r in arr]
+    # (one unpack a bin: reading the structures' attributes took 45 us more of
+    # a 256-bin call: 303 -> 258 us with a rect map of 500 x 500)
+    return [{"max2F": f, "logB": b, "t0": t0, "tau": tau, "m": m, "n": n}
+            for f, b, t0, tau, m, n in _RESULT.iter_unpack(arr)]
 
 
 class Context:
@@ -287,9 +294,9 @@ class Batch:
         kernel when timed); per map, the list of its per-bin result dicts."""
         res = (_abi.BinResult * sum(self._bins))()
         _abi.check(self._lib.tfstat_batch_run(self._ctx._ctx, self._h, 1 if timed else 0, res))
-        out, o = [], 0
+        rows, out, o = _results(res), [], 0
         for nb in self._bins:
-            out.append(_results(res[o:o + nb]))
+            out.append(rows[o:o + nb])
             o += nb
         return out
 
