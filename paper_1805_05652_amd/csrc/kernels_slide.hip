@@ -650,18 +650,21 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, double *
 
 // ---------------------------------------------------------------------------
 // Once per upload: the FP32 plane, and what the sums ask of the atoms.
-// Workgroup = 64 columns (4 per bin; the last one: the antenna's 4); a lane
+// Workgroup = 16 columns (4 per bin; the last one: the antenna's 4); a lane
 // takes stretches of 64 slots of one column, as many lanes per column as fit.
+// Bound by a stretch's loads in turn, so the stretches are spread (16 columns
+// against 64: 47 against 70 us an upload of up to 8000 slots and 16 bins).
 // ---------------------------------------------------------------------------
 constexpr int kRangeWaves = 16;
+constexpr int kRangeCols = 16;
 __global__ __launch_bounds__(64 * kRangeWaves) void atoms_kernel(const double *x64, const double *abc, float *x32,
                                                                  int32_t K, int32_t n_bins, RangeInfo *info) {
     __shared__ double smax[kRangeWaves][64], smin[kRangeWaves][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bool ant = blockIdx.x == gridDim.x - 1;
     const int C = ant ? 4 : 4 * n_bins;
-    const int c0 = ant ? 0 : blockIdx.x * 64;
-    const int n_c = min(C - c0, 64);          // columns of this workgroup
+    const int c0 = ant ? 0 : blockIdx.x * kRangeCols;
+    const int n_c = min(C - c0, kRangeCols);          // columns of this workgroup
     const int subs = 64 / n_c;                // lanes per column
     const int c = c0 + lane % n_c;
     const int sub = lane / n_c;
@@ -672,7 +675,7 @@ __global__ __launch_bounds__(64 * kRangeWaves) void atoms_kernel(const double *x
         for (int k0 = (wave * subs + sub) * 64; k0 < K; k0 += kRangeWaves * subs * 64) {
             double b = 0.0;
             const int k1 = min(k0 + 64, K);
-#pragma unroll 8
+#pragma unroll 16
             for (int k = k0; k < k1; ++k) {
                 const double v = in[(size_t)k * C + c];
                 const float f = (float)v;
@@ -777,7 +780,7 @@ hipError_t launch_slide_batch(const SlideBatchParams &p, hipStream_t s) {
 
 hipError_t launch_atoms(const double *x64, const double *abc, float *x32, int32_t K, int32_t n_bins, RangeInfo *info,
                         hipStream_t s) {
-    const unsigned g = (unsigned)((4 * (int64_t)n_bins + 63) / 64) + 1u;
+    const unsigned g = (unsigned)((4 * (int64_t)n_bins + kRangeCols - 1) / kRangeCols) + 1u;
     hipLaunchKernelGGL(atoms_kernel, dim3(g), dim3(64 * kRangeWaves), 0, s, x64, abc, x32, K, n_bins, info);
     return hipGetLastError();
 }
