@@ -77,8 +77,7 @@ __device__ inline void red_add(Red &r, double F, long long idx) {
 
 // Wave reduction: the maximum and its first index by butterfly, then every
 // lane's sum rescaled to that maximum (one exponential per lane; FP32
-// argument unless EXACT) and added by butterfly; lane 0's result is used.
-template <bool EXACT = false>
+// argument) and added by butterfly; lane 0's result is used.
 __device__ inline Red red_wave(Red v) {
     double fm = v.f;
     long long im = v.i;
@@ -92,8 +91,7 @@ __device__ inline Red red_wave(Red v) {
         }
     }
     if (fm == -INFINITY) return red_empty();
-    const double e = EXACT ? exp(v.f - fm) : (double)__expf((float)(v.f - fm));
-    double sv = (v.f == -INFINITY) ? 0.0 : v.s * e;
+    double sv = (v.f == -INFINITY) ? 0.0 : v.s * (double)__expf((float)(v.f - fm));
 #pragma unroll
     for (int o = 1; o < kLanes; o <<= 1) sv += __shfl_xor(sv, o, kLanes);
     return Red{fm, sv, im};
