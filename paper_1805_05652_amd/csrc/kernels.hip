@@ -1626,7 +1626,7 @@ __global__ __launch_bounds__(kMapThreads) void map_reduce_kernel(MapReduceParams
         const bool whole = c + kMapThreads * (kMapChunk - 1) < c1 && f - 0.5 * (double)lo < 700.0 && sum == sum;
         if (whole) {
             if (f > r.f) {
-                r.s *= exp(r.f - f);   // (r.f = -inf: s = 0)
+                r.s = r.f == -INFINITY ? 0.0 : r.s * exp(r.f - f);
                 r.f = f;
 #pragma unroll
                 for (int u = kMapChunk - 1; u >= 0; --u)
@@ -1641,7 +1641,7 @@ __global__ __launch_bounds__(kMapThreads) void map_reduce_kernel(MapReduceParams
                     r.s = (r.f == -INFINITY) ? 1.0 : r.s * exp(r.f - F) + 1.0;
                     r.f = F;
                     r.i = c + kMapThreads * u;
-                } else {
+                } else if (r.f > -INFINITY) {   // (nothing but -inf so far: no sum yet)
                     r.s += exp(F - r.f);
                 }
             }
