@@ -1739,8 +1739,8 @@ hipError_t launch_weights(const WeightParams &p, int64_t max_per_block, hipStrea
 hipError_t launch_scan(const ScanJob &abc, const ScanJob &x, hipStream_t s) {
     const unsigned chunks = 1u + (unsigned)((x.C + 63) / 64);
     const unsigned blocks = (unsigned)((x.K + kScanBlock - 1) / kScanBlock);
-    if (blocks > 65535u) return hipErrorInvalidValue;
     const bool split = blocks > 1 && x.tot != nullptr;
+    if (split && blocks > 65535u) return hipErrorInvalidValue;
     if (split)
         hipLaunchKernelGGL(scan_kernel, dim3(chunks, blocks - 1), dim3(kScanWaves * 64), 0, s, abc, x, 1);
     hipLaunchKernelGGL(scan_kernel, dim3(chunks, split ? blocks : 1u), dim3(kScanWaves * 64), 0, s, abc, x, 0);
