@@ -279,6 +279,8 @@ constexpr int32_t kSplitMinBins = 8;
 constexpr int64_t kCus = 256;
 constexpr int64_t kSlideMost = 16384;
 constexpr int64_t kSlideRanges = 1536;
+// Blocks of 256 slots that a rect map's prefix sums are split into at most.
+constexpr int64_t kScanMostBlocks = 6144;
 
 // ---------------------------------------------------------------------------
 // One map computation: plan (host, integer), workspace, launches, results.
@@ -730,9 +732,12 @@ void plan_job(Job &j) {
     } else {
         j.off_pabc = take(sizeof(double) * 8 * ((size_t)at.K + 1));
         j.off_px = take(sizeof(double) * 8 * (size_t)at.n_bins * ((size_t)at.K + 1));
-        // block totals of the prefix sums (one set per 64 channels)
+        // block totals of the prefix sums (one set per 64 channels); every
+        // block adds those before it, so their time grows with the square of
+        // the blocks (one bin: 1.5 M slots 28 ms, 4 M 246, 8 M 1002; without
+        // totals 39 ms at 1.6 M slots, 98 and 197)
         const int64_t n_blk = (at.K + tfs::kScanBlock - 1) / tfs::kScanBlock;
-        j.scan_blk = n_blk > 1 && n_blk <= 65535 && !j.small_ws ? (int32_t)n_blk : 0;
+        j.scan_blk = n_blk > 1 && n_blk <= kScanMostBlocks && !j.small_ws ? (int32_t)n_blk : 0;
         j.off_ptot = take(sizeof(double2) * 64 * (size_t)j.scan_blk * (1 + (4 * (size_t)at.n_bins + 63) / 64));
     }
     j.off_part = take(sizeof(tfs::Partial) * (size_t)j.n_tiles * at.n_bins);

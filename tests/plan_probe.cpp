@@ -1,0 +1,40 @@
+// Prints the plans of maps (the runtime's plan_job, host code only): one map
+// per input line, one line of "name=value" fields per map.
+//   kind precision K bins t_sft exact32 n_t0 t0... n_tau tau...
+// kind: 0 rect, 1 exp; precision: tfstat_precision; t0 relative to the data's start.
+#include "../paper_1805_05652_amd/csrc/runtime.cpp"
+
+#include <iostream>
+
+int main() {
+    int kind, prec, exact32;
+    int64_t K, bins, T;
+    while (std::cin >> kind >> prec >> K >> bins >> T >> exact32) {
+        AtomsSet at;
+        at.K = (int32_t)K;
+        at.n_bins = (int32_t)bins;
+        at.t_sft = T;
+        at.slide_ok = (K + 1) * bins * 32 < ((int64_t)1 << 31);
+        at.exact32 = exact32 != 0;
+        at.amax = at.bmax = 1.0;
+        Job j;
+        j.at = &at;
+        j.prec = prec;
+        j.win.type = kind == 0 ? TFSTAT_WIN_RECT : TFSTAT_WIN_EXP;
+        int64_t n = 0;
+        std::cin >> n;
+        j.win.t0.resize(n);
+        for (auto &v : j.win.t0) std::cin >> v;
+        std::cin >> n;
+        j.win.tau.resize(n);
+        for (auto &v : j.win.tau) std::cin >> v;
+        j.runs_min_spread = kRunsAuto;
+        j.split_min_bins = kSplitMinBins;
+        plan_job(j);
+        std::cout << "slide=" << j.slide << " bg=" << j.bg << " n_bg=" << j.n_bg << " n_tt=" << j.n_tt << " n_seg=" << j.n_seg
+                  << " seg_rows=" << j.seg_rows << " range_len=" << j.range_len << " n_range=" << j.n_range << " n_sup=" << j.n_sup
+                  << " kbeg=" << j.kbeg << " waves=" << j.waves << " stage=" << j.stage << " rect_rows=" << j.rect_rows
+                  << " scan_blk=" << j.scan_blk << " ws=" << j.ws_bytes << std::endl;
+    }
+    return 0;
+}
