@@ -443,6 +443,8 @@ void plan_slide(Job &j) {
     auto columns = [&](int bg) { return (int64_t)j.n_tt * ((at.n_bins + bg - 1) / bg); };
     // anchor ranges: long where the columns alone fill the chip
     while (rl > 16 && columns(bg_full) * (at.K / rl) < kSlideRanges) rl /= 2;
+    // (super-ranges are a grid's second dimension)
+    while ((int64_t)rl * tfs::kSlideWaves * 65535 < at.K) rl *= 2;
     // Bins per group, segments and segments per workgroup by an estimate of
     // the rows kernel's time in VALU instructions: a cell's, a front and a back
     // slot's (counted in its loop), a segment's start (latencies, half a range
@@ -503,7 +505,7 @@ void plan_slide(Job &j) {
     const tfs::RowPlan &last = j.rows[n_t0 - 1];
     for (tfs::SlideTile &t : j.tiles)
         t.kend = std::max(std::min(std::max(last.k0 + t.q1 + (t.r1 > last.delta ? 1 : 0), 0), at.K), j.kbeg);
-    j.n_sup = std::max<int32_t>(1, (at.K + rl * tfs::kSlideWaves - 1) / (rl * tfs::kSlideWaves));
+    j.n_sup = (int32_t)std::max<int64_t>(1, ((int64_t)at.K + rl * tfs::kSlideWaves - 1) / (rl * tfs::kSlideWaves));
     j.n_range = j.n_sup * tfs::kSlideWaves;
 }
 

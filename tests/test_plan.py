@@ -86,3 +86,16 @@ def test_rect_block_totals(probe, K, split):
     p = probe("rect", "fp32", K, 1, [0, 5 * T], [2 * T, 9 * T])
     assert (p["scan_blk"] > 0) == split
     assert p["scan_blk"] in (0, -(-K // 256))
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64", "recur64", "f16x3"])
+@pytest.mark.parametrize("K,bins", [(65535 * 512, 1), (65535 * 512 + 1, 1), ((1 << 26) - 2, 1), ((1 << 25) - 2, 2),
+                                    (1 << 24, 3), (5000, 1), (1, 1)])
+def test_slide_launch_limits(probe, prec, K, bins):
+    """Anchors of data as long as the sliding sums take (2 GiB of atoms): no
+    more super-ranges than a grid's second dimension has blocks, and they
+    cover the data."""
+    t0 = [0, max(1, K // 2) * T, (K + 5) * T]
+    p = probe("exp", prec, K, bins, t0, [T, K * T // 4 + 1, K * T])
+    assert p["slide"] and p["range_len"] % 16 == 0 and p["n_sup"] <= 65535
+    assert p["range_len"] * 8 * p["n_sup"] >= K and p["n_range"] == 8 * p["n_sup"]
