@@ -1769,8 +1769,12 @@ hipError_t launch_rect(const RectParams &p, hipStream_t s) {
 }
 
 hipError_t launch_rect_batch(const RectBatchParams &p, hipStream_t s) {
-    if (p.n_entries <= 0) return hipSuccess;
-    hipLaunchKernelGGL(rect_batch_kernel, dim3((unsigned)p.n_entries), dim3(64 * kRectWaves), p.lds_bytes, s, p);
+    for (int32_t i = 0; i < p.n_entries; i += kLaunchMost) {
+        RectBatchParams q = p;
+        q.entries += 4 * (size_t)i;
+        q.n_entries = std::min(p.n_entries - i, kLaunchMost);
+        hipLaunchKernelGGL(rect_batch_kernel, dim3((unsigned)q.n_entries), dim3(64 * kRectWaves), q.lds_bytes, s, q);
+    }
     return hipGetLastError();
 }
 

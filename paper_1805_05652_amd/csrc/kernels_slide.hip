@@ -33,6 +33,8 @@
 
 #include <hip/hip_runtime.h>
 #include <math.h>
+
+#include <algorithm>
 #include <stdint.h>
 
 namespace tfs {
@@ -771,10 +773,22 @@ __global__ __launch_bounds__(64 * kRowsWaves) void slide_rows_batch_kernel(Slide
 }  // namespace
 
 hipError_t launch_slide_batch(const SlideBatchParams &p, hipStream_t s) {
-    if (p.n_rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(slide_anchor_batch_kernel, dim3((unsigned)p.n_anchors), dim3(64 * kSlideWaves), 0, s, p);
-    hipLaunchKernelGGL(slide_supers_batch_kernel, dim3((unsigned)p.n_anchors), dim3(256), 0, s, p);
-    hipLaunchKernelGGL(slide_rows_batch_kernel, dim3((unsigned)p.n_rows), dim3(64 * kRowsWaves), p.lds_bytes, s, p);
+    SlideBatchParams q = p;
+    for (int32_t i = 0; i < p.n_anchors; i += kLaunchMost) {
+        q.anchors = p.anchors + 4 * (size_t)i;
+        q.n_anchors = std::min(p.n_anchors - i, kLaunchMost);
+        hipLaunchKernelGGL(slide_anchor_batch_kernel, dim3((unsigned)q.n_anchors), dim3(64 * kSlideWaves), 0, s, q);
+    }
+    for (int32_t i = 0; i < p.n_anchors; i += kLaunchMost) {
+        q.anchors = p.anchors + 4 * (size_t)i;
+        q.n_anchors = std::min(p.n_anchors - i, kLaunchMost);
+        hipLaunchKernelGGL(slide_supers_batch_kernel, dim3((unsigned)q.n_anchors), dim3(256), 0, s, q);
+    }
+    for (int32_t i = 0; i < p.n_rows; i += kLaunchMost) {
+        q.rows = p.rows + 4 * (size_t)i;
+        q.n_rows = std::min(p.n_rows - i, kLaunchMost);
+        hipLaunchKernelGGL(slide_rows_batch_kernel, dim3((unsigned)q.n_rows), dim3(64 * kRowsWaves), q.lds_bytes, s, q);
+    }
     return hipGetLastError();
 }
 

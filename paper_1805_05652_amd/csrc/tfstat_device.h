@@ -369,6 +369,9 @@ inline __host__ __device__ int rect_pitch(int stage) { return (stage + 11) / 16 
 inline unsigned rect_stage_bytes(int bg, int stage) {
     return stage > 0 ? 16u * (4u * bg + 3u) * (unsigned)rect_pitch(stage) : 0u;
 }
+// Workgroups of one launch over a list of entries: a grid has less than 2^32
+// threads, 4.2 million workgroups of sixteen waves.
+constexpr int32_t kLaunchMost = 1 << 21;
 struct RectBatchParams {
     const RectParams *jobs;
     const int32_t *entries;   // [n_entries][4]: job, tau tile, row tile, bin group

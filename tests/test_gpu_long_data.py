@@ -51,3 +51,20 @@ def test_rect_over_more_slots_than_a_grid_has_blocks(ctx):
         ctx.free(aid)
     check_map(twoF.cpu().numpy(), ref, TOL["fp64"])
     check_results(res, ref, win, TOL["fp64"])
+
+
+def test_rect_batch_of_more_tiles_than_a_launch_takes(ctx):
+    """A batch whose map has 4.2 million tiles, past the threads of one
+    launch; the same map alone gives the same numbers."""
+    print("case: rect batch, 4.2 million tiles", flush=True)
+    atoms = tfsynth.make_atoms(5, 6000, 0.1, n_bins=1)
+    # taus 90 slots apart: the window ends of one tile exceed the stage, 64 rows a tile
+    win = tfsynth.regular_window("rect", 0, 7, 40001, T, 90 * T, 430000)
+    aid = ctx.upload_atoms(atoms)
+    try:
+        alone, _ = ctx.fmap(aid, win, "fp32")
+        with ctx.batch([(aid, win)], "fp32") as b:
+            assert b.stats()["n_tiles"] > 1 << 22
+            assert b.run() == [alone]
+    finally:
+        ctx.free(aid)
