@@ -651,64 +651,124 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, double *
 }
 
 // ---------------------------------------------------------------------------
-// Once per upload: the FP32 plane, and what the sums ask of the atoms.
-// Workgroup = 16 columns (4 per bin; the last one: the antenna's 4); a lane
-// takes stretches of 64 slots of one column, as many lanes per column as fit.
-// Bound by a stretch's loads in turn, so the stretches are spread (16 columns
-// against 64: 47 against 70 us an upload of up to 8000 slots and 16 bins).
+// Once per upload: the FP32 plane, and the ranges of the atoms' values.
+// Workgroup = up to kAtomBins bins (the last group: the antenna) x a chunk of
+// 64-slot stretches.  Eight lanes share a (stretch, bin), every eighth slot
+// each, so that a stretch is one round of loads in flight (bound by that
+// latency, and by the copies around it) and lanes next to each other read slots
+// or bins next to each other.  The findings go straight to pinned host memory,
+// a record per workgroup, which the host combines: a copy back costs more than
+// the kernel (an upload of one bin x 200 slots: 52 us with one workgroup per 16
+// columns and a copy, 26 us now, 24 us without the ranges; 16 bins x 8000 slots:
+// the kernel 47 and 13 us).
 // ---------------------------------------------------------------------------
-constexpr int kRangeWaves = 16;
-constexpr int kRangeCols = 16;
-__global__ __launch_bounds__(64 * kRangeWaves) void atoms_kernel(const double *x64, const double *abc, float *x32,
-                                                                 int32_t K, int32_t n_bins, RangeInfo *info) {
-    __shared__ double smax[kRangeWaves][64], smin[kRangeWaves][64];
+// v over the n (a power of two) lanes that lie `stride` apart around this one,
+// `at` its place among them.
+template <typename Op>
+__device__ __attribute__((always_inline)) inline double ring(double v, int lane, int stride, int at, int n, Op op) {
+    const int first = lane - at * stride;
+    for (int o = n / 2; o > 0; o >>= 1) v = op(v, __shfl(v, first + ((at + o) & (n - 1)) * stride, 64));
+    return v;
+}
+
+__global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x64, const double *abc, float *x32,
+                                                               int32_t K, int32_t n_bins, RangeInfo *out) {
+    constexpr int kSlots = 64 / kAtomLanes;              // slots of a lane
+    __shared__ double smax[kAtomWaves][4][kAtomBins], smin[kAtomWaves][4][kAtomBins];
+    __shared__ int sflags;
+    auto larger = [](double x, double y) { return fmax(x, y); };
+    auto smaller = [](double x, double y) { return fmin(x, y); };
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bool ant = blockIdx.x == gridDim.x - 1;
-    const int C = ant ? 4 : 4 * n_bins;
-    const int c0 = ant ? 0 : blockIdx.x * kRangeCols;
-    const int n_c = min(C - c0, kRangeCols);          // columns of this workgroup
-    const int subs = 64 / n_c;                // lanes per column
-    const int c = c0 + lane % n_c;
-    const int sub = lane / n_c;
-    const double *in = ant ? abc : x64;
-    double mx = 0.0, mn = INFINITY;
-    bool bad = false, inexact = false;
-    if (sub < subs) {
-        for (int k0 = (wave * subs + sub) * 64; k0 < K; k0 += kRangeWaves * subs * 64) {
-            double b = 0.0;
-            const int k1 = min(k0 + 64, K);
-#pragma unroll 16
-            for (int k = k0; k < k1; ++k) {
-                const double v = in[(size_t)k * C + c];
-                const float f = (float)v;
-                if (!ant) x32[(size_t)k * C + c] = f;
-                bad |= !(fabs(v) < INFINITY);
-                inexact |= (double)f != v;
-                b = fmax(b, fabs(v));
-            }
-            mx = fmax(mx, b);
-            if (b > 0.0) mn = fmin(mn, b);
-        }
-        if (!ant && wave == 0 && sub == 0) x32[(size_t)K * C + c] = 0.f;   // row K is zero
-    }
-    smax[wave][lane] = mx;
-    smin[wave][lane] = mn;
+    const int b0 = ant ? 0 : blockIdx.x * kAtomBins;
+    const int row = ant ? 1 : n_bins;                    // groups of four values per slot
+    const int W = min(row - b0, kAtomBins);              // bins of this workgroup
+    const int subs = W == 1 ? 8 : W == 2 ? 4 : W <= 4 ? 2 : 1;   // stretches of a wave
+    const int t = lane / W;
+    const int b = lane - t * W, s8 = t % kAtomLanes, sub = t / kAtomLanes;
+    const double *in = (ant ? abc : x64) + 4 * b0;
+    if (threadIdx.x == 0) sflags = 0;
     __syncthreads();
-    if (wave == 0 && lane < n_c) {
-        for (int w = 0; w < kRangeWaves; ++w)
-            for (int l = lane; l < subs * n_c; l += n_c) {
-                mx = fmax(mx, smax[w][l]);
-                mn = fmin(mn, smin[w][l]);
+    double mx[4], mn[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        mx[c] = 0.0;
+        mn[c] = INFINITY;
+    }
+    bool bad = false, inexact = false;
+    for (int k0 = (blockIdx.y * kAtomWaves + wave) * subs * 64; k0 < K; k0 += gridDim.y * kAtomWaves * subs * 64) {
+        const int kb = k0 + sub * 64 + s8;
+        double v[kSlots][4];
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i) {
+            const int k = kb + i * kAtomLanes;
+            const bool on = sub < subs && k < K;
+            const double *x = in + ((size_t)(on ? k : 0) * row + b) * 4;
+            const double2 u0 = *reinterpret_cast<const double2 *>(x);
+            const double2 u1 = *reinterpret_cast<const double2 *>(x + 2);
+            v[i][0] = on ? u0.x : 0.0;
+            v[i][1] = on ? u0.y : 0.0;
+            v[i][2] = on ? u1.x : 0.0;
+            v[i][3] = on ? u1.y : 0.0;
+        }
+        double m[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i) {
+            const int k = kb + i * kAtomLanes;
+            float4 f;
+            f.x = (float)v[i][0];
+            f.y = (float)v[i][1];
+            f.z = (float)v[i][2];
+            f.w = (float)v[i][3];
+            if (!ant && sub < subs && k < K)
+                *reinterpret_cast<float4 *>(x32 + ((size_t)k * n_bins + b0 + b) * 4) = f;
+            inexact |= f.x != v[i][0] || f.y != v[i][1] || f.z != v[i][2] || f.w != v[i][3];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                bad |= !(fabs(v[i][c]) < INFINITY);
+                m[c] = fmax(m[c], fabs(v[i][c]));
             }
-        if (ant) {
-            if (lane == 0) info->amax = (unsigned long long)__double_as_longlong(mx);
-            if (lane == 1) info->bmax = (unsigned long long)__double_as_longlong(mx);
-        } else {
-            bad |= mn < mx * 0x1p-20;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            m[c] = ring(m[c], lane, W, s8, kAtomLanes, larger);   // the stretch's
+            mx[c] = fmax(mx[c], m[c]);
+            if (m[c] > 0.0) mn[c] = fmin(mn[c], m[c]);
         }
     }
-    if (bad) atomicOr(&info->wide, 1);
-    if (inexact && !ant) atomicOr(&info->inexact32, 1);
+    if (!ant && blockIdx.y == 0 && threadIdx.x < W) {   // row K is zero
+        const float4 z = {0.f, 0.f, 0.f, 0.f};
+        *reinterpret_cast<float4 *>(x32 + ((size_t)K * n_bins + b0 + threadIdx.x) * 4) = z;
+    }
+    const int flags = (__any(bad) ? 1 : 0) | (__any(inexact) ? 2 : 0);
+    if (lane == 0 && flags) atomicOr(&sflags, flags);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        mx[c] = ring(mx[c], lane, kAtomLanes * W, sub, subs, larger);
+        mn[c] = ring(mn[c], lane, kAtomLanes * W, sub, subs, smaller);
+        if (lane < W) {
+            smax[wave][c][lane] = mx[c];
+            smin[wave][c][lane] = mn[c];
+        }
+    }
+    __syncthreads();
+    // the waves': sixteen lanes a (bin, column)
+    RangeInfo &r = out[blockIdx.y * gridDim.x + blockIdx.x];
+    if (threadIdx.x == 0) r.flags = sflags;
+    const int e = threadIdx.x / kAtomWaves, w = threadIdx.x % kAtomWaves;
+    const int eb = e >> 2, ec = e & 3;
+    if (eb < W) {   // (whole groups of sixteen lanes)
+        double x = smax[w][ec][eb], n = smin[w][ec][eb];
+#pragma unroll
+        for (int o = 1; o < kAtomWaves; o <<= 1) {
+            x = fmax(x, __shfl_xor(x, o, kAtomWaves));
+            n = fmin(n, __shfl_xor(n, o, kAtomWaves));
+        }
+        if (w == 0) {
+            r.most[eb][ec] = x;
+            r.least[eb][ec] = n;
+        }
+    }
 }
 
 template <int BG>
@@ -792,10 +852,11 @@ hipError_t launch_slide_batch(const SlideBatchParams &p, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_atoms(const double *x64, const double *abc, float *x32, int32_t K, int32_t n_bins, RangeInfo *info,
+hipError_t launch_atoms(const double *x64, const double *abc, float *x32, int32_t K, int32_t n_bins, RangeInfo *out,
                         hipStream_t s) {
-    const unsigned g = (unsigned)((4 * (int64_t)n_bins + kRangeCols - 1) / kRangeCols) + 1u;
-    hipLaunchKernelGGL(atoms_kernel, dim3(g), dim3(64 * kRangeWaves), 0, s, x64, abc, x32, K, n_bins, info);
+    static_assert(4 * kAtomBins * kAtomWaves <= 64 * kAtomWaves, "a lane for every (bin, column, wave)");
+    hipLaunchKernelGGL(atoms_kernel, dim3((unsigned)atom_groups(n_bins), (unsigned)atom_chunks(K, n_bins)),
+                       dim3(64 * kAtomWaves), 0, s, x64, abc, x32, K, n_bins, out);
     return hipGetLastError();
 }
 

@@ -1365,6 +1365,42 @@ void ensure_planes(tfstat_ctx *ctx, AtomsSet *at, int32_t prec) {
     at->bytes += 2 * plane_b + exp_b + 2 * cplane_b;
 }
 
+// Whether sliding sums apply to atoms of these ranges, and what they need of them.
+void set_ranges(AtomsSet &at, const tfs::RangeInfo *info) {
+    const int groups = tfs::atom_groups(at.n_bins), chunks = tfs::atom_chunks(at.K, at.n_bins);
+    at.slide_ok = ((int64_t)at.K + 1) * at.n_bins * 32 < ((int64_t)1 << 31);
+    at.exact32 = true;
+    for (int g = 0; g < groups; ++g) {
+        const bool ant = g == groups - 1;
+        const int nb = ant ? 1 : std::min(at.n_bins - g * tfs::kAtomBins, tfs::kAtomBins);
+        double most[tfs::kAtomBins][4] = {}, least[tfs::kAtomBins][4];
+        for (auto &l : least)
+            for (double &v : l) v = INFINITY;
+        for (int k = 0; k < chunks; ++k) {
+            const tfs::RangeInfo &r = info[k * groups + g];
+            at.slide_ok = at.slide_ok && !(r.flags & 1);
+            at.exact32 = at.exact32 && (ant || !(r.flags & 2));
+            for (int b = 0; b < nb; ++b)
+                for (int c = 0; c < 4; ++c) {
+                    most[b][c] = std::max(most[b][c], r.most[b][c]);
+                    least[b][c] = std::min(least[b][c], r.least[b][c]);
+                }
+        }
+        if (ant) {
+            at.amax = most[0][0];
+            at.bmax = most[0][1];
+            // (products of two antenna sums and their inverses stay normal)
+            for (double v : {at.amax, at.bmax})
+                if (v != 0.0 && !(v > 0x1p-200 && v < 0x1p+200)) at.slide_ok = false;
+        } else {
+            // a 64-slot stretch of a column far below the column's largest value
+            for (int b = 0; b < nb; ++b)
+                for (int c = 0; c < 4; ++c)
+                    if (least[b][c] < most[b][c] * 0x1p-20) at.slide_ok = false;
+        }
+    }
+}
+
 AtomsSet *find_atoms(tfstat_ctx *ctx, tfstat_atoms_id id) {
     auto it = ctx->atoms.find(id);
     if (it == ctx->atoms.end()) raise(TFSTAT_E_NOTFOUND, "unknown atoms id");
@@ -2282,7 +2318,7 @@ int tfstat_atoms_upload(tfstat_ctx *ctx, const tfstat_atoms_desc *d, tfstat_atom
         const size_t abc_b = round_up(sizeof(double) * 4 * rows, 256);
         const size_t x64_b = round_up(sizeof(double) * 4 * nb * rows, 256);
         const size_t x32_b = round_up(sizeof(float) * 4 * nb * rows, 256);
-        const size_t ri_b = 256;   // RangeInfo
+        const size_t ri_b = sizeof(tfs::RangeInfo) * tfs::atom_groups(nb) * tfs::atom_chunks(K, nb);
         auto set = std::make_unique<AtomsSet>();
         set->K = K;
         set->n_bins = nb;
@@ -2291,19 +2327,18 @@ int tfstat_atoms_upload(tfstat_ctx *ctx, const tfstat_atoms_desc *d, tfstat_atom
         set->t_sft = T;
         {
             std::lock_guard<std::mutex> g(ctx->mu);
-            set->mem = ctx->arena.alloc(abc_b + x64_b + x32_b + ri_b);
+            set->mem = ctx->arena.alloc(abc_b + x64_b + x32_b);
         }
         if (!set->mem) raise(TFSTAT_E_NOMEM, "arena cannot hold the atoms");
-        set->bytes = abc_b + x64_b + x32_b + ri_b;
+        set->bytes = abc_b + x64_b + x32_b;
         char *base = static_cast<char *>(set->mem);
         set->abc = reinterpret_cast<double *>(base);
         set->x64 = reinterpret_cast<double *>(base + abc_b);
-        auto *info = reinterpret_cast<tfs::RangeInfo *>(base + abc_b + x64_b);   // uploaded as zeros
-        set->x32 = reinterpret_cast<float *>(base + abc_b + x64_b + ri_b);
+        set->x32 = reinterpret_cast<float *>(base + abc_b + x64_b);
         size_t pin_bytes = 0;
         void *pin = ctx->pinned.get(abc_b + x64_b + ri_b, &pin_bytes);
         try {
-            std::memset(pin, 0, abc_b + x64_b + ri_b);
+            std::memset(pin, 0, abc_b + x64_b);
             double *habc = static_cast<double *>(pin);
             double *hx = reinterpret_cast<double *>(static_cast<char *>(pin) + abc_b);
             for (int32_t i = 0; i < d->n_sft; ++i) {
@@ -2322,23 +2357,16 @@ int tfstat_atoms_upload(tfstat_ctx *ctx, const tfstat_atoms_desc *d, tfstat_atom
                 }
             }
             hip_check(hipSetDevice(ctx->device), "hipSetDevice");
-            auto *hinfo = reinterpret_cast<tfs::RangeInfo *>(static_cast<char *>(pin) + abc_b + x64_b);
-            hip_check(hipMemcpyAsync(set->mem, pin, abc_b + x64_b + ri_b, hipMemcpyHostToDevice, ctx->stream),
+            auto *info = reinterpret_cast<tfs::RangeInfo *>(static_cast<char *>(pin) + abc_b + x64_b);
+            hip_check(hipMemcpyAsync(set->mem, pin, abc_b + x64_b, hipMemcpyHostToDevice, ctx->stream),
                       "upload atoms");
             Job dummy;
             record_kernel(ctx, dummy, TFSTAT_K_UPLOAD, ctx->stream, true);
             hip_check(tfs::launch_atoms(set->x64, set->abc, set->x32, K, nb, info, ctx->stream), "atoms kernel");
             record_kernel(ctx, dummy, TFSTAT_K_UPLOAD, ctx->stream, false);
-            hip_check(hipMemcpyAsync(hinfo, info, sizeof(*info), hipMemcpyDeviceToHost, ctx->stream), "range");
             hip_check(hipStreamSynchronize(ctx->stream), "hipStreamSynchronize");
             collect_timing(ctx, dummy);
-            // (products of two antenna sums and their inverses stay normal)
-            set->slide_ok = hinfo->wide == 0 && (int64_t)rows * nb * 32 < ((int64_t)1 << 31);
-            set->exact32 = hinfo->inexact32 == 0;
-            std::memcpy(&set->amax, &hinfo->amax, sizeof(double));
-            std::memcpy(&set->bmax, &hinfo->bmax, sizeof(double));
-            for (double v : {set->amax, set->bmax})
-                if (v != 0.0 && !(v > 0x1p-200 && v < 0x1p+200)) set->slide_ok = false;
+            set_ranges(*set, info);
         } catch (...) {
             ctx->pinned.put(pin, pin_bytes);
             std::lock_guard<std::mutex> g(ctx->mu);

@@ -269,13 +269,22 @@ struct SlideBatchParams {
     int32_t pad;
 };
 
-// What the sliding sums ask of the atoms, found once at upload.
+// Ranges of the atoms' values, found once at upload: a record per kAtomBins
+// bins (the last group: the antenna, a^2, b^2, ab and an unused column) and
+// chunk of 64-slot stretches.
+constexpr int kAtomBins = 8, kAtomWaves = 16, kAtomLanes = 8;
 struct RangeInfo {
-    int32_t wide;             // non-finite values, or a 64-slot stretch of a data column
-                              // under 2^-20 of the column's largest value
-    int32_t inexact32;        // some datum is not a single-precision number
-    unsigned long long amax, bmax;   // largest |a^2|, |b^2| (bits of the double)
+    int32_t flags;                // 1: non-finite values, 2: some value is no single-precision number
+    int32_t pad;
+    double most[kAtomBins][4];    // per bin and column: the largest magnitude,
+    double least[kAtomBins][4];   // and the smallest of the stretches' largest that is not 0 (inf: none)
 };
+inline int atom_groups(int n_bins) { return (n_bins + kAtomBins - 1) / kAtomBins + 1; }
+// a stretch per wave and round, in at most 1024 workgroups
+inline int atom_chunks(int K, int n_bins) {
+    const int64_t rounds = ((int64_t)K + 64 * kAtomWaves - 1) / (64 * kAtomWaves), most = 1024 / atom_groups(n_bins);
+    return (int)(rounds < 1 || most < 1 ? 1 : rounds < most ? rounds : most);
+}
 
 // Weight tables [blk][d][R] of a banded window: exponential g[d] =
 // exp(-d T / tau), or a shape window g[d] = s((delta + d T) / tau) with s
@@ -540,8 +549,9 @@ hipError_t launch_mfma_batch(const MfmaBatchParams &p, hipStream_t s);
 hipError_t launch_slide_anchors(const SlideParams &p, hipStream_t s);
 hipError_t launch_slide_rows(const SlideParams &p, hipStream_t s);
 hipError_t launch_slide_batch(const SlideBatchParams &p, hipStream_t s);
-// The FP32 plane x32 and the atoms' RangeInfo (info zeroed by the caller).
-hipError_t launch_atoms(const double *x64, const double *abc, float *x32, int32_t K, int32_t n_bins, RangeInfo *info,
+// The FP32 plane x32 and the atoms' ranges: atom_groups records per chunk, the
+// antenna's last (out: pinned host memory).
+hipError_t launch_atoms(const double *x64, const double *abc, float *x32, int32_t K, int32_t n_bins, RangeInfo *out,
                         hipStream_t s);
 hipError_t launch_shift_tables(const ShiftTableParams &p, int64_t max_entries, hipStream_t s);
 // Entries per shifted table (one tau, part and shift) for a band of lblk.

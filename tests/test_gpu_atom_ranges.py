@@ -1,0 +1,76 @@
+"""GPU ranges of the atoms' values, found at upload: they decide whether an
+exponential map is summed by sliding windows, and the FP32 plane written with
+them feeds those sums."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+import tfsynth
+from checks import TOL, check_map
+
+pytestmark = pytest.mark.gpu
+
+T = tfsynth.T_SFT
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_1805_05652_amd as tf
+    c = tf.Context(0, arena_bytes=1 << 30)
+    yield c
+    c.close()
+
+
+def slides(ctx, atoms, win, prec="fp32"):
+    """(map, whether it was summed by sliding windows)"""
+    aid = ctx.upload_atoms(atoms)
+    try:
+        ctx.profile_reset()
+        ctx.profile(True)
+        _, twoF = ctx.fmap(aid, win, prec, want_map=True)
+        return twoF.cpu().numpy(), ctx.profile_read()["recur"][0] == 1
+    finally:
+        ctx.profile(False)
+        ctx.free(aid)
+
+
+@pytest.mark.parametrize("slots", [2, 63, 64, 65, 1023, 1024, 1025, 8193, 17000])
+@pytest.mark.parametrize("n_bins", [1, 2, 3, 4, 5, 7, 8, 9, 17])
+def test_ranges_at_the_edges(ctx, n_bins, slots):
+    """Bins at the edges of a workgroup's eight and of the stretches a wave
+    takes side by side (8, 4, 2, 1), slots at the edges of stretches (64), of a
+    workgroup's sixteen waves (1024) and of more chunks: ordinary data slide;
+    one value that is not finite, in the first or last slot of any bin, does
+    not."""
+    print("case: ranges %d bins %d slots" % (n_bins, slots), flush=True)
+    base = tfsynth.make_atoms(9900 + slots + n_bins, slots, 0.0, n_bins=n_bins)
+    t0 = np.unique(np.linspace(0, (slots - 1) * T, 5).astype(np.int64))
+    win = tfsynth.list_window("exp", t0, np.unique([T, slots * T // 2, slots * T]))
+    got, n = slides(ctx, base, win)
+    assert n
+    check_map(got, oracle.fmap_atoms(base, win), TOL["fp64"])
+    small = tfsynth.list_window("exp", t0[:1], [T])
+    for b in (0, n_bins // 2, n_bins - 1):
+        for k in (0, slots - 1):
+            fb = base.fb.copy()
+            fb[b, k, 1] = np.inf if b else np.nan
+            assert not slides(ctx, dataclasses.replace(base, fb=fb), small)[1], (b, k)
+
+
+@pytest.mark.parametrize("n_bins", [1, 3, 9])
+def test_weak_stretches(ctx, n_bins):
+    """A column's 64-slot stretch 2^-21 below the column's largest value: not
+    by sliding windows; 2^-18: by them (in single precision)."""
+    print("case: weak stretches %d bins" % n_bins, flush=True)
+    base = tfsynth.make_atoms(9950 + n_bins, 2300, 0.0, n_bins=n_bins)
+    win = tfsynth.list_window("exp", [0, 7 * T], [5 * T])
+    for shift, want in ((-18, True), (-21, False)):
+        for stretch in (0, 17, 35):
+            fa = base.fa.copy()
+            col = fa[n_bins - 1, :, 1]
+            at = slice(64 * stretch, 64 * stretch + 64)
+            col[at] *= np.abs(col).max() / np.abs(col[at]).max() * 2.0 ** shift
+            fa = fa.astype(np.float32).astype(np.float64)
+            assert slides(ctx, dataclasses.replace(base, fa=fa), win)[1] == want, (shift, stretch)
