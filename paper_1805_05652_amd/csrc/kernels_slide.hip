@@ -23,12 +23,18 @@
 // range_len-th slot.
 //
 // Errors.  The factors are below one, so rounding errors fade with the
-// weights; what an earlier, stronger slot leaves behind is 2^-52 of it.  A
+// weights.  A slot enters by multiplications with the rounded rho and leaves
+// with a weight of its own, so what it leaves behind is up to n 2^-53 of it, n
+// the slots that the segment slid since (strong slots side by side add up).  A
 // cell whose A or B is below 2^-13 of the largest slot's a^2 or b^2 (an empty
-// window, or one of weak SFTs only) is summed directly, so that D keeps at
-// least 38 bits relative to A B and the degenerate rule decides as on direct
-// sums.  Atoms with non-finite values or with 64-slot stretches far below
-// their column's largest value (atoms_kernel) keep the direct forms.
+// window, or one of weak SFTs only) is summed directly, so that the degenerate
+// rule decides as on direct sums (D keeps about 38 bits of A B for n of a few
+// slots).  What data may spread over (set_ranges in the runtime) follows from
+// the same: simulated with a stretch of 64 strong slots, windows of 1200 slots
+// and segments of 3000 rows, the cells after it are off by 3e-12 in 2F at a
+// spread of 2^10 (double precision slides up to that) and 2e-9 at 2^19 (the
+// others up to 2^20); 5e-14 without.  Atoms beyond, or not finite, keep the
+// direct forms.
 #include "tfstat_device.h"
 
 #include <hip/hip_runtime.h>
@@ -675,6 +681,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x6
                                                                int32_t K, int32_t n_bins, RangeInfo *out) {
     constexpr int kSlots = 64 / kAtomLanes;              // slots of a lane
     __shared__ double smax[kAtomWaves][4][kAtomBins], smin[kAtomWaves][4][kAtomBins];
+    __shared__ double sslot[kAtomWaves][kAtomBins], sjoint[kAtomWaves][kAtomBins];
     __shared__ int sflags;
     auto larger = [](double x, double y) { return fmax(x, y); };
     auto smaller = [](double x, double y) { return fmin(x, y); };
@@ -695,6 +702,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x6
         mx[c] = 0.0;
         mn[c] = INFINITY;
     }
+    double slot = INFINITY, joint = INFINITY;   // of all four columns together
     bool bad = false, inexact = false;
     for (int k0 = (blockIdx.y * kAtomWaves + wave) * subs * 64; k0 < K; k0 += gridDim.y * kAtomWaves * subs * 64) {
         const int kb = k0 + sub * 64 + s8;
@@ -728,6 +736,8 @@ __global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x6
                 bad |= !(fabs(v[i][c]) < INFINITY);
                 m[c] = fmax(m[c], fabs(v[i][c]));
             }
+            const double all = fmax(fmax(fabs(v[i][0]), fabs(v[i][1])), fmax(fabs(v[i][2]), fabs(v[i][3])));
+            if (all > 0.0) slot = fmin(slot, all);
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -735,6 +745,8 @@ __global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x6
             mx[c] = fmax(mx[c], m[c]);
             if (m[c] > 0.0) mn[c] = fmin(mn[c], m[c]);
         }
+        const double all = fmax(fmax(m[0], m[1]), fmax(m[2], m[3]));
+        if (all > 0.0) joint = fmin(joint, all);
     }
     if (!ant && blockIdx.y == 0 && threadIdx.x < W) {   // row K is zero
         const float4 z = {0.f, 0.f, 0.f, 0.f};
@@ -751,6 +763,13 @@ __global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x6
             smin[wave][c][lane] = mn[c];
         }
     }
+    slot = ring(slot, lane, W, s8, kAtomLanes, smaller);
+    slot = ring(slot, lane, kAtomLanes * W, sub, subs, smaller);
+    joint = ring(joint, lane, kAtomLanes * W, sub, subs, smaller);
+    if (lane < W) {
+        sslot[wave][lane] = slot;
+        sjoint[wave][lane] = joint;
+    }
     __syncthreads();
     // the waves': sixteen lanes a (bin, column)
     RangeInfo &r = out[blockIdx.y * gridDim.x + blockIdx.x];
@@ -759,14 +778,18 @@ __global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x6
     const int eb = e >> 2, ec = e & 3;
     if (eb < W) {   // (whole groups of sixteen lanes)
         double x = smax[w][ec][eb], n = smin[w][ec][eb];
+        double y = ec ? sjoint[w][eb] : sslot[w][eb];   // (columns 2 and 3: the same again)
 #pragma unroll
         for (int o = 1; o < kAtomWaves; o <<= 1) {
             x = fmax(x, __shfl_xor(x, o, kAtomWaves));
             n = fmin(n, __shfl_xor(n, o, kAtomWaves));
+            y = fmin(y, __shfl_xor(y, o, kAtomWaves));
         }
         if (w == 0) {
             r.most[eb][ec] = x;
             r.least[eb][ec] = n;
+            if (ec == 0) r.slot[eb] = y;
+            if (ec == 1) r.joint[eb] = y;
         }
     }
 }

@@ -167,9 +167,10 @@ struct AtomsSet {
     double *abc = nullptr;
     double *x64 = nullptr;
     float *x32 = nullptr;
-    // sliding sums (kernels_slide.hip): whether they apply to these atoms,
-    // whether x32 holds x64 exactly, and the largest a^2 and b^2
-    bool slide_ok = false, exact32 = false;
+    // sliding sums (kernels_slide.hip): whether they apply to these atoms (and
+    // to maps in double precision), whether x32 holds x64 exactly, and the
+    // largest a^2 and b^2
+    bool slide_ok = false, slide_ok64 = false, exact32 = false;
     double amax = 0.0, bmax = 0.0;
     // bf16 hi / lo planes for the matrix-core path, built on first use
     void *planes = nullptr;
@@ -427,6 +428,7 @@ void plan_slide(Job &j) {
     const AtomsSet &at = *j.at;
     const bool tiling = j.runs_min_spread != kRunsAuto || j.split_min_bins != kSplitMinBins;
     if (!at.slide_ok || j.no_slide > 1 || j.forced) return;
+    if (j.prec == TFSTAT_PREC_FP64 && !at.slide_ok64) return;
     if (tiling && j.prec != TFSTAT_PREC_RECUR64) return;
     const int n_t0 = (int)j.win.t0.size(), n_tau = (int)j.win.tau.size();
     j.slide = true;
@@ -1365,40 +1367,54 @@ void ensure_planes(tfstat_ctx *ctx, AtomsSet *at, int32_t prec) {
     at->bytes += 2 * plane_b + exp_b + 2 * cplane_b;
 }
 
-// Whether sliding sums apply to atoms of these ranges, and what they need of them.
+// Whether sliding sums apply to atoms of these ranges, and what they need of
+// them.  What a strong slot leaves behind grows with its distance above the
+// slots after it, so the data must not spread too far: a 64-slot stretch of a
+// column not under 2^-20 of the column's largest value, a single slot (of all
+// columns together; windows may be that short) not under 2^-26 of the bin's;
+// for double precision a stretch not under 2^-10 and a slot not under 2^-18.
+// (A slot of Gaussian noise falls below 2^-18 of the largest with a chance of
+// 2e-10.)
 void set_ranges(AtomsSet &at, const tfs::RangeInfo *info) {
     const int groups = tfs::atom_groups(at.n_bins), chunks = tfs::atom_chunks(at.K, at.n_bins);
-    at.slide_ok = ((int64_t)at.K + 1) * at.n_bins * 32 < ((int64_t)1 << 31);
+    at.slide_ok = at.slide_ok64 = ((int64_t)at.K + 1) * at.n_bins * 32 < ((int64_t)1 << 31);
     at.exact32 = true;
     for (int g = 0; g < groups; ++g) {
         const bool ant = g == groups - 1;
         const int nb = ant ? 1 : std::min(at.n_bins - g * tfs::kAtomBins, tfs::kAtomBins);
-        double most[tfs::kAtomBins][4] = {}, least[tfs::kAtomBins][4];
-        for (auto &l : least)
-            for (double &v : l) v = INFINITY;
         for (int k = 0; k < chunks; ++k) {
             const tfs::RangeInfo &r = info[k * groups + g];
             at.slide_ok = at.slide_ok && !(r.flags & 1);
             at.exact32 = at.exact32 && (ant || !(r.flags & 2));
-            for (int b = 0; b < nb; ++b)
-                for (int c = 0; c < 4; ++c) {
-                    most[b][c] = std::max(most[b][c], r.most[b][c]);
-                    least[b][c] = std::min(least[b][c], r.least[b][c]);
-                }
         }
-        if (ant) {
-            at.amax = most[0][0];
-            at.bmax = most[0][1];
-            // (products of two antenna sums and their inverses stay normal)
-            for (double v : {at.amax, at.bmax})
-                if (v != 0.0 && !(v > 0x1p-200 && v < 0x1p+200)) at.slide_ok = false;
-        } else {
-            // a 64-slot stretch of a column far below the column's largest value
-            for (int b = 0; b < nb; ++b)
+        for (int b = 0; b < nb; ++b) {
+            double most[4] = {}, least[4], joint = INFINITY, slot = INFINITY;
+            for (double &v : least) v = INFINITY;
+            for (int k = 0; k < chunks; ++k) {
+                const tfs::RangeInfo &r = info[k * groups + g];
+                for (int c = 0; c < 4; ++c) {
+                    most[c] = std::max(most[c], r.most[b][c]);
+                    least[c] = std::min(least[c], r.least[b][c]);
+                }
+                joint = std::min(joint, r.joint[b]);
+                slot = std::min(slot, r.slot[b]);
+            }
+            if (ant) {
+                at.amax = most[0];
+                at.bmax = most[1];
+                // (products of two antenna sums and their inverses stay normal)
+                for (double v : {at.amax, at.bmax})
+                    if (v != 0.0 && !(v > 0x1p-200 && v < 0x1p+200)) at.slide_ok = false;
+            } else {
+                const double top = *std::max_element(most, most + 4);
                 for (int c = 0; c < 4; ++c)
-                    if (least[b][c] < most[b][c] * 0x1p-20) at.slide_ok = false;
+                    if (least[c] < most[c] * 0x1p-20) at.slide_ok = false;
+                if (slot < top * 0x1p-26) at.slide_ok = false;
+                if (joint < top * 0x1p-10 || slot < top * 0x1p-18) at.slide_ok64 = false;
+            }
         }
     }
+    at.slide_ok64 = at.slide_ok64 && at.slide_ok;
 }
 
 AtomsSet *find_atoms(tfstat_ctx *ctx, tfstat_atoms_id id) {

@@ -278,6 +278,8 @@ struct RangeInfo {
     int32_t pad;
     double most[kAtomBins][4];    // per bin and column: the largest magnitude,
     double least[kAtomBins][4];   // and the smallest of the stretches' largest that is not 0 (inf: none)
+    double joint[kAtomBins];      // per bin: the same of all four columns together,
+    double slot[kAtomBins];       // and the smallest slot's largest that is not 0
 };
 inline int atom_groups(int n_bins) { return (n_bins + kAtomBins - 1) / kAtomBins + 1; }
 // a stretch per wave and round, in at most 1024 workgroups

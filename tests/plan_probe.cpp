@@ -14,7 +14,7 @@ int main() {
         at.K = (int32_t)K;
         at.n_bins = (int32_t)bins;
         at.t_sft = T;
-        at.slide_ok = (K + 1) * bins * 32 < ((int64_t)1 << 31);
+        at.slide_ok = at.slide_ok64 = (K + 1) * bins * 32 < ((int64_t)1 << 31);
         at.exact32 = exact32 != 0;
         at.amax = at.bmax = 1.0;
         Job j;

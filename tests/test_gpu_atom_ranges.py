@@ -74,3 +74,29 @@ def test_weak_stretches(ctx, n_bins):
             col[at] *= np.abs(col).max() / np.abs(col[at]).max() * 2.0 ** shift
             fa = fa.astype(np.float32).astype(np.float64)
             assert slides(ctx, dataclasses.replace(base, fa=fa), win)[1] == want, (shift, stretch)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64", "recur64", "f16x3"])
+@pytest.mark.parametrize("case", ["in_every_stretch", "one_stretch", "one_weak_slot"])
+def test_strong_slots(ctx, case, prec):
+    """Slots far above their neighbours in data and not in the antenna (2F of
+    other windows has to come out as if they were not there): one in every 20
+    slots at 2^40, which no stretch of 64 slots shows; a stretch at 2^12, which
+    double precision does not slide over; a slot 2^-22 below the others.  The
+    map's error is taken relative to max(2F, 1), as everywhere."""
+    print("case: strong slots %s %s" % (case, prec), flush=True)
+    base = tfsynth.make_atoms(9970, 640, 0.0, n_bins=2)
+    fa, fb = base.fa.copy(), base.fb.copy()
+    if case == "in_every_stretch":
+        at, by = slice(7, None, 20), 2.0 ** 40
+    elif case == "one_stretch":
+        at, by = slice(320, 384), 2.0 ** 12
+    else:
+        at, by = slice(333, 334), 2.0 ** -22
+    fa[1, at] *= by
+    fb[1, at] *= by
+    atoms = dataclasses.replace(base, fa=fa, fb=fb)
+    win = tfsynth.regular_window("exp", 0, T, 600, T // 2, T // 5, 33)   # windows of 1 to 20 slots
+    got, n = slides(ctx, atoms, win, prec)
+    check_map(got, oracle.fmap_atoms(atoms, win), TOL[prec])
+    assert n == (case != "in_every_stretch" and prec != "fp64")
