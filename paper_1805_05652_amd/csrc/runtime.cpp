@@ -1402,9 +1402,11 @@ void set_ranges(AtomsSet &at, const tfs::RangeInfo *info) {
             if (ant) {
                 at.amax = most[0];
                 at.bmax = most[1];
-                // (products of two antenna sums and their inverses stay normal)
+                // (products of two antenna sums and their inverses stay normal;
+                // |ab| of any SFT is at most the mean of a^2 and b^2)
                 for (double v : {at.amax, at.bmax})
                     if (v != 0.0 && !(v > 0x1p-200 && v < 0x1p+200)) at.slide_ok = false;
+                if (most[2] > std::max(at.amax, at.bmax)) at.slide_ok = false;
             } else {
                 const double top = *std::max_element(most, most + 4);
                 for (int c = 0; c < 4; ++c)

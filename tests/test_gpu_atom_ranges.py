@@ -100,3 +100,17 @@ def test_strong_slots(ctx, case, prec):
     got, n = slides(ctx, atoms, win, prec)
     check_map(got, oracle.fmap_atoms(atoms, win), TOL[prec])
     assert n == (case != "in_every_stretch" and prec != "fp64")
+
+
+def test_antenna_products_of_no_antenna(ctx):
+    """An |ab| beyond a^2 and b^2 of every SFT (no antenna's) makes D of its
+    own windows negative (2F = 0) and nothing else."""
+    print("case: ab beyond a^2 and b^2", flush=True)
+    base = tfsynth.make_atoms(9980, 200, 0.0, n_bins=1)
+    ab = base.ab.copy()
+    ab[120] = 1e200
+    atoms = dataclasses.replace(base, ab=ab)
+    win = tfsynth.regular_window("exp", 0, T, 190, T, T // 3, 20)
+    got, n = slides(ctx, atoms, win)
+    check_map(got, oracle.fmap_atoms(atoms, win), TOL["fp32"])
+    assert not n
