@@ -7,7 +7,8 @@
 // Bayes factor (appendix A footnote) is reduced from per-tile partials.
 //
 // Layout of resident atoms (slot grid, zero-filled gaps, row K all zeros):
-//   abc [K+1][4]          FP64 a^2, b^2, ab, 0
+//   abc [K+1][4]          FP64 a^2, b^2, ab; in the last eight bytes the int32
+//                         first slot from this one on that holds an SFT (K: none)
 //   x64 [K+1][bins][4]    FP64 Re Fa, Im Fa, Re Fb, Im Fb
 //   x32 [K+1][bins][4]    FP32 copy of x64
 #include "tfstat_device.h"

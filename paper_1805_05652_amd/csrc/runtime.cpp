@@ -2359,8 +2359,12 @@ int tfstat_atoms_upload(tfstat_ctx *ctx, const tfstat_atoms_desc *d, tfstat_atom
             std::memset(pin, 0, abc_b + x64_b);
             double *habc = static_cast<double *>(pin);
             double *hx = reinterpret_cast<double *>(static_cast<char *>(pin) + abc_b);
+            auto next_sft = [&](int64_t k, int32_t next) { std::memcpy(habc + k * 4 + 3, &next, sizeof(next)); };
+            next_sft(K, K);
+            int64_t filled = 0;
             for (int32_t i = 0; i < d->n_sft; ++i) {
                 const int64_t k = (d->timestamps[i] - T0) / T;
+                for (; filled <= k; ++filled) next_sft(filled, (int32_t)k);
                 habc[k * 4 + 0] = d->a2[i];
                 habc[k * 4 + 1] = d->b2[i];
                 habc[k * 4 + 2] = d->ab[i];

@@ -39,7 +39,7 @@ struct AtomsView {
     int32_t K;            // number of slots
     int32_t n_bins;
     int64_t t_sft;
-    const double *abc;    // [K+1][4]: a2, b2, ab, 0
+    const double *abc;    // [K+1][4]: a2, b2, ab, next SFT's slot (int32)
     const double *x64;    // [K+1][n_bins][4]: Re Fa, Im Fa, Re Fb, Im Fb
     const float *x32;     // [K+1][n_bins][4]
 };
