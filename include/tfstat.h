@@ -79,11 +79,15 @@ typedef enum {
  *            In every precision, exponential windows are summed by sliding
  *            windows along t0, in FP64 (maps of two or more bins with their
  *            range sums on the FP64 matrix cores): a cell costs the slots
- *            between two t0 rows instead of its whole window.  Atoms with
- *            non-finite values, or whose data spread over more than 2^20
- *            between 64-slot stretches, maps whose workspace the arena cannot
- *            hold, and maps planned under an explicit tfstat_tiling_config
- *            are summed directly, in the named precision as described here.
+ *            between two t0 rows instead of its whole window.  A map whose
+ *            workspace does not fit the arena takes its columns in several
+ *            passes, with the same results bit for bit.  Summed directly, in
+ *            the named precision as described here, are: atoms with non-finite
+ *            values or whose data spread too far (a 64-slot stretch of a column
+ *            more than 2^20 below the column's largest value, or one slot more
+ *            than 2^26 below the bin's; FP64: 2^10 and 2^18), maps whose anchors
+ *            of one pass do not fit where the direct sums do, and maps planned
+ *            under an explicit tfstat_tiling_config.
  *   BF16X3 : F_a, F_b sums on bf16 matrix cores with split hi + lo operands
  *            (three products: hi*hi + hi*lo + lo*hi) and FP32 accumulation
  *            (section 3, exponential case: every cell is one banded

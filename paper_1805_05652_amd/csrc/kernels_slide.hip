@@ -276,6 +276,12 @@ __device__ __attribute__((always_inline)) inline void anchor_horner(const double
     }
 }
 
+// The pass's column (tau tile, bin group) in the anchors' memory.
+template <typename PP>
+__device__ __attribute__((always_inline)) inline size_t pass_column(PP &p, int tt, int bg) {
+    return (size_t)(tt - p.tt0) * p.pass_bg + (bg - p.bg0);
+}
+
 // bg == p.n_bg: the antenna's channels.
 template <int BG, typename PP>
 __device__ __attribute__((always_inline)) inline void slide_anchor(PP &p, double *tot, int tt, int bg, int sup) {
@@ -318,10 +324,11 @@ __device__ __attribute__((always_inline)) inline void slide_anchor(PP &p, double
     }
     __syncthreads();
     if (ant) {
-        anchor_horner<3>(tot, 2.0 * c, RL, n_first, kb < ke, p.anc_a + ((size_t)tt * p.n_range + g0) * 3 * 64,
-                         p.sup_a + ((size_t)tt * p.n_sup + sup) * 3 * 64);
+        const size_t at = tt - p.tt0;
+        anchor_horner<3>(tot, 2.0 * c, RL, n_first, kb < ke, p.anc_a + (at * p.n_range + g0) * 3 * 64,
+                         p.sup_a + (at * p.n_sup + sup) * 3 * 64);
     } else {
-        const size_t col = (size_t)tt * p.n_bg + bg;
+        const size_t col = pass_column(p, tt, bg);
         anchor_horner<4 * BG>(tot, c, RL, n_first, kb < ke, p.anc + (col * p.n_range + g0) * (4 * BG) * 64,
                               p.sup + (col * p.n_sup + sup) * (4 * BG) * 64);
     }
@@ -339,7 +346,7 @@ __device__ __attribute__((always_inline)) inline void slide_supers(PP &p, int tt
     const double c = -(double)p.t_sft / (double)p.tau[min(tt * 64 + lane, p.n_tau - 1)] * (double)len;
     const double f = exp(ant ? 2.0 * c : c);
     for (int q = threadIdx.x >> 6; q < CH; q += 4) {
-        double *s = ant ? p.sup_a + (size_t)tt * p.n_sup * 3 * 64 : p.sup + ((size_t)tt * p.n_bg + bg) * p.n_sup * CH * 64;
+        double *s = ant ? p.sup_a + (size_t)(tt - p.tt0) * p.n_sup * 3 * 64 : p.sup + pass_column(p, tt, bg) * p.n_sup * CH * 64;
         s += q * 64 + lane;
         double H = 0.0;   // (a short super-range is the last: nothing comes after it)
 #pragma unroll 8
@@ -365,7 +372,7 @@ __device__ __attribute__((always_inline)) inline void slide_supers(PP &p, int tt
 // are in LDS from slot w_lo on.
 template <int BG, bool STAGED, typename PP>
 __device__ __attribute__((always_inline)) inline void slide_segment(PP &p, double *lds, int tt, int col, int bin0, int seg,
-                                                                  int w_lo) {
+                                                                  int w_lo) {   // col: of the pass
     const int lane = threadIdx.x & 63;
     const int n_bins = p.n_bins;
     const int K = p.K;
@@ -432,8 +439,8 @@ __device__ __attribute__((always_inline)) inline void slide_segment(PP &p, doubl
     // channel c of anchor g, or of H at the end of super-range g
     const double *anc = p.anc + (size_t)col * p.n_range * (4 * BG) * 64 + lane;
     const double *sup = p.sup + (size_t)col * p.n_sup * (4 * BG) * 64 + lane;
-    const double *anc_a = p.anc_a + (size_t)tt * p.n_range * 3 * 64 + lane;
-    const double *sup_a = p.sup_a + (size_t)tt * p.n_sup * 3 * 64 + lane;
+    const double *anc_a = p.anc_a + (size_t)(tt - p.tt0) * p.n_range * 3 * 64 + lane;
+    const double *sup_a = p.sup_a + (size_t)(tt - p.tt0) * p.n_sup * 3 * 64 + lane;
     auto load_sums = [&](const double *x, const double *a, int g) {
         Sums<BG> y;
 #pragma unroll
@@ -629,8 +636,9 @@ template <int BG, bool STAGED, typename PP>
 __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, double *lds, int col, int group) {
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tt = col / p.n_bg;
-    const int bin0 = (col - tt * p.n_bg) * BG;
+    const int at = col / p.pass_bg;
+    const int tt = p.tt0 + at;
+    const int bin0 = (p.bg0 + col - at * p.pass_bg) * BG;
     const int n_bins = p.n_bins;
     const int K = p.K;
     const int RL = p.range_len;
@@ -813,8 +821,9 @@ __global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x6
 template <int BG>
 __global__ __launch_bounds__(64 * kSlideWaves) void slide_anchor_kernel(SlideParams p) {
     __shared__ double tot[anchor_smem<BG>()];
-    const int tt = blockIdx.x / (p.n_bg + 1);
-    slide_anchor<BG>(p, tot, tt, blockIdx.x - tt * (p.n_bg + 1), blockIdx.y);
+    const int at = blockIdx.x / (p.pass_bg + 1);
+    const int i = blockIdx.x - at * (p.pass_bg + 1);   // (the last: the antenna)
+    slide_anchor<BG>(p, tot, p.tt0 + at, i == p.pass_bg ? p.n_bg : p.bg0 + i, blockIdx.y);
 }
 
 template <int BG, bool STAGED>
@@ -824,8 +833,9 @@ __global__ __launch_bounds__(64 * kRowsWaves) void slide_rows_kernel(SlideParams
 }
 
 __global__ __launch_bounds__(256) void slide_supers_kernel(SlideParams p) {
-    const int tt = blockIdx.x / (p.n_bg + 1);
-    slide_supers(p, tt, blockIdx.x - tt * (p.n_bg + 1));
+    const int at = blockIdx.x / (p.pass_bg + 1);
+    const int i = blockIdx.x - at * (p.pass_bg + 1);
+    slide_supers(p, p.tt0 + at, i == p.pass_bg ? p.n_bg : p.bg0 + i);
 }
 
 // Many maps, one workgroup per entry; the bins per group are the map's.
@@ -901,7 +911,7 @@ hipError_t launch_atoms(const double *x64, const double *abc, float *x32, int32_
 
 hipError_t launch_slide_anchors(const SlideParams &p, hipStream_t s) {
     if (p.n_tau <= 0 || p.n_t0 <= 0 || p.seg_rows < 1 || p.range_len < 16 || p.range_len % 16) return hipErrorInvalidValue;
-    const dim3 g((unsigned)(p.n_tt * (p.n_bg + 1)), (unsigned)p.n_sup), b(64 * kSlideWaves);
+    const dim3 g((unsigned)(p.pass_tt * (p.pass_bg + 1)), (unsigned)p.n_sup), b(64 * kSlideWaves);
     if (g.y > 65535u) return hipErrorInvalidValue;
     switch (p.bg) {
     case 1: hipLaunchKernelGGL(slide_anchor_kernel<1>, g, b, 0, s, p); break;
@@ -917,7 +927,7 @@ hipError_t launch_slide_anchors(const SlideParams &p, hipStream_t s) {
 hipError_t launch_slide_rows(const SlideParams &p, hipStream_t s) {
     const unsigned lds = slide_stage_bytes(p.bg, p.stage);
     if (p.waves < 1 || p.waves > kRowsWaves || p.stage < 0 || lds > kSlideStageBytes) return hipErrorInvalidValue;
-    const dim3 g((unsigned)(p.n_tt * p.n_bg), (unsigned)((p.n_seg + p.waves - 1) / p.waves)), b(64u * p.waves);
+    const dim3 g((unsigned)(p.pass_tt * p.pass_bg), (unsigned)((p.n_seg + p.waves - 1) / p.waves)), b(64u * p.waves);
     if (g.y > 65535u) return hipErrorInvalidValue;
     switch (2 * p.bg + (p.stage > 0)) {
     case 2: hipLaunchKernelGGL((slide_rows_kernel<1, false>), g, b, 0, s, p); break;

@@ -280,6 +280,11 @@ constexpr int32_t kSplitMinBins = 8;
 constexpr int64_t kCus = 256;
 constexpr int64_t kSlideMost = 16384;
 constexpr int64_t kSlideRanges = 1536;
+// Anchors of a sliding map: memory of one pass over its columns.  A map of 256
+// bins x 500 taus over 2000 slots takes 140 MB; a pass of this size fills the
+// chip many times over, so more passes cost their launches only, and long data
+// with many taus leave room for others in the arena.
+constexpr size_t kAnchorBytes = (size_t)256 << 20;
 // Blocks of 256 slots that a rect map's prefix sums are split into at most.
 constexpr int64_t kScanMostBlocks = 6144;
 
@@ -315,6 +320,8 @@ struct Job {
     bool forced = false;       // tile shape forced by the caller: the direct forms
     int32_t bg = 1, n_bg = 1, n_tt = 1, n_seg = 1, seg_rows = 1, range_len = 1, n_range = 1, n_sup = 1;
     int32_t kbeg = 0, waves = 1, stage = 0;
+    size_t anchor_most = kAnchorBytes;   // bytes its anchors may take,
+    int32_t pass_tt = 1, pass_bg = 1;    // and the tau tiles and bin groups of a pass within them
     int32_t rect_rows = 64;      // rect maps: rows of a tile
     int64_t tau_spread = 0;      // slots that 64 taus' window ends span at most
     std::vector<tfs::SlideTile> tiles;
@@ -511,6 +518,32 @@ void plan_slide(Job &j) {
     j.n_range = j.n_sup * tfs::kSlideWaves;
 }
 
+// Anchors of tts tau tiles x bgs bin groups, in bytes.
+size_t anchor_bytes(const Job &j, int64_t tts, int64_t bgs) {
+    return sizeof(double) * 64 * (size_t)tts * (size_t)(bgs * 4 * j.bg + 3) * (size_t)(j.n_range + j.n_sup);
+}
+
+// A map's columns in passes whose anchors fit anchor_most: whole tau tiles, or
+// some of one tile's bin groups (one at least).  What a column's sums are does
+// not depend on the passes.
+void plan_passes(Job &j) {
+    auto split = [](int64_t n, int64_t most) {   // n in equal parts of at most `most`
+        const int64_t parts = (n + most - 1) / most;
+        return (int32_t)((n + parts - 1) / parts);
+    };
+    const int64_t tts = (int64_t)(j.anchor_most / anchor_bytes(j, 1, j.n_bg));
+    j.pass_tt = tts > 0 ? split(j.n_tt, tts) : 1;
+    j.pass_bg = j.n_bg;
+    if (tts > 0) return;
+    int64_t bgs = j.n_bg;
+    while (bgs > 1 && anchor_bytes(j, 1, bgs) > j.anchor_most) bgs /= 2;
+    j.pass_bg = split(j.n_bg, bgs);
+}
+
+int32_t n_passes(const Job &j) {
+    return ((j.n_tt + j.pass_tt - 1) / j.pass_tt) * ((j.n_bg + j.pass_bg - 1) / j.pass_bg);
+}
+
 void plan_job(Job &j) {
     const AtomsSet &at = *j.at;
     const int64_t T = at.t_sft;
@@ -584,6 +617,7 @@ void plan_job(Job &j) {
         if (!j.use_mfma) j.mfma_rows = false;
     }
     if (j.slide) {
+        plan_passes(j);
         j.NB = 0;
         j.n_tiles = j.n_tt * j.n_seg;
     } else if (is_exp) {
@@ -716,8 +750,8 @@ void plan_job(Job &j) {
     if (j.slide || !is_exp) j.off_tiles = take(sizeof(tfs::SlideTile) * j.n_tt);
     j.tables_bytes = o;
     if (j.slide) {
-        const size_t ch = (size_t)j.n_tt * j.n_bg * (4 * j.bg) * 64 * sizeof(double);
-        const size_t ch_a = (size_t)j.n_tt * 3 * 64 * sizeof(double);
+        const size_t ch = (size_t)j.pass_tt * j.pass_bg * (4 * j.bg) * 64 * sizeof(double);
+        const size_t ch_a = (size_t)j.pass_tt * 3 * 64 * sizeof(double);
         j.off_anc = take(ch * j.n_range);
         j.off_sup = take(ch * j.n_sup);
         j.off_anca = take(ch_a * j.n_range);
@@ -750,16 +784,38 @@ void plan_job(Job &j) {
 }
 
 // Plans a map again with less workspace, for an arena that cannot hold it;
-// false when it has no smaller plan.  Sliding maps: RECUR64 ones (never large)
-// with the smallest workspace first, others by the direct forms; rect maps:
-// without block totals.
+// false when it has no smaller plan.  Sliding maps: more passes, which change
+// no result, down to what the direct sums would take (an arena that holds
+// neither refuses the map), and the direct sums where one column's anchors take
+// more than that; RECUR64 maps down to one column a pass, then with the
+// smallest workspace, then directly.  Rect maps: without block totals.
 bool plan_smaller(Job &j) {
-    if (j.slide)
-        j.no_slide = j.prec == TFSTAT_PREC_RECUR64 && j.no_slide == 0 ? 1 : 2;
-    else if (!banded(j.win.type) && j.scan_blk > 0)
+    if (!j.slide) {
+        if (banded(j.win.type) || j.scan_blk == 0) return false;
         j.small_ws = true;
-    else
-        return false;
+        plan_job(j);
+        return true;
+    }
+    const size_t now = j.ws_bytes;
+    const bool last = j.pass_tt == 1 && j.pass_bg == 1;
+    const size_t kept = now - anchor_bytes(j, j.pass_tt, j.pass_bg);   // (and up to 1 KB of padding)
+    if (j.prec == TFSTAT_PREC_RECUR64) {
+        if (last)
+            ++j.no_slide;
+        else
+            j.anchor_most = 0;
+        plan_job(j);
+        return true;
+    }
+    const int no_slide = j.no_slide;
+    j.no_slide = 2;
+    plan_job(j);
+    const size_t direct = j.ws_bytes;
+    j.no_slide = no_slide;
+    j.anchor_most = std::min(j.anchor_most, direct > kept ? direct - kept : 0);
+    plan_job(j);
+    if (j.ws_bytes <= direct) return j.ws_bytes < now;
+    j.no_slide = 2;
     plan_job(j);
     return true;
 }
@@ -1035,9 +1091,14 @@ tfs::AbcRecurParams abc_recur_params(Job &j) {
     return q;
 }
 
-tfs::SlideParams slide_params(Job &j) {
+tfs::SlideParams slide_params(Job &j, int32_t pass) {
     const AtomsSet &at = *j.at;
     tfs::SlideParams q{};
+    const int32_t across = (j.n_bg + j.pass_bg - 1) / j.pass_bg;   // passes of one tau tile
+    q.tt0 = pass / across * j.pass_tt;
+    q.pass_tt = std::min(j.pass_tt, j.n_tt - q.tt0);
+    q.bg0 = pass % across * j.pass_bg;
+    q.pass_bg = std::min(j.pass_bg, j.n_bg - q.bg0);
     q.K = at.K;
     q.n_bins = at.n_bins;
     q.n_t0 = (int32_t)j.win.t0.size();
@@ -1190,19 +1251,20 @@ void enqueue_job(tfstat_ctx *ctx, Job &j, hipStream_t s) {
     auto *res = ws_ptr<tfs::BinResultDev>(j, j.off_res);
 
     if (j.slide) {
-        const tfs::SlideParams sp = slide_params(j);
         // (the anchors' range sums are on the matrix cores; a one-bin map's
         // two launches are one entry)
         const bool apart = j.at->n_bins > 1;
-        if (apart) record_kernel(ctx, j, TFSTAT_K_MFMA, s, true);
-        else record_kernel(ctx, j, TFSTAT_K_RECUR, s, true);
-        hip_check(tfs::launch_slide_anchors(sp, s), "sliding anchors kernel");
-        if (apart) {
-            record_kernel(ctx, j, TFSTAT_K_MFMA, s, false);
-            record_kernel(ctx, j, TFSTAT_K_RECUR, s, true);
+        for (int32_t pass = 0; pass < n_passes(j); ++pass) {
+            const tfs::SlideParams sp = slide_params(j, pass);
+            record_kernel(ctx, j, apart ? TFSTAT_K_MFMA : TFSTAT_K_RECUR, s, true);
+            hip_check(tfs::launch_slide_anchors(sp, s), "sliding anchors kernel");
+            if (apart) {
+                record_kernel(ctx, j, TFSTAT_K_MFMA, s, false);
+                record_kernel(ctx, j, TFSTAT_K_RECUR, s, true);
+            }
+            hip_check(tfs::launch_slide_rows(sp, s), "sliding rows kernel");
+            record_kernel(ctx, j, TFSTAT_K_RECUR, s, false);
         }
-        hip_check(tfs::launch_slide_rows(sp, s), "sliding rows kernel");
-        record_kernel(ctx, j, TFSTAT_K_RECUR, s, false);
     } else if (is_exp) {
         tfs::WeightParams wp = weight_params(j);
         record_kernel(ctx, j, TFSTAT_K_WEIGHTS, s, true);
@@ -1463,8 +1525,8 @@ struct tfstat_batch {
     bool scan_split = false;
     tfs::MergeBatchParams mbp{};
     tfs::AbcBatchParams abp{};       // A/B/C pre-pass of the split-form and matrix-core maps
-    tfs::SlideBatchParams slp{};
-    tfs::RectBatchParams rbp{};     // sliding sums of exponential maps
+    std::vector<tfs::SlideBatchParams> slp;   // sliding sums of exponential maps, pass by pass
+    tfs::RectBatchParams rbp{};
     tfs::MfmaBatchParams mfp{};      // matrix-core work of the BF16X3 / F16X3 maps
     tfs::AbcRecurBatchParams rap{};  // recurrence A/B/C of exponential split and matrix-core maps
     tfs::BinResultDev *res_dev = nullptr;
@@ -1527,7 +1589,9 @@ int job_shape(const Job &j) {
 bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bool have_lock) {
     const int32_t n = (int32_t)b->jobs.size();
     std::vector<int> shape(n, -1), eidx(n, -1), ridx(n, -1), midx(n, -1), sidx(n, -1);
-    int n_slide = 0;
+    int n_slide = 0;                    // passes of sliding maps
+    int most_passes = 0;
+    uint32_t slide_lds = 0;
     size_t n_rent = 0;                  // rect tiles
     size_t n_anchor = 0, n_srows = 0;   // workgroups of the sliding maps' two launches
     int n_exp = 0, n_rect = 0, n_went = 0, n_scan = 0, n_abc = 0, n_mfma_maps = 0, n_rabc_maps = 0;
@@ -1538,12 +1602,14 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     b->res_off.assign(n, 0);
     b->n_results = 0;
     b->scan_split = false;
-    b->slp.lds_bytes = 0;
+    b->slp.clear();
     b->rbp.lds_bytes = 0;
     for (int32_t i = 0; i < n; ++i) {
         Job &j = *b->jobs[i];
         if (j.slide) {
-            sidx[i] = n_slide++;
+            sidx[i] = n_slide;
+            n_slide += n_passes(j);
+            most_passes = std::max<int>(most_passes, n_passes(j));
             // (one workgroup size for all maps: as many of its waves as fill
             // evenly and as the stage holds)
             int64_t wv = tfs::kRowsWaves;
@@ -1552,9 +1618,10 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
                 j.waves = (int32_t)((j.n_seg + wgs - 1) / wgs);
                 if (j.stage > 0) j.stage = (int32_t)slide_stage(j, (int64_t)j.waves * j.seg_rows, j.range_len);
             } while (tfs::slide_stage_bytes(j.bg, j.stage) > tfs::kSlideStageBytes && --wv >= 1);
-            n_anchor += (size_t)j.n_tt * (j.n_bg + 1) * j.n_sup;
+            // (every pass over some of a tile's bin groups has the antenna's anchors)
+            n_anchor += (size_t)j.n_tt * (j.n_bg + (j.n_bg + j.pass_bg - 1) / j.pass_bg) * j.n_sup;
             n_srows += (size_t)j.n_tt * j.n_bg * ((j.n_seg + j.waves - 1) / j.waves);
-            b->slp.lds_bytes = std::max(b->slp.lds_bytes, tfs::slide_stage_bytes(j.bg, j.stage));
+            slide_lds = std::max(slide_lds, tfs::slide_stage_bytes(j.bg, j.stage));
         } else if (banded(j.win.type)) {
             if (j.use_mfma && !j.mfma_rows)
                 raise(TFSTAT_E_INVAL, "a batch runs no matrix-core shape windows (use tfstat_fmap)");
@@ -1783,7 +1850,7 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
                         }
             }
         } else if (sidx[i] >= 0) {
-            slp[sidx[i]] = slide_params(j);
+            for (int32_t pass = 0; pass < n_passes(j); ++pass) slp[sidx[i] + pass] = slide_params(j, pass);
         } else {
             rp[ridx[i]] = rect_params(j);
             for (int c = -1; c < (4 * j.at->n_bins + 63) / 64; ++c)
@@ -1830,24 +1897,38 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
         };
         std::stable_sort(by.begin(), by.end(), [&](int32_t x, int32_t y) { return cost(x) > cost(y); });
         size_t ae_ = 0, sr_ = 0;
-        for (int32_t i : by) {
-            const Job &j = *b->jobs[i];
-            const int cols = j.n_tt * j.n_bg;
-            for (int u = 0; u < j.n_sup; ++u)
-                for (int c = 0; c < j.n_tt * (j.n_bg + 1); ++c, ++ae_) {
-                    aent[4 * ae_] = sidx[i];
-                    aent[4 * ae_ + 1] = c / (j.n_bg + 1);
-                    aent[4 * ae_ + 2] = c % (j.n_bg + 1);
-                    aent[4 * ae_ + 3] = u;
-                }
-            for (int q = 0; q < (j.n_seg + j.waves - 1) / j.waves; ++q)
-                for (int c = 0; c < cols; ++c, ++sr_) {
-                    sent[4 * sr_] = sidx[i];
-                    sent[4 * sr_ + 1] = c;
-                    sent[4 * sr_ + 2] = q;
-                    sent[4 * sr_ + 3] = 0;
-                }
+        for (int32_t pass = 0; pass < most_passes; ++pass) {
+            tfs::SlideBatchParams q{};
+            q.jobs = reinterpret_cast<const tfs::SlideParams *>(dptr(off_slp));
+            q.anchors = reinterpret_cast<const int32_t *>(dptr(off_aent)) + 4 * ae_;
+            q.rows = reinterpret_cast<const int32_t *>(dptr(off_sent)) + 4 * sr_;
+            q.lds_bytes = slide_lds;
+            const size_t ae0 = ae_, sr0 = sr_;
+            for (int32_t i : by) {
+                const Job &j = *b->jobs[i];
+                if (pass >= n_passes(j)) continue;
+                const tfs::SlideParams &sp = slp[sidx[i] + pass];
+                for (int u = 0; u < j.n_sup; ++u)
+                    for (int t = 0; t < sp.pass_tt; ++t)
+                        for (int g = 0; g <= sp.pass_bg; ++g, ++ae_) {
+                            aent[4 * ae_] = sidx[i] + pass;
+                            aent[4 * ae_ + 1] = sp.tt0 + t;
+                            aent[4 * ae_ + 2] = g == sp.pass_bg ? j.n_bg : sp.bg0 + g;
+                            aent[4 * ae_ + 3] = u;
+                        }
+                for (int g = 0; g < (j.n_seg + j.waves - 1) / j.waves; ++g)
+                    for (int c = 0; c < sp.pass_tt * sp.pass_bg; ++c, ++sr_) {
+                        sent[4 * sr_] = sidx[i] + pass;
+                        sent[4 * sr_ + 1] = c;
+                        sent[4 * sr_ + 2] = g;
+                        sent[4 * sr_ + 3] = 0;
+                    }
+            }
+            q.n_anchors = (int32_t)(ae_ - ae0);
+            q.n_rows = (int32_t)(sr_ - sr0);
+            b->slp.push_back(q);
         }
+        if (ae_ != n_anchor || sr_ != n_srows) raise(TFSTAT_E_INVAL, "internal: sliding entry count");
     }
 
     b->fp.exp_jobs = reinterpret_cast<const tfs::ExpValuParams *>(dptr(off_ep));
@@ -1872,11 +1953,6 @@ bool batch_layout(tfstat_ctx *ctx, tfstat_batch *b, hipStream_t s, bool sync, bo
     b->rbp.jobs = reinterpret_cast<const tfs::RectParams *>(dptr(off_rp));
     b->rbp.entries = reinterpret_cast<const int32_t *>(dptr(off_rtent));
     b->rbp.n_entries = (int32_t)n_rent;
-    b->slp.jobs = reinterpret_cast<const tfs::SlideParams *>(dptr(off_slp));
-    b->slp.anchors = reinterpret_cast<const int32_t *>(dptr(off_aent));
-    b->slp.rows = reinterpret_cast<const int32_t *>(dptr(off_sent));
-    b->slp.n_anchors = (int32_t)n_anchor;
-    b->slp.n_rows = (int32_t)n_srows;
     b->mfp.jobs = reinterpret_cast<const tfs::ExpMfmaRowsParams *>(dptr(off_mfp));
     b->mfp.entries = reinterpret_cast<const int32_t *>(dptr(off_ment));
     if (mfc != n_cells_entries || mfe != n_mfma_entries) raise(TFSTAT_E_INVAL, "internal: matrix-core entry count");
@@ -1945,8 +2021,19 @@ void batch_build(tfstat_ctx *ctx, tfstat_batch *b, int32_t n, const tfstat_atoms
                 if (j->use_mfma) ensure_planes(ctx, j->at, prec);
         }
         if (batch_layout(ctx, b, ctx->batch_stream, true, false)) break;
+        // the largest of those that have a smaller plan, and those of at least
+        // half its size
+        std::vector<Job *> by(b->jobs);
+        std::stable_sort(by.begin(), by.end(), [](const Job *x, const Job *y) { return x->ws_bytes > y->ws_bytes; });
+        size_t least = 0;
         bool smaller = false;
-        for (Job *j : b->jobs) smaller = plan_smaller(*j) || smaller;
+        for (Job *j : by) {
+            const size_t now = j->ws_bytes;
+            if (smaller && now < least) break;
+            if (!plan_smaller(*j) || smaller) continue;
+            smaller = true;
+            least = now / 2;
+        }
         if (!smaller) raise(TFSTAT_E_NOMEM, "arena cannot hold the batch workspace");
     }
 }
@@ -1966,7 +2053,8 @@ hipError_t batch_enqueue(tfstat_batch *b, hipStream_t s, bool timed) {
     if (e == hipSuccess && timed) e = hipEventRecord(b->evf1, s);
     if (e == hipSuccess) e = tfs::launch_mfma_batch(b->mfp, s);
     if (e == hipSuccess && timed) e = hipEventRecord(b->evm1, s);
-    if (e == hipSuccess) e = tfs::launch_slide_batch(b->slp, s);
+    for (const tfs::SlideBatchParams &q : b->slp)
+        if (e == hipSuccess) e = tfs::launch_slide_batch(q, s);
     if (e == hipSuccess) e = tfs::launch_merge_batch(b->mbp, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->pin, b->res_dev, sizeof(tfs::BinResultDev) * b->n_results,

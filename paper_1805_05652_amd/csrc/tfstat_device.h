@@ -243,6 +243,9 @@ struct SlideParams {
     int32_t exact32;          // x32 holds x64 exactly
     int32_t kbeg;             // first slot of the anchors' ranges
     int32_t waves, stage;     // rows kernel: segments per workgroup, slots its stage holds
+    // this pass's columns: pass_bg bin groups from bg0 on of pass_tt tau tiles
+    // from tt0 on (anchors are kept for one pass at a time)
+    int32_t tt0, pass_tt, bg0, pass_bg;
     int32_t pad;
     double guard_a, guard_b;  // cells with A or B below these are summed directly
     const RowPlan *rows;
@@ -251,15 +254,16 @@ struct SlideParams {
     const double *abc;        // [K+1][4]
     const double *x64;        // [K+1][n_bins][4]
     const float *x32;         // [K+1][n_bins][4]
-    double *anc;              // [n_tt * n_bg][n_range][4 bg][64] data anchors
-    double *sup;              // [n_tt * n_bg][n_sup][4 bg][64]
-    double *anc_a, *sup_a;    // the same of the antenna: [n_tt][n_range or n_sup][3][64]
+    double *anc;              // [pass_tt * pass_bg][n_range][4 bg][64] data anchors
+    double *sup;              // [pass_tt * pass_bg][n_sup][4 bg][64]
+    double *anc_a, *sup_a;    // the same of the antenna: [pass_tt][n_range or n_sup][3][64]
     float *twoF;
     Partial *part;            // [n_bins][n_tiles], tile tt * n_seg + seg
 };
 
-// Sliding maps of a batch: anchor entry = {map, tau tile, bin group (n_bg: the
-// antenna), super-range}, rows entry = {map, column, group of segments, 0}.
+// Sliding maps of a batch, one pass of each: anchor entry = {job, tau tile, bin
+// group (n_bg: the antenna), super-range}, rows entry = {job, column of the
+// pass, group of segments, 0}; a job is a map's pass.
 struct SlideBatchParams {
     const SlideParams *jobs;
     const int32_t *anchors;   // [n_anchors][4]

@@ -23,11 +23,14 @@ def probe(tmp_path_factory):
                     os.path.join(ROOT, "tests", "plan_probe.cpp"), "-o", exe, "-L" + lib, "-ltfstat",
                     "-Wl,-rpath," + lib, "-lpthread"], check=True, capture_output=True)
 
-    def plan(kind, prec, K, bins, t0, tau, exact32=True, t_sft=T):
-        line = [{"rect": 0, "exp": 1}[kind], PREC[prec], K, bins, t_sft, int(exact32), len(t0), *t0, len(tau), *tau]
+    def plan(kind, prec, K, bins, t0, tau, exact32=True, t_sft=T, anchor_most=-1, smaller=0):
+        line = [{"rect": 0, "exp": 1}[kind], PREC[prec], K, bins, t_sft, int(exact32), anchor_most, smaller,
+                len(t0), *t0, len(tau), *tau]
         out = subprocess.run([exe], input=" ".join(str(int(v)) for v in line), check=True, capture_output=True,
                              text=True).stdout
-        return {k: int(v) for k, v in (f.split("=") for f in out.split())}
+        p = dict(f.split("=") for f in out.split())
+        passes = [tuple(int(v) for v in p.pop(k).split(",")) for k in list(p) if k.startswith("pass")]
+        return {**{k: int(v) for k, v in p.items()}, "passes": passes}
     return plan
 
 
@@ -99,3 +102,55 @@ def test_slide_launch_limits(probe, prec, K, bins):
     p = probe("exp", prec, K, bins, t0, [T, K * T // 4 + 1, K * T])
     assert p["slide"] and p["range_len"] % 16 == 0 and p["n_sup"] <= 65535
     assert p["range_len"] * 8 * p["n_sup"] >= K and p["n_range"] == 8 * p["n_sup"]
+
+
+@pytest.mark.parametrize("bins,n_tau", [(1, 64), (1, 700), (4, 200), (9, 130), (64, 65), (256, 500), (3, 1)])
+@pytest.mark.parametrize("mib", [-1, 64, 8, 1, 0])
+def test_passes_cover_every_column_once(probe, bins, n_tau, mib):
+    """Tau tiles x bin groups in passes whose anchors fit the bytes they may
+    take (or hold one column); the default lets common maps run in one."""
+    t0, tau = np.arange(300) * T, (2 + np.arange(n_tau)) * T
+    p = probe("exp", "fp32", 2500, bins, t0, tau, anchor_most=mib << 20 if mib >= 0 else -1)
+    seen = np.zeros((p["n_tt"], p["n_bg"]), dtype=int)
+    for tt0, tts, bg0, bgs in p["passes"]:
+        assert tts >= 1 and bgs >= 1 and (tts == 1 or bgs == p["n_bg"])
+        seen[tt0:tt0 + tts, bg0:bg0 + bgs] += 1
+        assert tt0 + tts <= p["n_tt"] and bg0 + bgs <= p["n_bg"]
+    assert (seen == 1).all()
+    most = (mib if mib >= 0 else 256) << 20
+    assert p["anchors"] <= most or p["passes"][0][1::2] == (1, 1)
+    if mib < 0:
+        assert len(p["passes"]) == 1
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64", "f16x3"])
+@pytest.mark.parametrize("K,bins,n_t0,n_tau,longest", [(5000, 64, 600, 700, 1600), (5000, 1, 1000, 1000, 1600),
+                                                       (4000, 2, 700, 3, 100), (9000, 16, 100, 300, 40),
+                                                       (900, 5, 500, 300, 300), (3000, 256, 300, 200, 1000)])
+def test_smaller_plans(probe, prec, K, bins, n_t0, n_tau, longest):
+    """With less workspace a sliding map takes more passes, in no more than the
+    direct sums would take; where not even one column fits that, the direct
+    sums.  Nothing smaller when the direct sums would take more than all."""
+    t0, tau = np.arange(n_t0) * T, np.unique(np.linspace(2 * T, longest * T, n_tau).astype(np.int64))
+    full = probe("exp", prec, K, bins, t0, tau)
+    direct = probe("exp", prec, K, bins, t0, tau, anchor_most=0, smaller=9)
+    small = probe("exp", prec, K, bins, t0, tau, smaller=9)
+    assert full["slide"] and full["smaller"] == 0
+    if small["slide"]:
+        assert small["smaller"] == len(small["passes"]) - 1 == 0 or small["ws"] < full["ws"]
+        for k in ("bg", "n_seg", "seg_rows", "range_len", "n_range", "n_sup", "kbeg", "waves", "stage"):
+            assert small[k] == full[k], k   # (the same sums)
+    else:
+        assert direct["ws"] == small["ws"] and small["no_slide"] == 2
+    assert small["ws"] <= full["ws"]
+
+
+def test_smaller_plans_of_the_recurrence(probe):
+    """RECUR64 shrinks to one column a pass, then to the smallest workspace,
+    then to the direct sums."""
+    t0, tau = np.arange(700) * T, (2 + np.arange(130)) * T
+    got = [probe("exp", "recur64", 4000, 9, t0, tau, smaller=n) for n in range(5)]
+    assert [(p["slide"], p["no_slide"]) for p in got] == [(1, 0), (1, 0), (1, 1), (0, 2), (0, 2)]
+    assert got[1]["passes"][0][1::2] == got[2]["passes"][0][1::2] == (1, 1)
+    assert got[0]["ws"] > got[1]["ws"] > got[2]["ws"]
+    assert got[4]["smaller"] == 3
