@@ -2233,6 +2233,16 @@ void worker_loop(tfstat_ctx *ctx) {
                 continue;
             }
             auto &t = it->second;
+            // Nothing runs that would give memory back: what holds it is not the
+            // loop's (a batch, atoms uploaded since), so the request takes a
+            // smaller plan instead of waiting.
+            bool idle = true;
+            for (int s = 0; s < tfstat_ctx::kSlots; ++s) idle = idle && ctx->slot_tickets[s].empty();
+            auto shrink = [&] {
+                if (!idle || !plan_smaller(*t.job)) return false;
+                if (t.job->use_mfma) ensure_planes(ctx, t.job->at, t.job->prec);
+                return true;
+            };
             if (ctx->serve_max_batch > 1 && fusable(*t.job)) {
                 // the longest run of compatible requests at the head of the queue
                 std::vector<uint64_t> ids;
@@ -2259,7 +2269,10 @@ void worker_loop(tfstat_ctx *ctx) {
                         }
                         ids.pop_back();   // smaller batch
                     }
-                    if (!placed) break;   // wait for memory
+                    if (!placed) {
+                        if (shrink()) continue;
+                        break;   // wait for memory
+                    }
                     for (size_t i = 0; i < ids.size(); ++i) ctx->queue.pop_front();
                     popped = true;
                     hip_check(batch_enqueue(b.get(), ctx->slots[slot], false), "batch launch");
@@ -2296,9 +2309,14 @@ void worker_loop(tfstat_ctx *ctx) {
                 progressed = true;
                 continue;
             }
-            if (!alloc_job(ctx, *t.job)) break;  // wait for memory
-            ctx->queue.pop_front();
+            bool popped = false;
             try {
+                if (!alloc_job(ctx, *t.job)) {
+                    if (shrink()) continue;
+                    break;   // wait for memory
+                }
+                ctx->queue.pop_front();
+                popped = true;
                 enqueue_job(ctx, *t.job, ctx->slots[slot]);
                 ctx->slot_done[slot] = ctx->events.get();
                 hip_check(hipEventRecord(ctx->slot_done[slot], ctx->slots[slot]), "hipEventRecord");
@@ -2306,6 +2324,7 @@ void worker_loop(tfstat_ctx *ctx) {
                 t.slot = slot;
                 ctx->slot_tickets[slot] = {id};
             } catch (const Failure &f) {
+                if (!popped) ctx->queue.pop_front();
                 t.state = tfstat_ctx::Ticket::FAILED;
                 t.err = f.code;
                 t.msg = f.msg;

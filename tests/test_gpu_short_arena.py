@@ -1,5 +1,7 @@
 """GPU sliding maps where the arena cannot hold all anchors at once: more
 passes, the same numbers bit for bit."""
+import time
+
 import numpy as np
 import pytest
 
@@ -94,3 +96,34 @@ def test_one_map_of_a_batch_in_passes(roomy):
                     assert [got[0], got[1], got[3]] == [roomy[n, "fp64"][0] for n in (21, 1, 3)]
                 one = b.run(timed=True)
             assert one == got
+
+
+@pytest.mark.parametrize("max_batch", [1, 16])
+def test_served_request_beside_a_batch(roomy, max_batch):
+    """Requests that were admitted by the arena's size and meet a batch's
+    memory: they run in passes instead of waiting for what nobody gives back
+    (alone, and in fused admissions)."""
+    import paper_1805_05652_amd as tf
+    print("case: request beside a batch", flush=True)
+    atoms, win = _atoms_win(21)
+    rect = tfsynth.regular_window("rect", 3, T, 400, 2 * T, 3 * T, 330)
+    with tf.Context(0, arena_bytes=_atom_bytes(21) + (36 << 20)) as c:
+        aid = c.upload_atoms(atoms)
+        # rect maps take 3.4 MB each, the request 24 MB in one pass, 8 MB in three
+        with c.batch([(aid, rect)] * 6, "fp64") as b:
+            c.serve_config(max_batch)
+            tickets = [c.submit(aid, win, "fp64") for _ in range(3)]
+            got, end = {}, time.time() + 20
+            while len(got) < 3 and time.time() < end:
+                for t in tickets:
+                    if t not in got:
+                        r = c.poll(t, 21)
+                        if r is not None:
+                            got[t] = r
+                time.sleep(0.001)
+            for t in tickets:
+                if t not in got:
+                    c.cancel(t)
+            assert len(got) == 3, "requests wait for memory"
+            assert all(r == roomy[21, "fp64"][0] for r in got.values())
+            b.run()
