@@ -512,9 +512,12 @@ void plan_slide(Job &j) {
     j.range_len = rl;
     j.kbeg = std::min(std::max(j.rows[std::min<int32_t>(j.seg_rows, n_t0) - 1].k0, 0), at.K);
     const tfs::RowPlan &last = j.rows[n_t0 - 1];
-    for (tfs::SlideTile &t : j.tiles)
+    int32_t end = j.kbeg;
+    for (tfs::SlideTile &t : j.tiles) {
         t.kend = std::max(std::min(std::max(last.k0 + t.q1 + (t.r1 > last.delta ? 1 : 0), 0), at.K), j.kbeg);
-    j.n_sup = (int32_t)std::max<int64_t>(1, ((int64_t)at.K + rl * tfs::kSlideWaves - 1) / (rl * tfs::kSlideWaves));
+        end = std::max(end, t.kend);
+    }
+    j.n_sup = std::max<int32_t>(1, (end - j.kbeg + rl * tfs::kSlideWaves - 1) / (rl * tfs::kSlideWaves));
     j.n_range = j.n_sup * tfs::kSlideWaves;
 }
 

@@ -101,7 +101,17 @@ def test_slide_launch_limits(probe, prec, K, bins):
     t0 = [0, max(1, K // 2) * T, (K + 5) * T]
     p = probe("exp", prec, K, bins, t0, [T, K * T // 4 + 1, K * T])
     assert p["slide"] and p["range_len"] % 16 == 0 and p["n_sup"] <= 65535
-    assert p["range_len"] * 8 * p["n_sup"] >= K and p["n_range"] == 8 * p["n_sup"]
+    assert p["range_len"] * 8 * p["n_sup"] >= K - p["kbeg"] and p["n_range"] == 8 * p["n_sup"]
+
+
+def test_anchors_only_where_windows_end(probe):
+    """A few rows at the start of long data: anchors up to the last window's
+    end, not to the data's (0.9 GB)."""
+    p = probe("exp", "fp32", 16000000, 1, np.arange(200) * T, (2 + np.arange(64)) * T)
+    assert p["slide"] and p["ws"] < 1 << 20
+    last = probe("exp", "fp32", 16000000, 1, (15999800 + np.arange(200)) * T, (2 + np.arange(64)) * T)
+    assert last["slide"] and last["ws"] < 1 << 20
+    assert p["range_len"] * 8 * p["n_sup"] >= 200 + 3 * 66 - p["kbeg"]
 
 
 @pytest.mark.parametrize("bins,n_tau", [(1, 64), (1, 700), (4, 200), (9, 130), (64, 65), (256, 500), (3, 1)])
