@@ -427,10 +427,55 @@ void plan_rect(Job &j) {
     j.n_bg = (at.n_bins + j.bg - 1) / j.bg;
 }
 
+// Whether the direct sums of an exponential map planned for sliding take less
+// time.  Sliding costs the slots of the anchors (all from the first segment to
+// the last window's end, for every tau) and those between the rows, whatever the
+// windows' length; the direct sums cost the windows' slots.  Rows far apart in
+// long data with short windows are the direct sums': 200 rows over a million
+// slots, one bin, windows of 20 slots: 44 us against 457; 100 rows 80 slots
+// apart, 64 bins x 700 taus, windows of 20: 130 against 573; 40 rows together
+// every 500 slots, 64 bins, windows of 20: 203 against 627.  Windows of 2000
+// slots there: 2413, 1215 (10 rows) and 4229 against 605, 262 and 859.  Both
+// estimates in us, fitted to 495 such maps (each within a factor of two on nine
+// in ten of them); near the line the sliding sums, which are the more accurate.
+bool direct_is_cheaper(const Job &j) {
+    const AtomsSet &at = *j.at;
+    const int n_t0 = (int)j.win.t0.size(), n_tau = (int)j.win.tau.size();
+    // anchors; rows: instructions of all segments on the chip's SIMDs, or of
+    // the longest segment's wave alone
+    const double front = 13.0 + 4 * j.bg, back = 20.0 + 8 * j.bg;
+    double sum = 0.0, longest = 0.0;
+    for (int m = 0; m < n_t0; m += j.seg_rows) {
+        const int last = std::min(m + j.seg_rows, n_t0) - 1;
+        const double seg = 1000.0 + j.range_len * (front / 2 + back) + (45.0 + 27 * j.bg) * (last - m + 1) +
+                           (double)(j.rows[last].k0 - j.rows[m].k0) * (front + back);
+        sum += seg;
+        longest = std::max(longest, seg);
+    }
+    const double span = (double)j.n_sup * tfs::kSlideWaves * j.range_len;
+    const double rows = std::max(sum * j.n_tt * j.n_bg / (4 * kCus), 2.8 * longest);
+    const double slide = 31.0 + 62e-6 * j.n_tt * (j.n_bg + 1) * span + 0.18e-3 * j.n_sup + 3.6e-3 * rows;
+    // the longest window's chain of slots, or all windows' slots; cells
+    double slots = 0.0, chain = 0.0;
+    for (int n = 0; n < n_tau; ++n) {
+        const double L = (double)std::min<int64_t>(3 * j.win.tau[n] / at.t_sft, at.K);
+        slots += L;
+        chain = std::max(chain, L);
+    }
+    const bool one = at.n_bins == 1, f64 = j.prec == TFSTAT_PREC_FP64;
+    const bool matrix = matrix_prec(j.prec) && !one && chain >= kMfmaMinBandF16;
+    const double per_slot = f64 ? 0.3 : matrix ? 1.2 : one ? 0.1 : 0.22;
+    const double per_term = f64 ? 1.0e-6 : matrix ? 0.1e-6 : 0.35e-6;
+    const double direct = 48.0 + std::max(per_slot * chain, per_term * slots * n_t0 * at.n_bins) +
+                          (one ? 37e-6 : 18e-6) * (double)n_t0 * n_tau * at.n_bins;
+    return direct < 0.75 * slide;
+}
+
 // Sliding sums of an exponential map (kernels_slide.hip), from the map alone
 // (its results may not depend on what it is batched with).  They cost a
 // window's ends instead of its slots, so every map takes them whose atoms allow
-// it, unless the caller chose a tile form of the direct sums.
+// it, unless the caller chose a tile form of the direct sums or those take less
+// time (RECUR64 maps always slide).
 void plan_slide(Job &j) {
     const AtomsSet &at = *j.at;
     const bool tiling = j.runs_min_spread != kRunsAuto || j.split_min_bins != kSplitMinBins;
@@ -519,6 +564,7 @@ void plan_slide(Job &j) {
     }
     j.n_sup = std::max<int32_t>(1, (end - j.kbeg + rl * tfs::kSlideWaves - 1) / (rl * tfs::kSlideWaves));
     j.n_range = j.n_sup * tfs::kSlideWaves;
+    if (j.prec != TFSTAT_PREC_RECUR64 && direct_is_cheaper(j)) j.slide = false;
 }
 
 // Anchors of tts tau tiles x bgs bin groups, in bytes.

@@ -164,3 +164,27 @@ def test_smaller_plans_of_the_recurrence(probe):
     assert got[1]["passes"][0][1::2] == got[2]["passes"][0][1::2] == (1, 1)
     assert got[0]["ws"] > got[1]["ws"] > got[2]["ws"]
     assert got[4]["smaller"] == 3
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64", "f16x3", "recur64"])
+@pytest.mark.parametrize("case,direct", [("long_data", True), ("far_rows", True), ("clusters", True), ("far_rows_long", False),
+                                         ("clusters_long", False), ("two_rows_long", False), ("slots", False),
+                                         ("days30", False), ("small", False)])
+def test_sliding_where_it_is_cheaper(probe, case, direct, prec):
+    """Short windows of rows far apart in long data are summed directly, long
+    windows and rows near each other by sliding (the recurrence always)."""
+    K, bins, t0, L, n_tau = {
+        "long_data": (1000000, 1, np.arange(200) * 4999, 20, 64),
+        "far_rows": (8000, 64, np.arange(100) * 80, 20, 700),
+        "clusters": (8000, 64, np.concatenate([b + np.arange(40) for b in range(0, 8000, 500)]), 20, 300),
+        "far_rows_long": (8000, 64, np.arange(100) * 80, 2000, 700),
+        "clusters_long": (8000, 64, np.concatenate([b + np.arange(40) for b in range(0, 8000, 500)]), 2000, 300),
+        "two_rows_long": (8000, 4, np.array([0, 7000]), 2000, 300),
+        "slots": (2000, 256, np.arange(500), 1500, 500),
+        "days30": (5000, 1, np.arange(1000), 4320, 1000),
+        "small": (300, 2, np.arange(60) * 5, 20, 48)}[case]
+    tau = np.unique(np.linspace(2 * T, L * T / 3, n_tau).astype(np.int64))
+    p = probe("exp", prec, K, bins, t0 * T, tau)
+    if case == "clusters" and prec == "fp64":
+        return   # (its direct sums take three quarters of the sliding ones: near the line)
+    assert p["slide"] == (prec == "recur64" or not direct)
