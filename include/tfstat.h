@@ -359,9 +359,10 @@ int tfstat_tiling_config(tfstat_ctx *ctx, int32_t runs_min_spread, int32_t split
  *   n_maps     number of maps; ids[i] and wins[i] describe map i.
  *   precision  TFSTAT_PREC_FP32, TFSTAT_PREC_FP64, TFSTAT_PREC_BF16X3 or
  *              TFSTAT_PREC_F16X3 (exponential sums; rectangular windows
- *              always use compensated FP64 prefixes).  The sliding maps are
- *              two more launches after the persistent one, as is the
- *              matrix-core work of BF16X3 and F16X3 maps summed directly;
+ *              always use compensated FP64 prefixes).  The rect maps' tiles
+ *              and the sliding maps (three launches a pass) follow the
+ *              persistent launch, as does the matrix-core work of BF16X3 and
+ *              F16X3 maps summed directly;
  *              matrix-core shape windows are refused (E_INVAL; tfstat_fmap
  *              runs them).
  *   tune       0: each map's own tile shape, default launch width;
@@ -371,6 +372,9 @@ int tfstat_tiling_config(tfstat_ctx *ctx, int32_t runs_min_spread, int32_t split
  *              the fastest; the choice is cached in the context under the
  *              batch's shape signature and reused by later batches of the
  *              same shape.  Results are those of tfstat_fmap either way.
+ *              A batch without tiles for the persistent launch (all its maps
+ *              slide or are rect maps) has nothing to time and takes the
+ *              defaults.
  *              -1 - v: the fused-kernel variant v of tfstat_batch_stats
  *              (0 or 5 for FP64; 1..4 or 6..9 for FP32) at its widest
  *              launch, without the tuning cache; variants other than 0, 5

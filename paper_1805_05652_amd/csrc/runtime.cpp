@@ -22,6 +22,7 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <set>
 #include <string>
 #include <thread>
 #include <unordered_map>
@@ -945,6 +946,7 @@ struct tfstat_ctx {
     hipStream_t batch_stream = nullptr;
     int n_cu = 0;
     std::map<std::string, std::pair<int, int>> tuned;   // signature -> (variant, groups per CU)
+    std::set<std::string> tuned_none;                   // signatures of batches without persistent tiles
 };
 
 namespace {
@@ -2874,7 +2876,33 @@ int tfstat_batch_create(tfstat_ctx *ctx, int32_t n_maps, const tfstat_atoms_id *
                 found = true;
             }
         }
+        auto b = std::make_unique<tfstat_batch>();
+        b->prec = precision;
+        b->forced = tune < 0;
+        bool built = false;
         if (tune == 1 && !found) {
+            // No tile for the persistent kernel (every map slides or is a
+            // rect map): its builds and widths make no difference.
+            const auto t_start = std::chrono::steady_clock::now();
+            b->variant = variant;
+            try {
+                batch_build(ctx, b.get(), n_maps, ids, wins);
+            } catch (...) {
+                batch_release(ctx, b.get());
+                throw;
+            }
+            built = b->fp.n_tiles == 0;
+            if (built) {
+                std::lock_guard<std::mutex> g(ctx->mu);
+                if (ctx->tuned_none.insert(sig).second)
+                    tune_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
+            } else {
+                batch_release(ctx, b.get());
+                b = std::make_unique<tfstat_batch>();
+                b->prec = precision;
+            }
+        }
+        if (tune == 1 && !found && !built) {
             // Autotuner: each build that keeps the maps' own tile shapes x
             // every persistent width that fits; the fastest of three graph
             // replays after one warm-up counts.
@@ -2916,15 +2944,12 @@ int tfstat_batch_create(tfstat_ctx *ctx, int32_t n_maps, const tfstat_atoms_id *
             ctx->tuned[sig] = {variant, per_cu};
         }
         if (per_cu < 1) per_cu = tfs::fused_groups_per_cu(variant);
-        if (per_cu < 1) raise(TFSTAT_E_DEVICE, "fused kernel does not fit on a CU");
-        auto b = std::make_unique<tfstat_batch>();
-        b->prec = precision;
         b->variant = variant;
-        b->forced = tune < 0;
         b->groups = per_cu * ctx->n_cu;
         b->tune_ms = tune_ms;
         try {
-            batch_build(ctx, b.get(), n_maps, ids, wins);
+            if (per_cu < 1) raise(TFSTAT_E_DEVICE, "fused kernel does not fit on a CU");
+            if (!built) batch_build(ctx, b.get(), n_maps, ids, wins);
             batch_capture(ctx, b.get());
         } catch (...) {
             batch_release(ctx, b.get());
