@@ -1577,8 +1577,8 @@ __global__ __launch_bounds__(kThreads, (fused_waves<V, M>())) void fused_kernel(
 // takes kMapChunk cells at a time against one maximum, so that they are
 // independent and without branches, and exp(x) = 2^(j / 64) e^r 2^i with a table
 // of the 64 powers and r = x - (64 i + j) ln 2 / 64, |r| <= 0.0055, by its
-// Taylor series to r^5 (r^6 / 720 < 4e-17).  Chunks with a NaN or with cells too
-// far below the maximum for a normal power go cell by cell.  128 maps x 500 x
+// Taylor series to r^5 (r^6 / 720 < 4e-17).  Chunks with a NaN or +inf go cell
+// by cell, chunks of nothing but -inf are passed over.  128 maps x 500 x
 // 500: 89 us with a branch and a library exponential per cell, 46 us now (63 us
 // on workgroups of sixteen waves, each with its table and reduction).
 // ---------------------------------------------------------------------------
@@ -1588,43 +1588,51 @@ constexpr int kMapThreads = 256;
 __global__ __launch_bounds__(kMapThreads) void map_reduce_kernel(MapReduceParams p) {
     __shared__ Partial wred[kMapThreads / 64];
     __shared__ double pow2[64];
-    if (threadIdx.x < 64) pow2[threadIdx.x] = exp2((double)threadIdx.x * 0x1p-6);
-    __syncthreads();
     const int map = blockIdx.y;
     const int tile = blockIdx.x;
     const int64_t c0 = (int64_t)tile * p.cells_per_tile;
     const int64_t c1 = min(p.n_cells, c0 + p.cells_per_tile);
+    if (c1 - c0 > kMapThreads * (kMapChunk - 1)) {   // (some thread has a whole chunk)
+        if (threadIdx.x < 64) pow2[threadIdx.x] = exp2((double)threadIdx.x * 0x1p-6);
+        __syncthreads();
+    }
     const float *src = p.twoF + (size_t)map * p.n_cells;
     Red r = red_empty();
     for (int64_t c = c0 + threadIdx.x; c < c1; c += kMapThreads * kMapChunk) {
         float v[kMapChunk];
+        double f = 0.0, sum = 0.0;
+        bool whole = false;
+        float hi = 0.f;
+        if (c + kMapThreads * (kMapChunk - 1) < c1) {
 #pragma unroll
-        for (int u = 0; u < kMapChunk; ++u) v[u] = src[min(c + kMapThreads * u, c1 - 1)];
-        float hi = v[0], lo = v[0];
+            for (int u = 0; u < kMapChunk; ++u) v[u] = src[c + kMapThreads * u];
+            float all = v[0];
+            hi = v[0];
 #pragma unroll
-        for (int u = 1; u < kMapChunk; ++u) {
-            hi = fmaxf(hi, v[u]);
-            lo = fminf(lo, v[u]);
+            for (int u = 1; u < kMapChunk; ++u) {
+                hi = fmaxf(hi, v[u]);
+                all += v[u];   // NaN if a cell is, or for both infinities
+            }
+            if (hi == -INFINITY && all == all) continue;
+            f = fmax(r.f, 0.5 * (double)hi);
+#pragma unroll
+            for (int u = 0; u < kMapChunk; ++u) {
+                // (below e^-700 a cell adds nothing to a sum that holds the maximum's 1)
+                const double x = fmax(fma(0.5, (double)v[u], -f), -700.0);
+                const double n = rint(x * 92.33248261689366);   // 64 / ln 2
+                double e = fma(n, -0.010830424696249145, x);     // ln 2 / 64, and what it lacks
+                e = fma(n, -3.623510646634843e-19, e);
+                double q = fma(e, 1.0 / 120.0, 1.0 / 24.0);
+                q = fma(q, e, 1.0 / 6.0);
+                q = fma(q, e, 0.5);
+                q = fma(q, e, 1.0);
+                q = q * e;
+                const int i = (int)n;
+                const double t = pow2[i & 63];
+                sum += ldexp(fma(t, q, t), i >> 6);
+            }
+            whole = all == all && f < INFINITY;
         }
-        const double f = fmax(r.f, 0.5 * (double)hi);
-        double sum = 0.0;
-#pragma unroll
-        for (int u = 0; u < kMapChunk; ++u) {
-            const double x = fma(0.5, (double)v[u], -f);
-            const double n = rint(x * 92.33248261689366);   // 64 / ln 2
-            double e = fma(n, -0.010830424696249145, x);     // ln 2 / 64, and what it lacks
-            e = fma(n, -3.623510646634843e-19, e);
-            double q = fma(e, 1.0 / 120.0, 1.0 / 24.0);
-            q = fma(q, e, 1.0 / 6.0);
-            q = fma(q, e, 0.5);
-            q = fma(q, e, 1.0);
-            q = q * e;
-            const int i = (int)n;
-            const double t = pow2[i & 63];
-            sum += ldexp(fma(t, q, t), i >> 6);
-        }
-        // (a NaN: sum is not a number; an infinity: the range is not finite)
-        const bool whole = c + kMapThreads * (kMapChunk - 1) < c1 && f - 0.5 * (double)lo < 700.0 && sum == sum;
         if (whole) {
             if (f > r.f) {
                 r.s = r.f == -INFINITY ? 0.0 : r.s * exp(r.f - f);
