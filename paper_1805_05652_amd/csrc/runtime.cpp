@@ -456,20 +456,19 @@ bool direct_is_cheaper(const Job &j) {
     const double span = (double)j.n_sup * tfs::kSlideWaves * j.range_len;
     const double rows = std::max(sum * j.n_tt * j.n_bg / (4 * kCus), 2.8 * longest);
     const double slide = 31.0 + 62e-6 * j.n_tt * (j.n_bg + 1) * span + 0.18e-3 * j.n_sup + 3.6e-3 * rows;
-    // the longest window's chain of slots, or all windows' slots; cells
-    double slots = 0.0, chain = 0.0;
-    for (int n = 0; n < n_tau; ++n) {
-        const double L = (double)std::min<int64_t>(3 * j.win.tau[n] / at.t_sft, at.K);
-        slots += L;
-        chain = std::max(chain, L);
-    }
+    // cells; the longest window's chain of slots, or all windows' slots (looked
+    // at last: a division a tau)
+    auto slots_of = [&](int64_t tau) { return (double)std::min<int64_t>(3 * tau / at.t_sft, at.K); };
+    const double chain = slots_of(j.win.tau[n_tau - 1]);
     const bool one = at.n_bins == 1, f64 = j.prec == TFSTAT_PREC_FP64;
     const bool matrix = matrix_prec(j.prec) && !one && chain >= kMfmaMinBandF16;
     const double per_slot = f64 ? 0.3 : matrix ? 1.2 : one ? 0.1 : 0.22;
     const double per_term = f64 ? 1.0e-6 : matrix ? 0.1e-6 : 0.35e-6;
-    const double direct = 48.0 + std::max(per_slot * chain, per_term * slots * n_t0 * at.n_bins) +
-                          (one ? 37e-6 : 18e-6) * (double)n_t0 * n_tau * at.n_bins;
-    return direct < 0.75 * slide;
+    const double cells = 48.0 + (one ? 37e-6 : 18e-6) * (double)n_t0 * n_tau * at.n_bins;
+    if (cells + per_slot * chain >= 0.75 * slide) return false;
+    double slots = 0.0;
+    for (int64_t tau : j.win.tau) slots += slots_of(tau);
+    return cells + per_term * slots * n_t0 * at.n_bins < 0.75 * slide;
 }
 
 // Sliding sums of an exponential map (kernels_slide.hip), from the map alone
