@@ -12,15 +12,15 @@ its window, truncated at the data end (the paper's N_sums of appendix A,
 eq. Nsums-exp, counted over present SFTs).
 
 The same JSON line also carries, unless --no-extras:
-  exp_256_bins   256 bins sharing one set of antenna atoms, split hi + lo
-                 half-precision (f16x3) and bf16 (bf16x3) parts on matrix
-                 cores against FP32 (sliding windows), each with its 2F error
-                 against the oracle on sampled cells;
-  uneven_batch   64 uneven candidates as one batch (one captured graph, one
-                 persistent fused launch, the matrix-core launch) in FP32,
-                 F16X3 and BF16X3, against one map per call;
+  exp_256_bins   256 bins sharing one set of antenna atoms in FP32, F16X3 and
+                 BF16X3 (all by sliding windows in FP64, so they differ by
+                 nothing but the request), each with its 2F error against the
+                 oracle on sampled cells;
+  uneven_batch   64 uneven candidates as one batch (one captured graph: prefix
+                 sums, rect tiles, sliding windows, merges) in FP32, F16X3 and
+                 BF16X3, against one map per call;
   serving        a Poisson request stream (F16X3 requests) with continuous
-                 batching, p50/p99, a load ramp and the sequential plain FP32
+                 batching, p50/p99, a load ramp and the sequential FP32
                  baseline;
   cpu_baseline   the FP64 oracle on the host cores (all threads and one).
 
@@ -100,19 +100,6 @@ def mfma_cells(atoms, win, prec="bf16x3"):
         return 0
     sub = tfsynth.Window(win.kind, win.t0, win.tau[keep])
     return work_counts(atoms, sub)[0]
-
-
-def split_form(atoms, win, prec):
-    """Whether the library plans this exponential map in the split form (A/B/C
-    pass, then F_a, F_b only): FP32, at least 8 bins, and a median slot span
-    of its 64-row tiles within the band stage (448 slots) -- the library's
-    default rule, restated to count the fused kernel's own flops."""
-    if prec != "fp32" or atoms.n_bins < 8:
-        return False
-    T0 = int(atoms.timestamps[0])
-    k0 = np.minimum(-(-(win.t0 - T0) // atoms.t_sft), atoms.n_slots)
-    spans = [int(k0[min(s + 63, len(k0) - 1)] - k0[s]) for s in range(0, len(k0), 64)]
-    return sorted(spans)[len(spans) // 2] <= 448
 
 
 def work_counts(atoms, win):
@@ -307,7 +294,7 @@ def serving(ctx, seed: int = 4000, rate_hz: float = 200.0, duration_s: float = 1
     sp50, sp99 = _percentiles(seq_lat)
     return {
         "requests": len(jobs), "offered_rate_hz": rate_hz, "duration_s": duration_s,
-        "precision": precision, "admission": "continuous batching, up to 16 requests per fused launch",
+        "precision": precision, "admission": "continuous batching, up to 16 requests per admission",
         "maps_per_s": len(jobs) / wall,
         "bin_maps_per_s": sum(j[3] for j in jobs) / wall,
         "p50_ms": p50, "p99_ms": p99, "tail_samples_above_p99": int((lat > p99).sum()),
@@ -459,10 +446,9 @@ def time_map(ctx, aid, atoms, win, prec, twoF, steps, warmup, workload):
 
 def bench_exp256(args, tf, torch):
     """256 frequency bins sharing one set of antenna atoms (2000 slots, 10%
-    gaps, 500 x 500 grid, map written): the batched mixed-precision forms
-    (split hi + lo half-precision or bf16 parts on matrix cores, FP32
-    accumulation, A/B/C/D in FP64) against FP32 (sliding windows), each
-    with its largest 2F error against the FP64 oracle on sampled cells."""
+    gaps, 500 x 500 grid, map written) in FP32, F16X3 and BF16X3 (all by
+    sliding windows in FP64), each with its largest 2F error against the FP64
+    oracle on sampled cells."""
     atoms, win = tfsynth.workload_exp_bins()
     present, slots = work_counts(atoms, win)
     ctx = tf.Context(0, arena_bytes=2 << 30)
@@ -488,10 +474,9 @@ def bench_exp256(args, tf, torch):
 def bench_batch(args, tf, torch, prec):
     """The uneven batch: 64 follow-up candidates (slots log-uniform in
     [500, 8000], gaps U[0, 0.3], grids U{100..1500}^2, 1..16 bins, rect and
-    exp alternating) as one planned batch -- one captured graph with one
-    persistent fused launch per step (and, in F16X3 / BF16X3, one matrix-core
-    launch for the exponential maps of 2 or more bins) -- against the same
-    maps computed one map per call.  Returns the record of the step."""
+    exp alternating) as one planned batch -- one captured graph per step --
+    against the same maps computed one map per call.  Returns the record of
+    the step."""
     cands = [tfsynth.candidate(i) for i in range(64)]
     exp_present = exp_slots = rect_cells = 0
     slide = 0.0          # flops of the exponential maps by sliding windows
@@ -521,12 +506,12 @@ def bench_batch(args, tf, torch, prec):
         t1 = time.perf_counter()
     st = batch.stats()
     ms = (t1 - t0) * 1e3 / args.steps
-    # the fused kernel alone, timed with HIP events on its stream (direct
-    # launches)
-    fused = []
+    # the rect tiles alone (between the events around the persistent launch,
+    # which these maps leave empty, and the rect launch), direct launches
+    rect = []
     for _ in range(3):
         timed = batch.run(timed=True)
-        fused.append(batch.stats()["last_fused_ms"])
+        rect.append(batch.stats()["last_fused_ms"])
     # one map per call: the same maps, sequentially, plain launches
     for aid, w in items[:4]:
         ctx.fmap(aid, w, prec)
@@ -547,14 +532,13 @@ def bench_batch(args, tf, torch, prec):
         err = max(err, e)
         n_cmp += n * a.n_bins
         del twoF
-    fused_ms = float(np.mean(fused))
-    # the fused kernel's own flops: about 30 FP64 flops per rect cell*bin
+    rect_ms = float(np.mean(rect))
+    # about 30 FP64 flops per rect cell*bin
     flops = 30.0 * rect_cells
-    roof_f = {"bound": "alu", "achieved": flops / (fused_ms * 1e-3) / 1e12, "peak": PEAK_ALU_TFLOPS,
-              "unit": "TFLOP/s", "kernel": "fused", "kernel_avg_ms": fused_ms,
-              "traffic": traffic_from_profile("batch_" + prec, "fused", st["variant"])}
-    roof_f["frac"] = roof_f["achieved"] / roof_f["peak"]
-    roof = roof_f
+    roof_r = {"bound": "alu", "achieved": flops / (rect_ms * 1e-3) / 1e12, "peak": PEAK_ALU_TFLOPS,
+              "unit": "TFLOP/s", "kernel": "rect_batch", "kernel_avg_ms": rect_ms, "traffic": None}
+    roof_r["frac"] = roof_r["achieved"] / roof_r["peak"]
+    roof = roof_r
     out = {
         "workload": "uneven batch: 64 candidates, 32 exp + 32 rect maps, 1-16 bins",
         "value": exp_present / (ms * 1e-3), "unit": "cells*SFTs*bins/s", "ms_per_step": ms,
@@ -576,7 +560,7 @@ def bench_batch(args, tf, torch, prec):
         roof = {"bound": "alu", "achieved": total / (st["last_ms"] * 1e-3) / 1e12, "peak": PEAK_ALU_TFLOPS,
                 "unit": "TFLOP/s", "kernel": "step", "kernel_avg_ms": st["last_ms"], "traffic": None}
         roof["frac"] = roof["achieved"] / roof["peak"]
-        out["roofline_fused"] = roof_f
+        out["roofline_rect"] = roof_r
     out["roofline"] = roof
     batch.close()
     for aid in ids:
