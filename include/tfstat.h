@@ -85,9 +85,11 @@ typedef enum {
  *            the named precision as described here, are: atoms with non-finite
  *            values or whose data spread too far (a 64-slot stretch of a column
  *            more than 2^20 below the column's largest value, or one slot more
- *            than 2^26 below the bin's; FP64: 2^10 and 2^18), maps whose anchors
- *            of one pass do not fit where the direct sums do, and maps planned
- *            under an explicit tfstat_tiling_config.
+ *            than 2^26 below the bin's; FP64: 2^10 and 2^18), maps of short
+ *            windows with rows far apart (where the direct sums take less
+ *            time; not RECUR64), maps whose anchors of one pass do not fit
+ *            where the direct sums do, and maps planned under an explicit
+ *            tfstat_tiling_config.
  *   BF16X3 : F_a, F_b sums on bf16 matrix cores with split hi + lo operands
  *            (three products: hi*hi + hi*lo + lo*hi) and FP32 accumulation
  *            (section 3, exponential case: every cell is one banded

@@ -1579,7 +1579,7 @@ __global__ __launch_bounds__(kThreads, (fused_waves<V, M>())) void fused_kernel(
 // of the 64 powers and r = x - (64 i + j) ln 2 / 64, |r| <= 0.0055, by its
 // Taylor series to r^5 (r^6 / 720 < 4e-17).  Chunks with a NaN or +inf go cell
 // by cell, chunks of nothing but -inf are passed over.  128 maps x 500 x
-// 500: 89 us with a branch and a library exponential per cell, 46 us now (63 us
+// 500: 89 us with a branch and a library exponential per cell, 43 us now (63 us
 // on workgroups of sixteen waves, each with its table and reduction).
 // ---------------------------------------------------------------------------
 constexpr int kMapChunk = 8;

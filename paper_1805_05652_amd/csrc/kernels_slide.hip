@@ -359,14 +359,18 @@ __device__ __attribute__((always_inline)) inline void slide_supers(PP &p, int tt
 }
 
 // ---------------------------------------------------------------------------
-// Rows.  Bound by VALU issue: a row of a wave of four bins is about 220
-// instructions plus 30 a front and 50 a back slot, nearly all FP64 (counters at
-// 256 bins x 500 x 500: VALU busy 77 %, 250 instructions a row).  What it took
-// to get there: G changed in place (branches around its update cost a move of
-// all its registers a row), four waves per SIMD, the first front slot and the
-// next row's plan loaded a row ahead, back slots from LDS.  Rows kernel at 64
-// bins x 611 x 703 on 3001 slots: 464 us with the back slots through the
-// caches, 268 us staged, 196 us now; 256 bins x 500 x 500: 481, 340, 199 us.
+// Rows.  Bound by VALU issue where segments are long: a row of a wave of four
+// bins is about 220 instructions plus 30 a front and 50 a back slot, nearly all
+// FP64 (counters at 256 bins x 500 x 500: VALU busy 77 %, 250 instructions a
+// row).  Short segments wait for their starts and, with taus far apart, for the
+// back slots' LDS reads (64 bins x 611 x 703: VALU busy 56 %, half of the LDS
+// cycles in conflicts; one bin x 1000 x 1000 54 %; a mixed batch of 24 43 %).
+// What it took to get there: G changed in place (branches around its update
+// cost a move of all its registers a row), four waves per SIMD, the first front
+// slot and the next row's plan loaded a row ahead, back slots from LDS.  Rows
+// kernel at 64 bins x 611 x 703 on 3001 slots: 464 us with the back slots
+// through the caches, 268 us staged, 196 us now; 256 bins x 500 x 500: 481, 340,
+// 199 us.
 // ---------------------------------------------------------------------------
 // The segment's rows, from the last down, on one wave.  STAGED: the back slots
 // are in LDS from slot w_lo on.

@@ -2179,8 +2179,8 @@ void ensure_batch_stream(tfstat_ctx *ctx) {
 // requests at the head of the queue are admitted together -- up to
 // serve_max_batch of them, as many as the arena can hold -- and run as one
 // fused batch (one persistent launch over all their tiles) on that slot;
-// requests that the fused kernel does not cover (matrix-core and recurrence
-// precisions) and large requests run alone.  Up to kSlots admissions are in
+// requests that no batch covers (the recurrence, matrix-core shape windows) and
+// large requests run alone.  Up to kSlots admissions are in
 // flight at once, so
 // requests arriving while others run overlap with them on the device.  A
 // request's results do not depend on what it was batched with.

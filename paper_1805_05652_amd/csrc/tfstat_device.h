@@ -219,9 +219,9 @@ struct ShiftTableParams {
 // range_len slots (kSlideWaves ranges make a super-range).
 constexpr int kSlideWaves = 8;
 // The rows kernel: up to kRowsWaves segments per workgroup (four waves per
-// SIMD; the FP32 maps' 25 spilled registers cost less than a fourth wave
-// gives: 193 against 256 us at 256 bins), the back slots they drop staged in
-// LDS.
+// SIMD; the spilled registers of four-bin groups, 12 now and 24 when it was
+// measured, cost less than a fourth wave gives: 193 against 256 us at 256 bins),
+// the back slots they drop staged in LDS.
 constexpr int kRowsWaves = 16;
 constexpr unsigned kSlideStageBytes = 160 * 1024;
 inline unsigned slide_stage_bytes(int bg, int stage) { return (24u + 16u * bg) * (unsigned)(stage + 1); }
@@ -543,11 +543,11 @@ hipError_t launch_exp_valu(const ExpValuParams &p, int prec, int R, int BG, int 
 // their runs tiles as bin pairs).
 hipError_t launch_exp_runs(const ExpValuParams &p, int prec, int R, int BG, int n_groups,
                            hipStream_t s);
-// A/B/C only (FP64), R = 8 blocks, into p.abc_out.
 // F_a, F_b only, R = 8 blocks, four bins per lane, n_groups bin groups from
-// p.bin_base; A, B, C of every cell read from p.abc_out (short-band blocks
-// of the matrix-core form).
+// p.bin_base; A, B, C of every cell read from p.abc_out (the split form, and
+// short-band blocks of the matrix-core form).
 hipError_t launch_exp_fonly(const ExpValuParams &p, int n_groups, hipStream_t s);
+// A/B/C only (FP64), R = 8 blocks, into p.abc_out.
 hipError_t launch_exp_abc(const ExpValuParams &p, hipStream_t s);
 hipError_t launch_exp_mfma(const ExpMfmaParams &p, hipStream_t s);
 hipError_t launch_exp_mfma_rows(const ExpMfmaRowsParams &p, hipStream_t s);
