@@ -395,11 +395,12 @@ typedef struct {
                                  when built for one wave per SIMD fewer than the
                                  stand-alone kernel (more registers per wave) */
     int32_t groups;           /* persistent workgroups of the fused launch */
-    int32_t n_tiles;          /* tiles in the shared list */
+    int32_t n_tiles;          /* tiles of the persistent launch and of the rect maps */
     int32_t n_results;        /* sum of n_bins over the maps */
     double tune_ms;           /* host time spent tuning (0 if not tuned here) */
     double last_ms;           /* device time of the last run (HIP events) */
-    double last_fused_ms;     /* device time of the fused launch in the last timed run */
+    double last_fused_ms;     /* device time of the persistent launch and the rect tiles in
+                                 the last timed run */
     double last_mfma_ms;      /* device time of the matrix-core launches of BF16X3 / F16X3
                                  maps in the last timed run (0 without such maps) */
 } tfstat_batch_stats;

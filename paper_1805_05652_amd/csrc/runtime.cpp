@@ -847,7 +847,7 @@ bool plan_smaller(Job &j) {
     }
     const size_t now = j.ws_bytes;
     const bool last = j.pass_tt == 1 && j.pass_bg == 1;
-    const size_t kept = now - anchor_bytes(j, j.pass_tt, j.pass_bg);   // (and up to 1 KB of padding)
+    const size_t kept = now - anchor_bytes(j, j.pass_tt, j.pass_bg) + 1024;   // (the most that padding can add)
     if (j.prec == TFSTAT_PREC_RECUR64) {
         if (last)
             ++j.no_slide;
