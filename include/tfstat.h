@@ -113,7 +113,9 @@ typedef enum {
  *            has a block of 8 taus with every band at least 64 slots long,
  *            the blocks whose shortest band is at least 24 slots run on the
  *            matrix cores (shorter windows amplify the parts' rounding).
- *            Builds its own planes on first use (16 bytes per slot and bin;
+ *            Atoms whose data spread over more than 2^20 (a 64-slot stretch
+ *            of a column, or one slot of a bin) run the FP32 sums: the parts
+ *            would lose the weaker values.  Builds its own planes on first use (16 bytes per slot and bin;
  *            sets of 2 to 48 bins 32 more).
  *   RECUR64: exponential windows: every sum in FP64 by the exact recurrence
  *            of the window sums from one t0 to the next (the sliding windows

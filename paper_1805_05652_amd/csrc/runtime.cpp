@@ -172,6 +172,7 @@ struct AtomsSet {
     // to maps in double precision), whether x32 holds x64 exactly, and the
     // largest a^2 and b^2
     bool slide_ok = false, slide_ok64 = false, exact32 = false;
+    bool half_ok = false;   // half-precision parts hold every column to about 2^-16 (F16X3, directly)
     double amax = 0.0, bmax = 0.0;
     // bf16 hi / lo planes for the matrix-core path, built on first use
     void *planes = nullptr;
@@ -654,7 +655,8 @@ void plan_job(Job &j) {
         } else {
             const int64_t bins16 = (at.n_bins + 15) / 16 * 16;
             const int64_t kp = ((int64_t)at.K + 31) / 32 * 32 + 32;
-            ok = at.n_bins >= kMfmaMinBins && bins16 * kp * 2 < ((int64_t)1 << 31);
+            ok = at.n_bins >= kMfmaMinBins && bins16 * kp * 2 < ((int64_t)1 << 31) &&
+                 (j.prec != TFSTAT_PREC_F16X3 || at.half_ok);
             if (tfs::mfma_cells_form((int)(bins16 / 16)))
                 ok = ok && (int64_t)8 * tfs::kCellsCopies * at.n_bins * tfs::cells_plane_pitch(at.K) <
                                ((int64_t)1 << 31);
@@ -1486,11 +1488,14 @@ void ensure_planes(tfstat_ctx *ctx, AtomsSet *at, int32_t prec) {
 // columns together; windows may be that short) not under 2^-26 of the bin's;
 // for double precision a stretch not under 2^-10 and a slot not under 2^-18.
 // (A slot of Gaussian noise falls below 2^-18 of the largest with a chance of
-// 2e-10.)
+// 2e-10.)  Half-precision parts, scaled to a column's largest value, reach 2^-38
+// of it: direct F16X3 sums of data that spread over more than 2^20 are off by
+// 1e-4 and more (2F off by 2e-3 at 2^24, by 0.2 at 2^30), so those maps take the
+// FP32 sums (6e-6 at any spread).
 void set_ranges(AtomsSet &at, const tfs::RangeInfo *info) {
     const int groups = tfs::atom_groups(at.n_bins), chunks = tfs::atom_chunks(at.K, at.n_bins);
     at.slide_ok = at.slide_ok64 = ((int64_t)at.K + 1) * at.n_bins * 32 < ((int64_t)1 << 31);
-    at.exact32 = true;
+    at.exact32 = at.half_ok = true;
     for (int g = 0; g < groups; ++g) {
         const bool ant = g == groups - 1;
         const int nb = ant ? 1 : std::min(at.n_bins - g * tfs::kAtomBins, tfs::kAtomBins);
@@ -1522,8 +1527,12 @@ void set_ranges(AtomsSet &at, const tfs::RangeInfo *info) {
             } else {
                 const double top = *std::max_element(most, most + 4);
                 for (int c = 0; c < 4; ++c)
-                    if (least[c] < most[c] * 0x1p-20) at.slide_ok = false;
+                    if (least[c] < most[c] * 0x1p-20) {
+                        at.slide_ok = false;
+                        if (std::isfinite(most[c])) at.half_ok = false;
+                    }
                 if (slot < top * 0x1p-26) at.slide_ok = false;
+                if (std::isfinite(top) && slot < top * 0x1p-20) at.half_ok = false;
                 if (joint < top * 0x1p-10 || slot < top * 0x1p-18) at.slide_ok64 = false;
             }
         }

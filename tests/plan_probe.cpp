@@ -18,6 +18,7 @@ int main() {
         at.t_sft = T;
         at.slide_ok = at.slide_ok64 = (K + 1) * bins * 32 < ((int64_t)1 << 31);
         at.exact32 = exact32 != 0;
+        at.half_ok = true;
         at.amax = at.bmax = 1.0;
         Job j;
         j.at = &at;

@@ -165,3 +165,36 @@ def test_atoms_that_do_not_slide(_open, prec, n_bins):
     finally:
         c.profile(False)
         c.free(aid)
+
+
+@pytest.mark.parametrize("shift", [17, 22, 26, 30, 40])
+@pytest.mark.parametrize("case", ["one_slot", "every_fiftieth", "stretch"])
+@pytest.mark.parametrize("prec", ["f16x3", "bf16x3"])
+def test_strong_data_by_direct_sums(_open, prec, case, shift):
+    """Slots 2^17 to 2^40 above the others, under the default plans and under
+    an explicit tiling, bands long enough for the matrix cores: every cell to the
+    precision's bound relative to max(2F, 1), also where the windows hold none
+    of the strong slots."""
+    print("case: strong data %s %s 2^%d" % (prec, case, shift), flush=True)
+    c = _open
+    base = tfsynth.make_atoms(9995, 900, 0.1, n_bins=5)
+    at = {"one_slot": slice(400, 401), "every_fiftieth": slice(3, None, 50), "stretch": slice(300, 364)}[case]
+    fa, fb = base.fa.copy(), base.fb.copy()
+    fa[:, at] *= 2.0 ** shift
+    fb[:, at] *= 2.0 ** shift
+    atoms = dataclasses.replace(base, fa=fa, fb=fb)
+    # (every fiftieth: also windows that fit between two strong slots)
+    tau = np.arange(T // 2, 30 * T, T // 2) if case == "every_fiftieth" else np.arange(9, 129, 2) * T
+    win = tfsynth.list_window("exp", np.arange(880) * T, tau)
+    ref = oracle.fmap_atoms(atoms, win)
+    aid = c.upload_atoms(atoms)
+    try:
+        for tiling in ((-1, -1), (DENSE, -1)):
+            c.tiling_config(*tiling)
+            res, twoF = c.fmap(aid, win, prec, want_map=True)
+            check_map(twoF.cpu().numpy(), ref, TOL[prec])
+            with c.batch([(aid, win)], prec) as b:
+                assert b.run() == [res]
+    finally:
+        c.tiling_config(-1, -1)
+        c.free(aid)
