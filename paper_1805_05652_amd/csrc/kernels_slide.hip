@@ -698,8 +698,8 @@ __device__ __attribute__((always_inline)) inline void slide_rows(PP &p, double *
 // ---------------------------------------------------------------------------
 // v over the n (a power of two) lanes that lie `stride` apart around this one,
 // `at` its place among them.
-template <typename Op>
-__device__ __attribute__((always_inline)) inline double ring(double v, int lane, int stride, int at, int n, Op op) {
+template <typename T, typename Op>
+__device__ __attribute__((always_inline)) inline T ring(T v, int lane, int stride, int at, int n, Op op) {
     const int first = lane - at * stride;
     for (int o = n / 2; o > 0; o >>= 1) v = op(v, __shfl(v, first + ((at + o) & (n - 1)) * stride, 64));
     return v;
@@ -713,6 +713,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x6
     __shared__ int sflags;
     auto larger = [](double x, double y) { return fmax(x, y); };
     auto smaller = [](double x, double y) { return fmin(x, y); };
+    auto sum = [](int x, int y) { return x + y; };
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const bool ant = blockIdx.x == gridDim.x - 1;
     const int b0 = ant ? 0 : blockIdx.x * kAtomBins;
@@ -748,6 +749,7 @@ __global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x6
             v[i][3] = on ? u1.y : 0.0;
         }
         double m[4] = {0.0, 0.0, 0.0, 0.0};
+        int n_sft = 0;   // slots with data
 #pragma unroll
         for (int i = 0; i < kSlots; ++i) {
             const int k = kb + i * kAtomLanes;
@@ -766,15 +768,20 @@ __global__ __launch_bounds__(64 * kAtomWaves) void atoms_kernel(const double *x6
             }
             const double all = fmax(fmax(fabs(v[i][0]), fabs(v[i][1])), fmax(fabs(v[i][2]), fabs(v[i][3])));
             if (all > 0.0) slot = fmin(slot, all);
+            n_sft += all > 0.0;
         }
+        // (a stretch of a few SFTs has no level of its own: of one SFT's values
+        // three in a million lie 2^-20 below their column's largest by chance,
+        // which is one a map where 256 bins have hundreds of such stretches)
+        const bool counts = ring(n_sft, lane, W, s8, kAtomLanes, sum) >= kAtomSfts;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             m[c] = ring(m[c], lane, W, s8, kAtomLanes, larger);   // the stretch's
             mx[c] = fmax(mx[c], m[c]);
-            if (m[c] > 0.0) mn[c] = fmin(mn[c], m[c]);
+            if (counts && m[c] > 0.0) mn[c] = fmin(mn[c], m[c]);
         }
         const double all = fmax(fmax(m[0], m[1]), fmax(m[2], m[3]));
-        if (all > 0.0) joint = fmin(joint, all);
+        if (counts && all > 0.0) joint = fmin(joint, all);
     }
     if (!ant && blockIdx.y == 0 && threadIdx.x < W) {   // row K is zero
         const float4 z = {0.f, 0.f, 0.f, 0.f};

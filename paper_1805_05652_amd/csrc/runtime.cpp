@@ -1486,7 +1486,8 @@ void ensure_planes(tfstat_ctx *ctx, AtomsSet *at, int32_t prec) {
 // slots after it, so the data must not spread too far: a 64-slot stretch of a
 // column not under 2^-20 of the column's largest value, a single slot (of all
 // columns together; windows may be that short) not under 2^-26 of the bin's;
-// for double precision a stretch not under 2^-10 and a slot not under 2^-18.
+// for double precision a stretch not under 2^-10 and a slot not under 2^-18
+// (stretches of fewer than kAtomSfts SFTs are judged by their slots alone).
 // (A slot of Gaussian noise falls below 2^-18 of the largest with a chance of
 // 2e-10.)  Half-precision parts, scaled to a column's largest value, reach 2^-38
 // of it: direct F16X3 sums of data that spread over more than 2^20 are off by

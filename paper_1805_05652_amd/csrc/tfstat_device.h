@@ -277,6 +277,7 @@ struct SlideBatchParams {
 // bins (the last group: the antenna, a^2, b^2, ab and an unused column) and
 // chunk of 64-slot stretches.
 constexpr int kAtomBins = 8, kAtomWaves = 16, kAtomLanes = 8;
+constexpr int kAtomSfts = 8;      // SFTs of a bin that a stretch must hold to count
 struct RangeInfo {
     int32_t flags;                // 1: non-finite values, 2: some value is no single-precision number
     int32_t pad;

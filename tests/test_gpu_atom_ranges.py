@@ -114,3 +114,51 @@ def test_antenna_products_of_no_antenna(ctx):
     got, n = slides(ctx, atoms, win)
     check_map(got, oracle.fmap_atoms(atoms, win), TOL["fp32"])
     assert not n
+
+
+@pytest.mark.parametrize("n_bins", [1, 3, 9])
+@pytest.mark.parametrize("sfts", [1, 7, 8])
+def test_stretches_of_a_few_sfts(ctx, n_bins, sfts):
+    """A last stretch of few SFTs has no level of its own: weak by 2^-13, seven
+    SFTs slide in double precision and eight do not."""
+    print("case: %d SFTs in the last stretch, %d bins" % (sfts, n_bins), flush=True)
+    base = tfsynth.make_atoms(9960 + n_bins, 64 * 20 + sfts, 0.0, n_bins=n_bins)
+    fa, fb = base.fa.copy(), base.fb.copy()
+    b = n_bins - 1
+    top = max(np.abs(fa[b]).max(), np.abs(fb[b]).max())
+    at = slice(64 * 20, None)
+    scale = 2.0 ** -13 * top / max(np.abs(fa[b, at]).max(), np.abs(fb[b, at]).max())
+    fa[b, at] = (fa[b, at] * scale).astype(np.float32)
+    fb[b, at] = (fb[b, at] * scale).astype(np.float32)
+    # (every one of them above the single slots' bound, 2^-18)
+    low = np.maximum(np.abs(fa[b, at]).max(axis=1), np.abs(fb[b, at]).max(axis=1))
+    fa[b, at, 0] = np.where(low < 2.0 ** -17 * top, np.float32(2.0 ** -16 * top), fa[b, at, 0])
+    atoms = dataclasses.replace(base, fa=fa, fb=fb)
+    win = tfsynth.list_window("exp", np.arange(1200, 1280) * T, np.arange(1, 40) * T)
+    got, n = slides(ctx, atoms, win, "fp64")
+    check_map(got, oracle.fmap_atoms(atoms, win), TOL["fp64"])
+    assert n == (sfts < 8)
+    assert slides(ctx, atoms, win, "fp32")[1]
+
+
+@pytest.mark.parametrize("n_bins", [1, 2, 8])
+@pytest.mark.parametrize("sfts", [7, 8])
+def test_a_column_of_a_few_sfts(ctx, n_bins, sfts):
+    """SFTs far apart, a few a stretch, one column of one stretch 2^-24 below
+    its largest as chance has it: the others bound what is left behind.  Seven
+    SFTs slide, eight (a level of their own) do not."""
+    print("case: one column of %d SFTs, %d bins" % (sfts, n_bins), flush=True)
+    slots = 64 * 12
+    base = tfsynth.make_atoms(9980 + n_bins, slots, 0.0, n_bins=n_bins)
+    on = np.arange(slots) % 64 < sfts
+    fa, fb = (np.where(on[None, :, None], x, 0.0).astype(np.float32) for x in (base.fa, base.fb))
+    at = slice(64 * 5, 64 * 6)
+    scale = 2.0 ** -24 * np.abs(fb[-1, :, 1]).max() / np.abs(fb[-1, at, 1]).max()
+    fb[-1, at, 1] = (fb[-1, at, 1] * scale).astype(np.float32)
+    abc = {name: np.where(on, getattr(base, name), 0.0) for name in ("a2", "b2", "ab")}
+    atoms = dataclasses.replace(base, fa=fa, fb=fb, **abc)
+    win = tfsynth.list_window("exp", np.arange(250, 450) * T, np.arange(1, 40) * T)
+    for prec in ("fp32", "fp64"):
+        got, n = slides(ctx, atoms, win, prec)
+        check_map(got, oracle.fmap_atoms(atoms, win), TOL[prec])
+        assert n == (sfts < 8), prec
